@@ -331,6 +331,7 @@ struct pic_ctx {
     uint32_t all_species;   // mask of every species
     uint32_t pushed;        // species pushed in the current step
     uint32_t launch_mask;   // species of the next launch (Params::species_mask)
+    bool step_b;            // the next push leaves B after both half updates in the scratch planes
     uint8_t *scratch;       // this device's static scratch (pic_diagnostics_static)
 };
 
@@ -460,6 +461,7 @@ struct Impl {
     static pic_status push_launch(pic_ctx *x)
     {
         Params<R> p = params<R>(x);
+        if (x->step_b) p.bnext = reinterpret_cast<R *>(x->ws + x->L.off_jtmp);
         size_t lds = push_lds(x, FUSED, sizeof(A));
         dim3 b(x->block);
         const int64_t items = x->L.pub.tiles_total * x->ns;
@@ -553,6 +555,17 @@ struct Impl {
             hipLaunchKernelGGL((pic::k_fold<R, D, true>), g, dim3(256), 0, x->stream, p, (R)x->c);
         else
             hipLaunchKernelGGL((pic::k_fold<R, D, false>), g, dim3(256), 0, x->stream, p, R(0));
+        HIP_OK(hipGetLastError());
+        return PIC_OK;
+    }
+
+    // after the push of a whole step (step_b): fold, E update, B and arrivals
+    static pic_status finish_step(pic_ctx *x)
+    {
+        Params<R> p = params<R>(x);
+        p.bnext = reinterpret_cast<R *>(x->ws + x->L.off_jtmp);
+        const dim3 g((unsigned)(x->L.pub.tiles_total * (1 + x->ns)));
+        hipLaunchKernelGGL((pic::k_finish_step<R, D>), g, dim3(256), 0, x->stream, p, (R)x->c);
         HIP_OK(hipGetLastError());
         return PIC_OK;
     }
@@ -889,6 +902,7 @@ pic_status do_init(pic_ctx *x, const int64_t *counts, const pic_init_data *in) {
 pic_status do_fdtd(pic_ctx *x, int phase) { PIC_DISPATCH(x, fdtd(x, phase)); }
 pic_status do_push(pic_ctx *x, bool fused, bool halfb) { PIC_DISPATCH(x, push(x, fused, halfb)); }
 pic_status do_deposit(pic_ctx *x, bool unfused, bool curl_e) { PIC_DISPATCH(x, deposit(x, unfused, curl_e)); }
+pic_status do_finish_step(pic_ctx *x) { PIC_DISPATCH(x, finish_step(x)); }
 pic_status do_migrate(pic_ctx *x, bool out, bool in, bool sort, int32_t *mc, int64_t *fl, int64_t fcap)
 {
     PIC_DISPATCH(x, migrate(x, out, in, sort, mc, fl, fcap));
@@ -1014,6 +1028,7 @@ pic_status pic_init_tiles(const pic_config *cfg, const int64_t *counts, void *wo
     x->all_species = (1u << x->ns) - 1u;
     x->pushed = 0;
     x->launch_mask = x->all_species;
+    x->step_b = false;
     const Layout &L = x->L;
     auto cleanup = [&](pic_status s) {
         delete x;
@@ -1147,6 +1162,24 @@ pic_status pic_step(pic_ctx *x, uint32_t flags)
     if (x->order == 4) flags &= ~PIC_PUSH_HALF_B;   // the in-LDS half update is second order
     flags &= ~PIC_DEPOSIT_CURL_E;                    // chosen below
     if (flags & PIC_PUSH_HALF_B) {
+        if ((flags & PIC_FUSED) && x->order == 2 && !x->filter_passes && x->state == 0) {
+            // two launches: the push, which also leaves B after both half
+            // updates in the filter's scratch planes, and the rest of the
+            // step.  After the push, half B, fold with E and migration as
+            // launches of their own took 12.6 us (1D, 512 cells FP64), 17 us
+            // (2D 256^2 FP32), 69 us (2D 1024^2 FP32) and 126 us (3D
+            // 256x64x64 with walls FP32), the one launch 4.0, 5.9, 54.6 and
+            // 89 us.  FDTD4 and the current filter, whose rows come between,
+            // keep the separate launches.
+            x->step_b = true;
+            st = pic_push_interp(x, PIC_ALL_SPECIES, flags);
+            x->step_b = false;
+            if (st || (st = do_finish_step(x))) return st;
+            x->state = 0;
+            x->pushed = 0;
+            ++x->steps;
+            return flags & PIC_SORT_CELLS ? do_migrate(x, false, false, true, nullptr, nullptr, 0) : PIC_OK;
+        }
         // push_half_b1 happens inside the push on its LDS copy of B; both
         // half updates are then applied to the stored B in one pass
         if ((st = pic_push_interp(x, PIC_ALL_SPECIES, flags))) return st;

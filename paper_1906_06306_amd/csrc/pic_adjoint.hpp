@@ -297,7 +297,7 @@ __global__ void __launch_bounds__(256) k_adj_push(Params<R> p, AdjParams<R> a)
     for (int k = threadIdx.x; k < 3 * cb.n; k += blockDim.x) aE[k] = 0.0;
     for (int k = threadIdx.x; k < 3 * fb.n; k += blockDim.x) aB[k] = 0.0;
     __syncthreads();
-    half_b_lds<R, D>(sB, fb, sE, cb, R(0.5) * p.c);   // B^n, as the push saw it
+    half_b_lds<R, D>(sB, fb, sE, cb, R(0.5) * p.c, td, p.T, nullptr, 0);   // B^n, as the push saw it
     __syncthreads();
     const R c = p.c, inv_c = p.inv_c;
     const int64_t cap = p.cap_total;

@@ -65,6 +65,7 @@ struct Params {
     int32_t *ob_ids;          // [tile*species][ob_cap] origin of each leaver
     int32_t *ob_boff;         // [tile*species][ncodes+1] outbox bucket starts by direction code
     int32_t *ob_idx;          // [tile*species][ob_cap] outbox slots in bucket order
+    R *bnext;                 // [3][cells_total] B after both half updates (whole step), or null
 };
 
 enum : int32_t { ERR_CAPACITY = 1, ERR_CFL = 2, ERR_NONFINITE = 4, ERR_OUT_OF_TILE = 8, ERR_ADJ_MAP = 16 };
@@ -94,6 +95,11 @@ __device__ __forceinline__ int xcd_tile(int b, int n)
 // both far below 2^23): v_mul_i32_i24 issues at the full VALU rate, the
 // 32-bit v_mul_lo_u32 at a quarter of it.
 __device__ __forceinline__ int imul24(int a, int b) { return (int)__umul24((unsigned)a, (unsigned)b); }
+
+// k / n for a cell index inside a tile (k and n far below 2^20), from
+// inv = 1.0f / n: (k + 1/2) / n lies at least 1/(2n) from an integer, more
+// than the rounding of the product, so the truncation is exact.
+__device__ __forceinline__ int div_small(int k, float inv) { return (int)(((float)k + 0.5f) * inv); }
 
 // Loads and stores at a 32-bit byte offset from a uniform base pointer: the
 // memory instruction adds the 64-bit scalar base and the 32-bit vector
@@ -228,8 +234,13 @@ __device__ __forceinline__ void stage_block(const R *__restrict__ src, int64_t N
 
 // First half of the B advance (push_half_b1) applied to the LDS copy of B:
 // B -= h curl+ E on local cells -1..T, from the staged E (cells -1..T+1).
+// With bnext, the tile's own cells also get their second half (push_half_b2,
+// the same E) and go to the planes bnext: the stored B must stay as it is
+// until every work-group has staged its halo, and the E update, which needs
+// B after both halves, runs in the next launch.
 template <typename R, int D>
-__device__ __forceinline__ void half_b_lds(R *sB, const FieldBox<D> &fb, const R *sE, const CurBox<D> &cb, R h)
+__device__ __forceinline__ void half_b_lds(R *sB, const FieldBox<D> &fb, const R *sE, const CurBox<D> &cb, R h,
+                                           const TileDesc &td, const int32_t T[3], R *bnext, int64_t N)
 {
     for (int k = threadIdx.x; k < fb.n; k += blockDim.x) {
         const int lx = k % fb.e0, ly = (k / fb.e0) % fb.e1, lz = k / (fb.e0 * fb.e1);
@@ -240,9 +251,21 @@ __device__ __forceinline__ void half_b_lds(R *sB, const FieldBox<D> &fb, const R
         const R cx = (Ez[e + jp] - ez) - (Ey[e + kp] - ey);
         const R cy = (Ex[e + kp] - ex) - (Ez[e + ip] - ez);
         const R cz = (Ey[e + ip] - ey) - (Ex[e + jp] - ex);
-        sB[k] -= h * cx;
-        sB[fb.n + k] -= h * cy;
-        sB[2 * fb.n + k] -= h * cz;
+        const R bx = fma(-h, cx, sB[k]), by = fma(-h, cy, sB[fb.n + k]), bz = fma(-h, cz, sB[2 * fb.n + k]);
+        sB[k] = bx;
+        sB[fb.n + k] = by;
+        sB[2 * fb.n + k] = bz;
+        if (bnext) {
+            const int ox = lx - 1, oy = D > 1 ? ly - 1 : 0, oz = D > 2 ? lz - 1 : 0;
+            if (ox >= 0 && ox < T[0] && (D < 2 || (oy >= 0 && oy < T[1])) && (D < 3 || (oz >= 0 && oz < T[2]))) {
+                const int64_t g = td.cell0 + td.tc[0] * T[0] + ox +
+                                  (int64_t)td.n[0] * ((D > 1 ? td.tc[1] * T[1] + oy : 0) +
+                                                      (int64_t)td.n[1] * (D > 2 ? td.tc[2] * T[2] + oz : 0));
+                bnext[g] = fma(-h, cx, bx);
+                bnext[N + g] = fma(-h, cy, by);
+                bnext[2 * N + g] = fma(-h, cz, bz);
+            }
+        }
     }
 }
 

@@ -318,7 +318,7 @@ __device__ __forceinline__ void push_tile(const Params<R> &p, const int w, unsig
     }
     __syncthreads();
     if constexpr (HALFB) {
-        half_b_lds<R, D>(sB, fb, sE, cb, R(0.5) * p.c);
+        half_b_lds<R, D>(sB, fb, sE, cb, R(0.5) * p.c, td, T, s == 0 ? p.bnext : nullptr, p.cells_total);
         __syncthreads();
     }
     if constexpr (WALLS) {
@@ -634,8 +634,8 @@ __global__ void __launch_bounds__(1024) k_deposit(Params<R> p)
 // cell below along each axis a (bm[a]; the cell itself along axes at or
 // beyond D), periodic inside the box.
 template <typename R, int D>
-__device__ __forceinline__ void load_e_update(const Params<R> &p, const TileDesc &td, int gx, int gy, int gz,
-                                              int64_t g, R e[3], R b[3], R bm[3][3])
+__device__ __forceinline__ void load_e_update(const Params<R> &p, const R *B, const TileDesc &td, int gx, int gy,
+                                              int gz, int64_t g, R e[3], R b[3], R bm[3][3])
 {
     const int64_t N = p.cells_total;
     const int n0 = td.n[0], n1 = td.n[1], n2 = td.n[2];
@@ -645,15 +645,15 @@ __device__ __forceinline__ void load_e_update(const Params<R> &p, const TileDesc
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         e[c] = p.E[c * N + g];
-        b[c] = p.B[c * N + g];
+        b[c] = B[c * N + g];
     }
     // the six neighbour values the curl uses
-    bm[0][1] = p.B[N + m[0]];
-    bm[0][2] = p.B[2 * N + m[0]];
-    bm[1][0] = p.B[m[1]];
-    bm[1][2] = p.B[2 * N + m[1]];
-    bm[2][0] = p.B[m[2]];
-    bm[2][1] = p.B[N + m[2]];
+    bm[0][1] = B[N + m[0]];
+    bm[0][2] = B[2 * N + m[0]];
+    bm[1][0] = B[m[1]];
+    bm[1][2] = B[2 * N + m[1]];
+    bm[2][0] = B[m[2]];
+    bm[2][1] = B[N + m[2]];
 }
 
 // E += h curl- B at one cell with the second-order backward differences of
@@ -685,7 +685,7 @@ __device__ __forceinline__ void curl_b_update_e(const Params<R> &p, const TileDe
                                                 int64_t g, R h, const R j[3])
 {
     R e[3], b[3], bm[3][3];
-    load_e_update<R, D>(p, td, gx, gy, gz, g, e, b, bm);
+    load_e_update<R, D>(p, p.B, td, gx, gy, gz, g, e, b, bm);
     update_e_cell<R, D, SUB_J>(p, td, gx, g, h, j, e, b, bm);
 }
 
@@ -724,27 +724,32 @@ __device__ __forceinline__ void update_b_cell(const Params<R> &p, const TileDesc
 // cur_exchange: J on the lattice = sum of the current blocks (one per
 // species of species_mask) of the tile and of its neighbours whose halo covers the cell, in
 // a fixed order (species, then neighbour offsets ascending, z major).  A
-// block covers local cells -1..T+1, so along each dimension a cell is
-// covered by its own tile and, for l < 2, the tile below or, for l = T-1,
-// the tile above (edges T >= 4); a cell loads the blocks that cover it
-// (interior cells their own tile's alone), and an uncovered combination
-// adds 0.  Edges of 2 take the general loop.  With CURL_E the same pass
+// block covers local cells -1..T+1, so along each dimension the tile below
+// covers l < 2 and the tile above l = T-1.  The neighbours are walked one by
+// one: a neighbour's block is the same for the whole work-group, so its
+// address is scalar, a lane adds a 32-bit offset, and lanes (mostly whole
+// waves) that the block does not cover skip the load.  One z layer of
+// neighbours (9 blocks x 3 components) is in flight at a time.  With CURL_E the same pass
 // also applies E += h curl- B - J to the cell (push_e and add_cur after the
 // second half update of B), from the folded values still in registers: J
 // is written once and not read back.
-template <typename R, int D, bool CURL_E>
-__global__ void __launch_bounds__(256) k_fold(Params<R> p, R h)
+//
+// NEXT_B: B after both half updates is read from p.bnext, where the push of
+// a whole step left it, and the cell's own value is stored to B as well (no
+// other work-group of the launch reads B).
+template <typename R, int D, bool CURL_E, bool NEXT_B>
+__device__ __forceinline__ void fold_tile(const Params<R> &p, R h, const int t)
 {
-    const int t = xcd_tile(blockIdx.x, gridDim.x);
     const TileDesc td = p.tiles[t];
     const CurBox<D> cb(p.T);
     const int T0 = p.T[0], T1 = D > 1 ? p.T[1] : 1, T2 = D > 2 ? p.T[2] : 1;
     const int ncell = T0 * T1 * T2;
-    bool small = false;
-#pragma unroll
-    for (int d = 0; d < D; ++d) small = small || p.T[d] < 4;
+    const float inv0 = 1.0f / T0, inv1 = 1.0f / T1;
+    const int e1 = cb.e0, e2 = cb.e0 * cb.e1;
+    const int64_t blk_len = 3 * (int64_t)cb.n;
     for (int k = threadIdx.x; k < ncell; k += blockDim.x) {
-        const int l[3] = {k % T0, (k / T0) % T1, k / (T0 * T1)};
+        const int r = D > 1 ? div_small(k, inv0) : 0, lz = D > 2 ? div_small(r, inv1) : 0;
+        const int l[3] = {D > 1 ? k - r * T0 : k, D > 2 ? r - lz * T1 : r, lz};
         const int gx = td.tc[0] * T0 + l[0];
         const int gy = D > 1 ? td.tc[1] * T1 + l[1] : 0;
         const int gz = D > 2 ? td.tc[2] * T2 + l[2] : 0;
@@ -753,93 +758,73 @@ __global__ void __launch_bounds__(256) k_fold(Params<R> p, R h)
         // the compiler may not move them across), all of the cell's loads are
         // in flight together
         R ee[3], eb[3], ebm[3][3];
-        if constexpr (CURL_E) load_e_update<R, D>(p, td, gx, gy, gz, g, ee, eb, ebm);
+        if constexpr (CURL_E) load_e_update<R, D>(p, NEXT_B ? p.bnext : p.B, td, gx, gy, gz, g, ee, eb, ebm);
         R acc[3] = {0, 0, 0};
-        if (!small) {
-            // per dimension: offsets o0 < o1 and whether o1 covers the cell
-            int o0[3] = {0, 0, 0}, o1[3] = {0, 0, 0};
-            bool v1[3] = {false, false, false};
+        // the cell in its own tile's block, and per dimension whether the
+        // tile below or above covers it
+        const uint32_t own = (uint32_t)(l[0] + 1 + (D > 1 ? imul24(l[1] + 1, e1) : 0) +
+                                        (D > 2 ? imul24(l[2] + 1, e2) : 0)) * (uint32_t)sizeof(R);
+        bool cov[2][3];
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
-                const bool low = l[d] < 2;
-                o0[d] = low ? -1 : 0;
-                o1[d] = low ? 0 : 1;
-                v1[d] = low || l[d] >= p.T[d] - 1;
-            }
-            constexpr int NCOMB = 1 << D;
-            int idx[NCOMB];
-            int64_t base[NCOMB];
-            bool ok[NCOMB];
+        for (int d = 0; d < (D < 2 ? D : 2); ++d) {
+            cov[d][0] = l[d] < 2;
+            cov[d][1] = true;
+            cov[d][2] = l[d] >= p.T[d] - 1;
+        }
+        for (int sp = 0; sp < p.nspecies; ++sp) {
+            if (!((p.species_mask >> sp) & 1u)) continue;
+#pragma unroll 1
+            for (int oz = 0; oz < (D > 2 ? 3 : 1); ++oz) {
+                constexpr int NY = D > 1 ? 3 : 1;
+                const int wz = td.tc[2] + oz - 1;
+                const int nz = D > 2 ? (wz < 0 ? wz + td.nt[2] : (wz >= td.nt[2] ? wz - td.nt[2] : wz)) : 0;
+                if (D > 2 && !(oz == 0 ? l[2] < 2 : (oz == 1 || l[2] >= T2 - 1))) continue;
+                R v[NY][3][3];
 #pragma unroll
-            for (int cmb = 0; cmb < NCOMB; ++cmb) {
-                int bi[3] = {0, 0, 0}, nc[3] = {0, 0, 0};
-                bool valid = true;
+                for (int oy = 0; oy < NY; ++oy) {
+                    const int wy = td.tc[1] + oy - 1;
+                    const int ny = D > 1 ? (wy < 0 ? wy + td.nt[1] : (wy >= td.nt[1] ? wy - td.nt[1] : wy)) : 0;
 #pragma unroll
-                for (int d = 0; d < D; ++d) {
-                    const bool hi = (cmb >> d) & 1;
-                    const int o = hi ? o1[d] : o0[d];
-                    valid = valid && (!hi || v1[d]);
-                    bi[d] = l[d] - o * p.T[d] + 1;
-                    const int v = td.tc[d] + o;    // neighbour tile, periodic
-                    nc[d] = v < 0 ? v + td.nt[d] : (v >= td.nt[d] ? v - td.nt[d] : v);
-                }
-                ok[cmb] = valid;
-                // an uncovered combination reads the tile's own entry and adds 0
-                const int nid = valid ? td.tile0 + nc[0] + td.nt[0] * (nc[1] + td.nt[1] * nc[2]) : t;
-                idx[cmb] = valid ? bi[0] + cb.e0 * (bi[1] + cb.e1 * bi[2])
-                                 : l[0] + 1 + cb.e0 * ((D > 1 ? l[1] + 1 : 0) + cb.e1 * (D > 2 ? l[2] + 1 : 0));
-                base[cmb] = (int64_t)nid * p.nspecies;
-            }
-            for (int sp = 0; sp < p.nspecies; ++sp) {
-                if (!((p.species_mask >> sp) & 1u)) continue;
-                R v[NCOMB][3];
+                    for (int ox = 0; ox < 3; ++ox) {
+                        const int wx = td.tc[0] + ox - 1;
+                        const int nx = wx < 0 ? wx + td.nt[0] : (wx >= td.nt[0] ? wx - td.nt[0] : wx);
+                        const int nid = td.tile0 + nx + td.nt[0] * (ny + td.nt[1] * nz);
+                        // the neighbour's block, shifted so that the cell's
+                        // entry lies at the same offset as in its own block
+                        const int shift = (ox - 1) * T0 + (D > 1 ? (oy - 1) * T1 * e1 : 0) +
+                                          (D > 2 ? (oz - 1) * T2 * e2 : 0);
+                        const R *blk = p.jblk + (((int64_t)nid * p.nspecies + sp) * blk_len - shift);
 #pragma unroll
-                for (int cmb = 0; cmb < NCOMB; ++cmb) {
-                    const R *blk = p.jblk + (base[cmb] + sp) * 3 * cb.n + idx[cmb];
+                        for (int m = 0; m < 3; ++m) v[oy][ox][m] = R(0);
+                        if (cov[0][ox] && (D < 2 || cov[1][oy])) {
 #pragma unroll
-                    for (int m = 0; m < 3; ++m) v[cmb][m] = R(0);
-                    if (cmb == 0 || ok[cmb]) {
-#pragma unroll
-                        for (int m = 0; m < 3; ++m) v[cmb][m] = blk[m * cb.n];
+                            for (int m = 0; m < 3; ++m) v[oy][ox][m] = ld_off(blk + m * cb.n, own);
+                        }
                     }
                 }
 #pragma unroll
-                for (int cmb = 0; cmb < NCOMB; ++cmb) {
+                for (int oy = 0; oy < NY; ++oy)
 #pragma unroll
-                    for (int m = 0; m < 3; ++m) acc[m] += ok[cmb] ? v[cmb][m] : R(0);
-                }
-            }
-        } else {
-            for (int sp = 0; sp < p.nspecies; ++sp) {
-                if (!((p.species_mask >> sp) & 1u)) continue;
-                for (int oz = (D > 2 ? -1 : 0); oz <= (D > 2 ? 1 : 0); ++oz)
-                    for (int oy = (D > 1 ? -1 : 0); oy <= (D > 1 ? 1 : 0); ++oy)
-                        for (int ox = -1; ox <= 1; ++ox) {
-                            const int o[3] = {ox, oy, oz};
-                            int bi[3] = {0, 0, 0}, nc[3] = {0, 0, 0};
-                            bool in = true;
+                    for (int ox = 0; ox < 3; ++ox)
 #pragma unroll
-                            for (int d = 0; d < D; ++d) {
-                                bi[d] = l[d] - o[d] * p.T[d] + 1;
-                                in = in && bi[d] >= 0 && bi[d] < p.T[d] + 3;
-                                const int v = td.tc[d] + o[d];
-                                nc[d] = v < 0 ? v + td.nt[d] : (v >= td.nt[d] ? v - td.nt[d] : v);
-                            }
-                            if (!in) continue;
-                            const int nid = td.tile0 + nc[0] + td.nt[0] * (nc[1] + td.nt[1] * nc[2]);
-                            const int idx = bi[0] + cb.e0 * (bi[1] + cb.e1 * bi[2]);
-                            const R *blk = p.jblk + ((int64_t)nid * p.nspecies + sp) * 3 * cb.n;
-                            acc[0] += blk[idx];
-                            acc[1] += blk[cb.n + idx];
-                            acc[2] += blk[2 * cb.n + idx];
-                        }
+                        for (int m = 0; m < 3; ++m) acc[m] += v[oy][ox][m];
             }
         }
         p.J[g] = acc[0];
         p.J[p.cells_total + g] = acc[1];
         p.J[2 * p.cells_total + g] = acc[2];
         if constexpr (CURL_E) update_e_cell<R, D, true>(p, td, gx, g, h, acc, ee, eb, ebm);
+        if constexpr (NEXT_B) {
+#pragma unroll
+            for (int m = 0; m < 3; ++m) p.B[m * p.cells_total + g] = eb[m];
+        }
     }
+}
+
+template <typename R, int D, bool CURL_E>
+__global__ void __launch_bounds__(256) k_fold(Params<R> p, R h)
+{
+    fold_tile<R, D, CURL_E, false>(p, h, xcd_tile(blockIdx.x, gridDim.x));
 }
 
 // ---------------------------------------------------------------- fields
@@ -1025,14 +1010,12 @@ __global__ void __launch_bounds__(1024) k_migrate_bucket(Params<R> p)
 // bucket for that code, in the neighbour's order).  The buckets of all
 // neighbours are walked as one index space (direction-major).
 template <typename R, int D>
-__global__ void __launch_bounds__(1024) k_migrate_in(Params<R> p)
+__device__ __forceinline__ void receive_segment(const Params<R> &p, const int ts)
 {
     constexpr int NC = ncodes<D>();
     __shared__ int sOff[NC + 1];
     __shared__ int sSrc[NC];
     __shared__ int sB0[NC];
-    // one work-group per (tile, species) segment
-    const int ts = xcd_tile(blockIdx.x, gridDim.x);
     const int t = ts / p.nspecies, s = ts - t * p.nspecies;
     const TileDesc td = p.tiles[t];
     const int64_t cap = p.cap_total;
@@ -1058,12 +1041,13 @@ __global__ void __launch_bounds__(1024) k_migrate_in(Params<R> p)
                 }
                 const int sts = (td.tile0 + nc[0] + td.nt[0] * (nc[1] + td.nt[1] * nc[2])) * p.nspecies + s;
                 const int32_t *boff = p.ob_boff + (int64_t)sts * (NC + 1);
+                const int b0 = boff[code], b1 = boff[code + 1];   // both in flight before the LDS writes
                 sSrc[code] = sts;
-                sB0[code] = boff[code];
+                sB0[code] = b0;
                 // species not pushed in this step have no leavers (their
                 // bucket starts may be an earlier step's)
                 const bool pushed = (p.species_mask >> s) & 1u;
-                n_in = code == centre_code<D>() || !pushed ? 0 : boff[code + 1] - boff[code];
+                n_in = code == centre_code<D>() || !pushed ? 0 : b1 - b0;
             }
             int x = n_in;
 #pragma unroll
@@ -1085,15 +1069,25 @@ __global__ void __launch_bounds__(1024) k_migrate_in(Params<R> p)
                 if (sOff[mid + 1] <= e) code = mid + 1;
                 else hi = mid;
             }
-            const int64_t sts = sSrc[code];
-            const int64_t k = p.ob_idx[sts * p.ob_cap + sB0[code] + (e - sOff[code])];
+            const int64_t ob = (int64_t)sSrc[code] * p.ob_cap;
+            const int64_t k = p.ob_idx[ob + sB0[code] + (e - sOff[code])];
             const int dst = cnt + e;
             if (dst < scap) {
-                if (p.ids) p.ids[so + dst] = p.ob_ids[sts * p.ob_cap + k];
+                // every plane's load before the first store: the compiler
+                // keeps a load behind an earlier store that it cannot tell
+                // apart, and the planes then wait for one another
+                R x[3], u[3];
+                int32_t id = 0;
 #pragma unroll
-                for (int d = 0; d < D; ++d) p.pos[d * cap + so + dst] = p.ob_pos[sts * p.ob_cap * D + d * p.ob_cap + k];
+                for (int d = 0; d < D; ++d) x[d] = p.ob_pos[ob * D + d * p.ob_cap + k];
 #pragma unroll
-                for (int mm = 0; mm < 3; ++mm) p.u[mm * cap + so + dst] = p.ob_u[sts * p.ob_cap * 3 + mm * p.ob_cap + k];
+                for (int mm = 0; mm < 3; ++mm) u[mm] = p.ob_u[ob * 3 + mm * p.ob_cap + k];
+                if (p.ids) id = p.ob_ids[ob + k];
+#pragma unroll
+                for (int d = 0; d < D; ++d) p.pos[d * cap + so + dst] = x[d];
+#pragma unroll
+                for (int mm = 0; mm < 3; ++mm) p.u[mm * cap + so + dst] = u[mm];
+                if (p.ids) p.ids[so + dst] = id;
             } else {
                 errs |= ERR_CAPACITY;
             }
@@ -1101,6 +1095,24 @@ __global__ void __launch_bounds__(1024) k_migrate_in(Params<R> p)
         if (errs) latch(p.err, errs);
         if (threadIdx.x == 0) p.seg_cnt[ts] = min(cnt + total, scap);
     }
+}
+
+// one work-group per (tile, species) segment
+template <typename R, int D>
+__global__ void __launch_bounds__(1024) k_migrate_in(Params<R> p)
+{
+    receive_segment<R, D>(p, xcd_tile(blockIdx.x, gridDim.x));
+}
+
+// Everything of a whole step after its fused push, in one launch: the first
+// p.ntiles work-groups fold the current, advance E and store B (fold_tile),
+// the others receive their segment's arrivals.  The two touch no common
+// memory (blocks, E, B, J against outboxes and particles).
+template <typename R, int D>
+__global__ void __launch_bounds__(256) k_finish_step(Params<R> p, R h)
+{
+    if ((int)blockIdx.x < p.ntiles) fold_tile<R, D, true, true>(p, h, xcd_tile(blockIdx.x, p.ntiles));
+    else receive_segment<R, D>(p, xcd_tile(blockIdx.x - p.ntiles, gridDim.x - p.ntiles));
 }
 
 // Stable sort of every tile segment by cell index (x fastest).  Each wave
