@@ -23,11 +23,6 @@
 using pic::Params;
 using pic::TileDesc;
 
-// particles per thread per group in the fused push kernel
-#ifndef PUSH_UNROLL
-#define PUSH_UNROLL 1
-#endif
-
 namespace {
 
 // largest segment or outbox capacity: the push addresses slots by 32-bit
@@ -192,10 +187,9 @@ pic_status make_layout(const pic_config *c, const int64_t *counts, Layout &L)
     }
     if (L.max_ntb > (int64_t(1) << 24)) return fail(PIC_E_ARG, "a box has %lld tiles; at most 2^24 are supported", (long long)L.max_ntb);
     if (tiles > INT32_MAX / 8) return fail(PIC_E_ARG, "too many tiles");
-    // segment capacities: a multiple of the push kernel's group (threads x
-    // particles per thread), so every lane of the last group of a segment
-    // has a slot of its own to load from and store to
-    const int64_t group = (int64_t)PUSH_UNROLL * (c->block ? c->block : 256);
+    // segment capacities: a multiple of the push kernel's group (its threads),
+    // so every lane of the last group of a segment has a slot to load from
+    const int64_t group = c->block ? c->block : 256;
     double factor = c->capacity_factor > 0 ? c->capacity_factor : 1.25;
     L.seg_off.assign(tiles * ns, 0);
     L.seg_cap.assign(tiles * ns, 0);
@@ -414,15 +408,24 @@ pic_status fill(pic_ctx *x, T *p, int64_t n, T v)
 
 template <typename R, int D>
 struct Impl {
-    static size_t push_lds(pic_ctx *x, bool fused, size_t acc_bytes)
+    // LDS of the push (layout: push_tile), and the choice of the layout for
+    // tiles with runtime edges: the interleaved rows unless they do not fit
+    template <int TC>
+    static size_t push_lds(pic_ctx *x, Params<R> &p, bool fused, size_t acc_bytes)
     {
-        int64_t fbn = 1, cbn = 1;
-        for (int d = 0; d < D; ++d) {
-            fbn *= x->T[d] + 2;
-            cbn *= x->T[d] + 3;
-        }
-        return (3 * cbn + 3 * fbn) * sizeof(R) + (fused ? 3 * cbn * acc_bytes : 0) +
-               (2 * PUSH_UNROLL * pic::MAX_WAVES + 4 + (fused ? pic::bucket_lds_ints<D>() : 0)) * sizeof(int);
+        int64_t fbn = 1, rows = 1, e0 = x->T[0] + 3;
+        for (int d = 0; d < D; ++d) fbn *= x->T[d] + 2;
+        for (int d = 1; d < D; ++d) rows *= x->T[d] + 3;
+        const size_t tail = fused ? pic::push_lds_tail<D, true>() : pic::push_lds_tail<D, false>();
+        const size_t cur = fused ? 3 * e0 * rows * acc_bytes : 0;
+        const size_t planes = (3 * e0 * rows + 3 * fbn) * sizeof(R) + cur + tail;
+        const size_t bytes = (D == 3 ? planes : 6 * e0 * rows * sizeof(R) + cur + tail) + (fused ? pic::dir_lds<D>() : 0);
+        p.dir_lds = pic::dir_lds<D>();
+        p.lds_planes = 0;
+        if (TC > 0 || bytes <= 160 * 1024) return bytes;
+        p.dir_lds = 0;
+        p.lds_planes = 1;
+        return planes;
     }
 
     template <int ORDER>
@@ -462,7 +465,7 @@ struct Impl {
     {
         Params<R> p = params<R>(x);
         if (x->step_b) p.bnext = reinterpret_cast<R *>(x->ws + x->L.off_jtmp);
-        size_t lds = push_lds(x, FUSED, sizeof(A));
+        size_t lds = push_lds<TC>(x, p, FUSED, sizeof(A));
         dim3 b(x->block);
         const int64_t items = x->L.pub.tiles_total * x->ns;
         if (x->capturing || x->order_age >= ORDER_EVERY) {
@@ -472,7 +475,7 @@ struct Impl {
         }
         ++x->order_age;
         if (x->persistent) {
-            auto kern = pic::k_push_persistent<R, D, FUSED, HALFB, A, PUSH_UNROLL, TC, WALLS, PUSHER>;
+            auto kern = pic::k_push_persistent<R, D, FUSED, HALFB, A, TC, WALLS, PUSHER>;
             pic_status st = set_lds(kern, lds);
             if (st) return st;
             int per_cu = 0;
@@ -483,7 +486,7 @@ struct Impl {
             if (st) return st;
             hipLaunchKernelGGL(kern, dim3((unsigned)grid), b, lds, x->stream, p);
         } else {
-            auto kern = pic::k_push<R, D, FUSED, HALFB, A, PUSH_UNROLL, TC, WALLS, PUSHER>;
+            auto kern = pic::k_push<R, D, FUSED, HALFB, A, TC, WALLS, PUSHER>;
             pic_status st = set_lds(kern, lds);
             if (st) return st;
             hipLaunchKernelGGL(kern, dim3((unsigned)items), b, lds, x->stream, p);
@@ -585,10 +588,14 @@ struct Impl {
             // one small work-group per (tile, species) segment: both kernels
             // are chains of dependent loads, so many resident groups pay
             const dim3 gs((unsigned)(x->L.pub.tiles_total * x->ns));
-            // the fused push buckets its own outbox; the unfused path (and a
-            // call that wants the migration counts) runs the bucket pass here
-            if (need_out || mig_counts)
+            // the fused push buckets its own outbox; the unfused path runs the
+            // bucket pass here (with the migration counts, if wanted)
+            if (need_out)
                 hipLaunchKernelGGL((pic::k_migrate_bucket<R, D>), gs, dim3(128), 0, x->stream, p);
+            else if (mig_counts)
+                hipLaunchKernelGGL((pic::k_migration_counts<R, D>),
+                                   dim3((unsigned)((x->L.pub.tiles_total * x->ns * pic::ncodes<D>() + 255) / 256)),
+                                   dim3(256), 0, x->stream, p);
             hipLaunchKernelGGL((pic::k_migrate_in<R, D>), gs, dim3(128), 0, x->stream, p);
             HIP_OK(hipGetLastError());
         }

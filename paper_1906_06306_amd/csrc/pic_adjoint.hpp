@@ -119,8 +119,8 @@ __device__ __forceinline__ void zigzag_adjoint(const LA *sLJ, const CurBox<D> &c
     for (int k = 0; k < NI; ++k) lin[k] = R(0);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const R la = (R)sLJ[b1 + seg_offset<D>(cb, v)];
-        const R lb = (R)sLJ[b2 + seg_offset<D>(cb, v)];
+        const R la = (R)sLJ[b1 + seg_offset<D>(cb.planes(), v)];
+        const R lb = (R)sLJ[b2 + seg_offset<D>(cb.planes(), v)];
 #pragma unroll
         for (int k = 0; k < NI; ++k) lin[k] += la * v1[v].d[k] + lb * v2[v].d[k];
     }
@@ -297,7 +297,7 @@ __global__ void __launch_bounds__(256) k_adj_push(Params<R> p, AdjParams<R> a)
     for (int k = threadIdx.x; k < 3 * cb.n; k += blockDim.x) aE[k] = 0.0;
     for (int k = threadIdx.x; k < 3 * fb.n; k += blockDim.x) aB[k] = 0.0;
     __syncthreads();
-    half_b_lds<R, D>(sB, fb, sE, cb, R(0.5) * p.c, td, p.T, nullptr, 0);   // B^n, as the push saw it
+    half_b_lds<R, D>(sB, fb.planes(), fb, sE, cb.planes(), R(0.5) * p.c, td, p.T, nullptr, 0);   // B^n, as the push saw it
     __syncthreads();
     const R c = p.c, inv_c = p.inv_c;
     const int64_t cap = p.cap_total;

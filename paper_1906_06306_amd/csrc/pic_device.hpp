@@ -65,6 +65,9 @@ struct Params {
     int32_t *ob_ids;          // [tile*species][ob_cap] origin of each leaver
     int32_t *ob_boff;         // [tile*species][ncodes+1] outbox bucket starts by direction code
     int32_t *ob_idx;          // [tile*species][ob_cap] outbox slots in bucket order
+    int32_t lds_planes;       // the push keeps E and B in LDS as planes of their own (tiles
+                              // whose interleaved rows would not fit), see FieldLds
+    int32_t dir_lds;          // leavers whose direction code the push keeps in LDS
     R *bnext;                 // [3][cells_total] B after both half updates (whole step), or null
 };
 
@@ -139,6 +142,18 @@ __device__ __forceinline__ bool near_face(const R x[3], const R band[3])
     return f;
 }
 
+// The same flag as a sign: the smallest distance to a cell face less the
+// band, <= 0 exactly when near_face holds (a difference of two floats has the
+// sign of their comparison).
+template <typename R, int D>
+__device__ __forceinline__ R face_distance(const R x[3], const R band[3])
+{
+    R m = fabs(x[0] - rint(x[0])) - band[0];
+#pragma unroll
+    for (int d = 1; d < D; ++d) m = fmin(m, fabs(x[d] - rint(x[d])) - band[d]);
+    return m;
+}
+
 __device__ __forceinline__ void latch(int32_t *err, int32_t bits)
 {
     atomicOr(err, bits);
@@ -186,6 +201,12 @@ __device__ __forceinline__ int fixed_exponent(R q)
     return q == R(0) ? 0 : 29 - ilogb(q);
 }
 
+// Strides of a block of vector components in LDS, in elements: from one
+// component to the next, along y and along z (along x: 1).
+struct Strides {
+    int m, y, z;
+};
+
 // Field halo block in LDS: local cells -1..T per grid dimension.
 template <int D>
 struct FieldBox {
@@ -198,6 +219,7 @@ struct FieldBox {
         e2 = ext<D>(T, 2, 2);
         n = e0 * e1 * e2;
     }
+    __device__ __forceinline__ Strides planes() const { return {n, e0, e0 * e1}; }
 };
 
 // Current halo block: local cells -1..T+1 per grid dimension.
@@ -212,23 +234,129 @@ struct CurBox {
         e2 = ext<D>(T, 2, 3);
         n = e0 * e1 * e2;
     }
+    // Strides of a block over these cells whose rows along x hold NC
+    // components one after another, [row][NC][e0]: component, y row, z layer.
+    template <int NC>
+    __device__ __forceinline__ Strides rows() const
+    {
+        return {e0, NC * e0, NC * e0 * e1};
+    }
+    // every component in a plane of its own, [3][n]
+    __device__ __forceinline__ Strides planes() const { return {n, e0, e0 * e1}; }
+    // the current block, in LDS and in memory
+    __device__ __forceinline__ Strides current() const { return rows<3>(); }
 };
 
-// Copy E (local cells -1..T+1) and B (local cells -1..T) of the tile into
-// LDS, periodic wrap.  sE layout [3][cb.n], sB layout [3][fb.n].
+// Where the push keeps E and B in LDS (elements of sF).  1D and 2D: rows of
+// all six components, [row][6][e0].  The components and the next row of a cell
+// then lie within the 255 elements that one LDS read pair reaches by its
+// immediate offsets, so a particle's 12 (2D) read pairs share four base
+// addresses (2D FP32 push: 331 VALU instructions per 64 particles against 371
+// with one plane per component).  3D: one plane per component.  A z layer
+// lies beyond those offsets in any case, and rows of 66 elements map an 8 x 8
+// plane of cells, which an ordered plasma keeps in one wave, onto few banks (8^3
+// tiles, FP32, walls: push 611 us with rows, 587 us with planes).  Planes
+// also in 2D tiles whose rows would not fit the 160 KB of LDS.
+template <int D>
+struct FieldLds {
+    Strides e, b;
+    int b0;          // offset of Bx's block
+    __device__ FieldLds(const CurBox<D> &cb, const FieldBox<D> &fb, bool planes)
+    {
+        e = b = cb.template rows<6>();
+        b0 = 3 * cb.e0;
+        if (planes) {
+            e = cb.planes();
+            b = fb.planes();
+            b0 = 3 * cb.n;
+        }
+    }
+};
+
+// Cell coordinates of entry k of a block of extents e0, e1 (x fastest).
+template <int D>
+__device__ __forceinline__ void cell_of(int k, int e0, int e1, float inv0, float inv1, int &lx, int &ly, int &lz)
+{
+    const int r = D > 1 ? div_small(k, inv0) : 0;
+    lz = D > 2 ? div_small(r, inv1) : 0;
+    lx = D > 1 ? k - imul24(r, e0) : k;
+    ly = D > 2 ? r - imul24(lz, e1) : r;
+}
+
+// Storage index of the cell at local coordinates lx-1.. of the tile; a halo
+// reaches at most one box length beyond the box (every edge is >= 2).
+template <int D>
+__device__ __forceinline__ int64_t halo_cell(const TileDesc &td, const int32_t T[3], int lx, int ly, int lz)
+{
+    int g[3] = {0, 0, 0};
+    const int l[3] = {lx, ly, lz};
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        const int v = td.tc[d] * T[d] + l[d] - 1;
+        g[d] = v < 0 ? v + td.n[d] : (v >= td.n[d] ? v - td.n[d] : v);
+    }
+    return td.cell0 + g[0] + (D > 1 ? (int64_t)td.n[0] * (D > 2 ? g[1] + (int64_t)td.n[1] * g[2] : g[1]) : 0);
+}
+
+// Copy three planes of the tile's halo block into LDS, periodic wrap; dst
+// layout [3][bx.n].
 template <typename R, int D, typename BoxT>
 __device__ __forceinline__ void stage_block(const R *__restrict__ src, int64_t N, const TileDesc &td,
                                             const int32_t T[3], R *dst, const BoxT &bx)
 {
-    const int n0 = td.n[0], n1 = td.n[1], n2 = td.n[2];
+    const float inv0 = 1.0f / bx.e0, inv1 = 1.0f / bx.e1;
     for (int k = threadIdx.x; k < bx.n; k += blockDim.x) {
-        int lx = k % bx.e0, ly = (k / bx.e0) % bx.e1, lz = k / (bx.e0 * bx.e1);
-        int gx = D > 0 ? wrapi(td.tc[0] * T[0] + lx - 1, n0) : 0;
-        int gy = D > 1 ? wrapi(td.tc[1] * T[1] + ly - 1, n1) : 0;
-        int gz = D > 2 ? wrapi(td.tc[2] * T[2] + lz - 1, n2) : 0;
-        int64_t g = td.cell0 + gx + (int64_t)n0 * (gy + (int64_t)n1 * gz);
+        int lx, ly, lz;
+        cell_of<D>(k, bx.e0, bx.e1, inv0, inv1, lx, ly, lz);
+        const int64_t g = halo_cell<D>(td, T, lx, ly, lz);
 #pragma unroll
         for (int m = 0; m < 3; ++m) dst[m * bx.n + k] = src[m * N + g];
+    }
+}
+
+// E (local cells -1..T+1) and B (local cells -1..T) of the tile into the LDS
+// block sF.  Two cells per thread and trip, all of their loads before the
+// first LDS write: the staging is one or two memory latencies.
+template <typename R, int D>
+__device__ __forceinline__ void stage_fields(const R *__restrict__ E, const R *__restrict__ B, int64_t N,
+                                             const TileDesc &td, const int32_t T[3], R *sF, const CurBox<D> &cb,
+                                             const FieldLds<D> &fl)
+{
+    constexpr int U = 2;
+    const float inv0 = 1.0f / cb.e0, inv1 = 1.0f / cb.e1;
+    for (int k0 = threadIdx.x; k0 < cb.n; k0 += U * blockDim.x) {
+        R v[U][6];
+        int at[U], bt[U];
+        bool inb[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int k = k0 + j * blockDim.x;
+            int lx, ly, lz;
+            cell_of<D>(k, cb.e0, cb.e1, inv0, inv1, lx, ly, lz);
+            at[j] = lx + imul24(ly, fl.e.y) + imul24(lz, fl.e.z);
+            bt[j] = lx + imul24(ly, fl.b.y) + imul24(lz, fl.b.z) + fl.b0;
+            inb[j] = k < cb.n && lx < T[0] + 2 && (D < 2 || ly < T[1] + 2) && (D < 3 || lz < T[2] + 2);
+            if (k < cb.n) {
+                const int64_t g = halo_cell<D>(td, T, lx, ly, lz);
+#pragma unroll
+                for (int m = 0; m < 3; ++m) v[j][m] = E[m * N + g];
+                if (inb[j]) {
+#pragma unroll
+                    for (int m = 0; m < 3; ++m) v[j][3 + m] = B[m * N + g];
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            if (k0 + j * (int)blockDim.x < cb.n) {
+#pragma unroll
+                for (int m = 0; m < 3; ++m) sF[at[j] + m * fl.e.m] = v[j][m];
+                if (inb[j]) {
+#pragma unroll
+                    for (int m = 0; m < 3; ++m) sF[bt[j] + m * fl.b.m] = v[j][3 + m];
+                }
+            }
+        }
     }
 }
 
@@ -239,28 +367,29 @@ __device__ __forceinline__ void stage_block(const R *__restrict__ src, int64_t N
 // until every work-group has staged its halo, and the E update, which needs
 // B after both halves, runs in the next launch.
 template <typename R, int D>
-__device__ __forceinline__ void half_b_lds(R *sB, const FieldBox<D> &fb, const R *sE, const CurBox<D> &cb, R h,
-                                           const TileDesc &td, const int32_t T[3], R *bnext, int64_t N)
+__device__ __forceinline__ void half_b_lds(R *sB, const Strides sb, const FieldBox<D> &fb, const R *sE,
+                                           const Strides se, R h, const TileDesc &td, const int32_t T[3], R *bnext,
+                                           int64_t N)
 {
+    const float inv0 = 1.0f / fb.e0, inv1 = 1.0f / fb.e1;
     for (int k = threadIdx.x; k < fb.n; k += blockDim.x) {
-        const int lx = k % fb.e0, ly = (k / fb.e0) % fb.e1, lz = k / (fb.e0 * fb.e1);
-        const int e = lx + cb.e0 * (ly + cb.e1 * lz);
-        const int ip = D > 0 ? 1 : 0, jp = D > 1 ? cb.e0 : 0, kp = D > 2 ? cb.e0 * cb.e1 : 0;
-        const R *Ex = sE, *Ey = sE + cb.n, *Ez = sE + 2 * cb.n;
+        int lx, ly, lz;
+        cell_of<D>(k, fb.e0, fb.e1, inv0, inv1, lx, ly, lz);
+        const int e = lx + imul24(ly, se.y) + imul24(lz, se.z), f = lx + imul24(ly, sb.y) + imul24(lz, sb.z);
+        const int ip = D > 0 ? 1 : 0, jp = D > 1 ? se.y : 0, kp = D > 2 ? se.z : 0;
+        const R *Ex = sE, *Ey = sE + se.m, *Ez = sE + 2 * se.m;
         const R ex = Ex[e], ey = Ey[e], ez = Ez[e];
         const R cx = (Ez[e + jp] - ez) - (Ey[e + kp] - ey);
         const R cy = (Ex[e + kp] - ex) - (Ez[e + ip] - ez);
         const R cz = (Ey[e + ip] - ey) - (Ex[e + jp] - ex);
-        const R bx = fma(-h, cx, sB[k]), by = fma(-h, cy, sB[fb.n + k]), bz = fma(-h, cz, sB[2 * fb.n + k]);
-        sB[k] = bx;
-        sB[fb.n + k] = by;
-        sB[2 * fb.n + k] = bz;
+        const R bx = fma(-h, cx, sB[f]), by = fma(-h, cy, sB[f + sb.m]), bz = fma(-h, cz, sB[f + 2 * sb.m]);
+        sB[f] = bx;
+        sB[f + sb.m] = by;
+        sB[f + 2 * sb.m] = bz;
         if (bnext) {
             const int ox = lx - 1, oy = D > 1 ? ly - 1 : 0, oz = D > 2 ? lz - 1 : 0;
             if (ox >= 0 && ox < T[0] && (D < 2 || (oy >= 0 && oy < T[1])) && (D < 3 || (oz >= 0 && oz < T[2]))) {
-                const int64_t g = td.cell0 + td.tc[0] * T[0] + ox +
-                                  (int64_t)td.n[0] * ((D > 1 ? td.tc[1] * T[1] + oy : 0) +
-                                                      (int64_t)td.n[1] * (D > 2 ? td.tc[2] * T[2] + oz : 0));
+                const int64_t g = halo_cell<D>(td, T, lx, ly, lz);
                 bnext[g] = fma(-h, cx, bx);
                 bnext[N + g] = fma(-h, cy, by);
                 bnext[2 * N + g] = fma(-h, cz, bz);
@@ -296,54 +425,61 @@ __device__ __forceinline__ void make_stencil(const R x[3], const int32_t T[3], S
     }
 }
 
-// Linear interpolation of component COMP (0..5 = Ex..Bz) from its own
-// staggered sub-lattice: per dimension the half-cell lattice is used where
-// the component is staggered by 1/2.
-template <typename R, int D, int COMP>
-__device__ __forceinline__ R interp_comp(const R *__restrict__ F, int s1, int s2, const Stencil<R, D> &st)
+// Linear interpolation at the LDS base b of one component (Ex..Bz, each from
+// its own staggered sub-lattice: per dimension the half-cell lattice is used
+// where the component is staggered by 1/2; weights w0, w1, w2 of the upper
+// corners).
+template <typename R, int D>
+__device__ __forceinline__ R interp_at(const R *F, int b, const Strides st, R w0, R w1, R w2)
 {
-    constexpr bool h0 = COMP == 0 || COMP == 4 || COMP == 5;
-    constexpr bool h1 = COMP == 1 || COMP == 3 || COMP == 5;
-    constexpr bool h2 = COMP == 2 || COMP == 3 || COMP == 4;
-    int b = h0 ? st.bh[0] : st.bn[0];
-    R w0 = h0 ? st.wh[0] : st.wn[0];
+    const R *f = F + b;
     if constexpr (D == 1) {
-        return F[b] * (R(1) - w0) + F[b + 1] * w0;
+        return f[0] * (R(1) - w0) + f[1] * w0;
+    } else if constexpr (D == 2) {
+        const R a0 = f[0] * (R(1) - w0) + f[1] * w0;
+        const R a1 = f[st.y] * (R(1) - w0) + f[st.y + 1] * w0;
+        return a0 * (R(1) - w1) + a1 * w1;
     } else {
-        b += imul24(h1 ? st.bh[1] : st.bn[1], s1);
-        R w1 = h1 ? st.wh[1] : st.wn[1];
-        if constexpr (D == 2) {
-            R a0 = F[b] * (R(1) - w0) + F[b + 1] * w0;
-            R a1 = F[b + s1] * (R(1) - w0) + F[b + s1 + 1] * w0;
-            return a0 * (R(1) - w1) + a1 * w1;
-        } else {
-            b += imul24(h2 ? st.bh[2] : st.bn[2], s2);
-            R w2 = h2 ? st.wh[2] : st.wn[2];
-            R a00 = F[b] * (R(1) - w0) + F[b + 1] * w0;
-            R a10 = F[b + s1] * (R(1) - w0) + F[b + s1 + 1] * w0;
-            R a01 = F[b + s2] * (R(1) - w0) + F[b + s2 + 1] * w0;
-            R a11 = F[b + s1 + s2] * (R(1) - w0) + F[b + s1 + s2 + 1] * w0;
-            R c0 = a00 * (R(1) - w1) + a10 * w1;
-            R c1 = a01 * (R(1) - w1) + a11 * w1;
-            return c0 * (R(1) - w2) + c1 * w2;
-        }
+        const R *g = f + st.z;
+        const R a00 = f[0] * (R(1) - w0) + f[1] * w0;
+        const R a10 = f[st.y] * (R(1) - w0) + f[st.y + 1] * w0;
+        const R a01 = g[0] * (R(1) - w0) + g[1] * w0;
+        const R a11 = g[st.y] * (R(1) - w0) + g[st.y + 1] * w0;
+        const R c0 = a00 * (R(1) - w1) + a10 * w1;
+        const R c1 = a01 * (R(1) - w1) + a11 * w1;
+        return c0 * (R(1) - w2) + c1 * w2;
     }
 }
 
+// E and B at a particle from the block stage_fields filled.  Per dimension
+// one node-centred and one half-cell base; a component's base is their sum.
 template <typename R, int D>
-__device__ __forceinline__ void interp_all(const R *sE, const CurBox<D> &cb, const R *sB, const FieldBox<D> &fb,
-                                           const R x[3], const int32_t T[3], R e[3], R b[3])
+__device__ __forceinline__ void interp_all(const R *sF, const FieldLds<D> &fl, const R x[3], const int32_t T[3],
+                                           R e[3], R b[3])
 {
-    Stencil<R, D> st;
-    make_stencil<R, D>(x, T, st);
-    const int e1 = cb.e0, e2 = cb.e0 * cb.e1;
-    const int f1 = fb.e0, f2 = fb.e0 * fb.e1;
-    e[0] = interp_comp<R, D, 0>(sE + 0 * cb.n, e1, e2, st);
-    e[1] = interp_comp<R, D, 1>(sE + 1 * cb.n, e1, e2, st);
-    e[2] = interp_comp<R, D, 2>(sE + 2 * cb.n, e1, e2, st);
-    b[0] = interp_comp<R, D, 3>(sB + 0 * fb.n, f1, f2, st);
-    b[1] = interp_comp<R, D, 4>(sB + 1 * fb.n, f1, f2, st);
-    b[2] = interp_comp<R, D, 5>(sB + 2 * fb.n, f1, f2, st);
+    int n[3] = {0, 0, 0}, h[3] = {0, 0, 0}, bn[3] = {0, 0, 0}, bh[3] = {0, 0, 0};
+    R wn[3] = {0, 0, 0}, wh[3] = {0, 0, 0};
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        const int s = d == 0 ? 1 : (d == 1 ? fl.e.y : fl.e.z), sb = d == 0 ? 1 : (d == 1 ? fl.b.y : fl.b.z);
+        const R f0 = floor(x[d]);
+        const int ci = (int)f0 + T[d] / 2 + 1;   // node-centred base: LDS offset of local cell -1 is 0
+        const R f = x[d] - f0;
+        const bool up = f >= R(0.5);
+        n[d] = d == 0 ? ci : imul24(ci, s);
+        h[d] = n[d] - (up ? 0 : s);
+        bn[d] = d == 0 ? ci : imul24(ci, sb);
+        bh[d] = bn[d] - (up ? 0 : sb);
+        wn[d] = f;
+        wh[d] = up ? f - R(0.5) : f + R(0.5);
+    }
+    const R *sB = sF + fl.b0;
+    e[0] = interp_at<R, D>(sF, h[0] + n[1] + n[2], fl.e, wh[0], wn[1], wn[2]);
+    e[1] = interp_at<R, D>(sF + fl.e.m, n[0] + h[1] + n[2], fl.e, wn[0], wh[1], wn[2]);
+    e[2] = interp_at<R, D>(sF + 2 * fl.e.m, n[0] + n[1] + h[2], fl.e, wn[0], wn[1], wh[2]);
+    b[0] = interp_at<R, D>(sB, bn[0] + bh[1] + bh[2], fl.b, wn[0], wh[1], wh[2]);
+    b[1] = interp_at<R, D>(sB + fl.b.m, bh[0] + bn[1] + bh[2], fl.b, wh[0], wn[1], wh[2]);
+    b[2] = interp_at<R, D>(sB + 2 * fl.b.m, bh[0] + bh[1] + bn[2], fl.b, wh[0], wh[1], wn[2]);
 }
 
 // ------------------------------------------------------------------ Boris
@@ -590,9 +726,9 @@ __device__ __forceinline__ void segment_weights(const R W[3], const R dv[3], R w
 // LDS offsets (relative to the segment's cell) of those values: component
 // plane offset plus corner offset.
 template <int D>
-__device__ __forceinline__ int seg_offset(const CurBox<D> &cb, int k)
+__device__ __forceinline__ int seg_offset(const Strides st, int k)
 {
-    const int s1 = cb.e0, s2 = cb.e0 * cb.e1, n = cb.n;
+    const int s1 = st.y, s2 = st.z, n = st.m;
     if constexpr (D == 1) {
         return k == 0 ? 0 : (k == 1 ? n : (k == 2 ? n + 1 : (k == 3 ? 2 * n : 2 * n + 1)));
     } else if constexpr (D == 2) {
@@ -627,12 +763,15 @@ __device__ __forceinline__ int seg_offset(const CurBox<D> &cb, int k)
 // ZigZag deposit (App. D) of one particle moving from x1 to x2 (tile-local,
 // unrebased) with displacement dv (all three components) and charge q.
 // Relay point per grid dimension: min(min(i1,i2)+1, max(max(i1,i2),
-// (x1+x2)/2)); along non-grid dimensions the two segments share dv/2.
+// (x1+x2)/2)) (App. D); along non-grid dimensions the two segments share dv/2.
 // When both segments lie in the same cell they touch the same points, so
 // their values are added in registers (F1 w1 + F2 w2, one multiply-add) and
 // written with one set of atomics.
+// The two cells of a grid dimension differ by at most one, so the relay point
+// is the midpoint when they are the same and the larger of the two cell
+// indices when not.  st: strides of the block sJ.
 template <typename R, int D, typename A>
-__device__ __forceinline__ void zigzag(A *sJ, const CurBox<D> &cb, const int32_t T[3], const R x1[3], const R x2[3],
+__device__ __forceinline__ void zigzag(A *sJ, const Strides st, const int32_t T[3], const R x1[3], const R x2[3],
                                        const R dv[3], R q)
 {
     R F1[3], F2[3], W1[3] = {0, 0, 0}, W2[3] = {0, 0, 0}, d1[3], d2[3];
@@ -641,16 +780,15 @@ __device__ __forceinline__ void zigzag(A *sJ, const CurBox<D> &cb, const int32_t
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         if (d < D) {
-            R a = x1[d], b = x2[d];
-            R fa = floor(a), fb = floor(b);
-            R lo = fmin(fa, fb), hi = fmax(fa, fb);
-            R xr = fmin(lo + R(1), fmax(hi, R(0.5) * (a + b)));
+            const R a = x1[d], b = x2[d];
+            const R fa = floor(a), fb = floor(b);
+            const R xr = fa == fb ? R(0.5) * (a + b) : (fa > fb ? fa : fb);
             d1[d] = xr - a;
             d2[d] = b - xr;
             F1[d] = q * d1[d];
             F2[d] = q * d2[d];
-            W1[d] = R(0.5) * (a + xr) - fa;
-            W2[d] = R(0.5) * (b + xr) - fb;
+            W1[d] = fma(R(0.5), a + xr, -fa);
+            W2[d] = fma(R(0.5), b + xr, -fb);
             l1[d] = (int)fa + T[d] / 2 + 1;
             l2[d] = (int)fb + T[d] / 2 + 1;
             same = same && fa == fb;
@@ -668,17 +806,16 @@ __device__ __forceinline__ void zigzag(A *sJ, const CurBox<D> &cb, const int32_t
     segment_weights<R, D>(W2, d2, w2);
 #pragma unroll
     for (int d = 0; d < 3; ++d) F2s[d] = same ? F2[d] : R(0);
-    const int s1 = cb.e0, s2 = cb.e0 * cb.e1;
-    const int b1 = l1[0] + (D > 1 ? imul24(l1[1], s1) : 0) + (D > 2 ? imul24(l1[2], s2) : 0);
+    const int b1 = l1[0] + (D > 1 ? imul24(l1[1], st.y) : 0) + (D > 2 ? imul24(l1[2], st.z) : 0);
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
         const int m = seg_comp<D>(k);
-        lds_add(sJ + b1 + seg_offset<D>(cb, k), fma(F2s[m], w2[k], F1[m] * w1[k]));
+        lds_add(sJ + b1 + seg_offset<D>(st, k), fma(F2s[m], w2[k], F1[m] * w1[k]));
     }
     if (!same) {
-        const int b2 = l2[0] + (D > 1 ? imul24(l2[1], s1) : 0) + (D > 2 ? imul24(l2[2], s2) : 0);
+        const int b2 = l2[0] + (D > 1 ? imul24(l2[1], st.y) : 0) + (D > 2 ? imul24(l2[2], st.z) : 0);
 #pragma unroll
-        for (int k = 0; k < NV; ++k) lds_add(sJ + b2 + seg_offset<D>(cb, k), F2[seg_comp<D>(k)] * w2[k]);
+        for (int k = 0; k < NV; ++k) lds_add(sJ + b2 + seg_offset<D>(st, k), F2[seg_comp<D>(k)] * w2[k]);
     }
 }
 
@@ -691,29 +828,30 @@ __device__ __forceinline__ void zigzag(A *sJ, const CurBox<D> &cb, const int32_t
 // column (local x = -1) and the high wall's column (local x = T) take the
 // image values.
 template <typename R, int D>
-__device__ __forceinline__ void wall_images(R *sE, const CurBox<D> &cb, R *sB, const FieldBox<D> &fb,
+__device__ __forceinline__ void wall_images(R *sF, const CurBox<D> &cb, const FieldBox<D> &fb, const FieldLds<D> &fl,
                                             const int32_t T[3], int walls)
 {
-    const int rows_e = cb.e1 * cb.e2, rows_b = fb.e1 * fb.e2;
-    for (int r = threadIdx.x; r < rows_e; r += blockDim.x) {
-        R *row = sE + r * cb.e0;
-        if (walls & 1) row[0] = row[1];                         // Ex(-1/2) = Ex(1/2)
+    for (int r = threadIdx.x; r < cb.e1 * cb.e2; r += blockDim.x) {
+        const int ly = r % cb.e1, lz = r / cb.e1, m = fl.e.m;
+        R *E = sF + ly * fl.e.y + lz * fl.e.z;
+        if (walls & 1) E[0] = E[1];                             // Ex(-1/2) = Ex(1/2)
         if (walls & 2) {
-            row[T[0] + 1] = row[T[0]];                          // Ex(n0+1/2) = Ex(n0-1/2)
-            row[cb.n + T[0] + 1] = R(0);                        // Ey, Ez on the wall plane
-            row[2 * cb.n + T[0] + 1] = R(0);
+            E[T[0] + 1] = E[T[0]];                              // Ex(n0+1/2) = Ex(n0-1/2)
+            E[m + T[0] + 1] = R(0);                             // Ey, Ez on the wall plane
+            E[2 * m + T[0] + 1] = R(0);
         }
     }
-    for (int r = threadIdx.x; r < rows_b; r += blockDim.x) {
-        R *row = sB + r * fb.e0;
+    for (int r = threadIdx.x; r < fb.e1 * fb.e2; r += blockDim.x) {
+        const int ly = r % fb.e1, lz = r / fb.e1, m = fl.b.m;
+        R *B = sF + fl.b0 + ly * fl.b.y + lz * fl.b.z;
         if (walls & 1) {
-            row[fb.n] = row[fb.n + 1];                          // By, Bz mirror
-            row[2 * fb.n] = row[2 * fb.n + 1];
+            B[m] = B[m + 1];                                    // By, Bz mirror
+            B[2 * m] = B[2 * m + 1];
         }
         if (walls & 2) {
-            row[T[0] + 1] = R(0);                               // Bx on the wall plane
-            row[fb.n + T[0] + 1] = row[fb.n + T[0]];
-            row[2 * fb.n + T[0] + 1] = row[2 * fb.n + T[0]];
+            B[T[0] + 1] = R(0);                                 // Bx on the wall plane
+            B[m + T[0] + 1] = B[m + T[0]];
+            B[2 * m + T[0] + 1] = B[2 * m + T[0]];
         }
     }
 }
@@ -723,7 +861,7 @@ __device__ __forceinline__ void wall_images(R *sE, const CurBox<D> &cb, R *sB, c
 // (two ZigZag moves, the non-grid displacement split in proportion), then
 // x2 and u_x are mirrored.  Returns false (nothing done) for other moves.
 template <typename R, int D, typename A>
-__device__ __forceinline__ bool wall_reflect(A *sJ, const CurBox<D> &cb, const int32_t T[3], int walls,
+__device__ __forceinline__ bool wall_reflect(A *sJ, const Strides st, const int32_t T[3], int walls,
                                              const R x1[3], R x2[3], R u[3], const R dv[3], R q)
 {
     const R half = R(T[0] / 2);
@@ -745,12 +883,18 @@ __device__ __forceinline__ bool wall_reflect(A *sJ, const CurBox<D> &cb, const i
     }
     r[0] = lo ? -R(T[0]) - x2[0] : R(T[0]) - x2[0];
     if (r[0] >= half) r[0] = nextafter(half, R(0));
-    zigzag<R, D, A>(sJ, cb, T, x1, w, dv1, q);
-    zigzag<R, D, A>(sJ, cb, T, w, r, dv2, q);
+    zigzag<R, D, A>(sJ, st, T, x1, w, dv1, q);
+    zigzag<R, D, A>(sJ, st, T, w, r, dv2, q);
 #pragma unroll
     for (int d = 0; d < D; ++d) x2[d] = r[d];
     u[0] = -u[0];
     return true;
+}
+
+template <int D>
+__host__ __device__ constexpr int centre_code()
+{
+    return D == 1 ? 1 : (D == 2 ? 4 : 13);
 }
 
 // Tile offset code sum (delta_d+1) 3^d of a position after the push.
@@ -768,10 +912,22 @@ __device__ __forceinline__ int direction_code(const R x[3], const int32_t T[3], 
     return code;
 }
 
-template <int D>
-__host__ __device__ constexpr int centre_code()
+// The same code, and the position rebased by -delta T, without comparisons
+// per face: the tile offset of the cell floor(x) is floor((cell + T/2) / T),
+// and (cell + T/2 + 1/2) / T stays 1/(2T) away from an integer, more than the
+// rounding of the product with 1/T.  Exact for any even T below 2^20.
+template <typename R, int D>
+__device__ __forceinline__ int rebase(const R x[3], const int32_t T[3], R xr[3])
 {
-    return D == 1 ? 1 : (D == 2 ? 4 : 13);
+    R code = R(0);
+#pragma unroll
+    for (int d = D - 1; d >= 0; --d) {
+        const R inv = R(1) / R(T[d]);
+        const R delta = floor(fma(floor(x[d]), inv, R(0.5) + R(0.5) * inv));
+        xr[d] = fma(-R(T[d]), delta, x[d]);
+        code = fma(code, R(3), delta);
+    }
+    return (int)code + centre_code<D>();
 }
 
 template <int D>

@@ -11,12 +11,6 @@ namespace pic {
 
 constexpr int MAX_WAVES = 16;
 
-// groups of particles the push loads ahead of the one it works on: one.  A
-// second group in flight (in registers, or in a second buffer of registers
-// the loop alternates) measured slower on the 2D FP32 push: the compiler's
-// waits for the alternate buffer come back, and the registers lower occupancy.
-constexpr int PUSH_PREFETCH = 1;
-
 // Inclusive prefix sum of v over each row of 16 lanes (DPP row shifts; a
 // shifted-in lane outside the row reads 0).  Lanes 0..15 hold the prefix of
 // lanes 0..15.
@@ -30,28 +24,30 @@ __device__ __forceinline__ int row_prefix16(int v)
 }
 
 // The per-wave totals of a work-group scan (written by lane 0 of every wave
-// to tot[wave], before a barrier): returns the sum over the waves below this
-// one and, in all, over every wave.  Lane w reads the total of wave w and the
-// first 16 lanes scan them, so the cost does not grow with the wave count.
+// to tot[wave], before a barrier; the entries past the wave count are zero):
+// returns the sum over the waves below this one and, in all, over every wave.
+// Lane w reads the total of wave w and the first 16 lanes scan them, so the
+// cost does not grow with the wave count.
 __device__ __forceinline__ int wave_totals(const int *tot, int wave, int nw, int &all)
 {
     const int lane = threadIdx.x & 63;
-    const int v = lane < nw ? tot[lane & (MAX_WAVES - 1)] : 0;
+    const int v = tot[lane & (MAX_WAVES - 1)];
     const int incl = row_prefix16(v);
     all = __builtin_amdgcn_readlane(incl, nw - 1);
     return __builtin_amdgcn_readlane(incl - v, wave);
 }
 
 // Exclusive prefix of a per-thread flag over the whole work-group (wave
-// ballots, then per-wave totals in LDS).  sTot holds 2*MAX_WAVES ints and the
-// two halves alternate by `parity`, so one barrier per call suffices.
+// ballots, then per-wave totals in LDS).  sTot holds 2*MAX_WAVES ints, zero
+// before the first call, and the two halves alternate by `parity`, so one
+// barrier per call suffices.
 __device__ __forceinline__ int wg_scan_flag(bool flag, int *sTot, int parity, int &total)
 {
     const int lane = threadIdx.x & 63;
     // the wave index and wave count are uniform (scalar registers)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nw = __builtin_amdgcn_readfirstlane(blockDim.x >> 6);
-    unsigned long long m = __ballot(flag);
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(flag);
     int below = lanes_below(m);
     int *tot = sTot + parity * MAX_WAVES;
     if (lane == 0) tot[wave] = __popcll(m);
@@ -60,81 +56,66 @@ __device__ __forceinline__ int wg_scan_flag(bool flag, int *sTot, int parity, in
     return off + below;
 }
 
-// Exclusive prefix of U flags per thread over the work-group, in (j, thread)
-// order: flag j of thread t is element j*blockDim + t.  sTot holds
-// 2*U*MAX_WAVES ints; the halves alternate by `parity` (one barrier).
-template <int U>
-__device__ __forceinline__ int wg_scan_flags(const bool f[U], int *sTot, int parity, int pre[U])
+// LDS of bucket_outbox, in ints: the histogram of the codes, which becomes
+// the bucket starts, and per-wave code counts.
+template <int D>
+__host__ __device__ constexpr int bucket_lds_ints()
 {
-    const int lane = threadIdx.x & 63;
-    // the wave index and wave count are uniform (scalar registers)
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int nw = __builtin_amdgcn_readfirstlane(blockDim.x >> 6);
-    int *tot = sTot + parity * U * MAX_WAVES;
-    int below[U];
-#pragma unroll
-    for (int j = 0; j < U; ++j) {
-        unsigned long long m = __ballot(f[j]);
-        below[j] = lanes_below(m);
-        if (lane == 0) tot[j * MAX_WAVES + wave] = __popcll(m);
-    }
-    __syncthreads();
-    int run = 0;
-#pragma unroll
-    for (int j = 0; j < U; ++j) {
-        int all;
-        const int off = wave_totals(tot + j * MAX_WAVES, wave, nw, all);
-        pre[j] = run + off + below[j];
-        run += all;
-    }
-    return run;
+    return ncodes<D>() + 1 + MAX_WAVES * ncodes<D>();
 }
 
 // Stable counting sort of one segment's n outbox entries by direction code:
 // the bucket starts ob_boff[ncodes + 1] and the outbox slots in bucket order
 // ob_idx, so that each neighbour reads exactly the leavers addressed to it.
-// The rank of an entry among equal codes of its wave comes from ballots on
-// the code bits; waves are ordered through per-wave counts in LDS.  With
-// mig_counts, also the segment's migration counts by direction code.  Called
-// by the whole work-group (barriers inside).
-template <typename R, int D>
-__device__ __forceinline__ void bucket_outbox(const Params<R> &p, const int ts, const int n, int *sCnt, int *sBase)
+// code_of(k) is the code of entry k; sBase holds the histogram of the codes
+// (complete before a barrier) and receives the bucket starts.  The rank of an entry among equal codes of its
+// wave comes from ballots on the code bits; waves are ordered through
+// per-wave counts in LDS.  With mig_counts, also the segment's migration
+// counts by direction code.  Called by the whole work-group (barriers
+// inside); up to a work-group of leavers take two barriers.
+template <typename R, int D, typename F>
+__device__ __forceinline__ void bucket_outbox(const Params<R> &p, const int ts, const int n, F code_of,
+                                              int *sBase, int *sCnt)
 {
-    // sCnt: MAX_WAVES * ncodes ints, sBase: ncodes + 1 ints of LDS
+    // sBase: ncodes + 1 ints, sCnt: MAX_WAVES * ncodes ints of LDS
     constexpr int NC = ncodes<D>();
+    constexpr int BITS = D == 1 ? 2 : (D == 2 ? 4 : 5);
     const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const int32_t *dir = p.ob_dir + (int64_t)ts * p.ob_dir_stride;
     int32_t *boff = p.ob_boff + (int64_t)ts * (NC + 1);
     int32_t *idx = p.ob_idx + (int64_t)ts * p.ob_cap;
-    // histogram and bucket starts
-    for (int k = threadIdx.x; k <= NC; k += blockDim.x) sBase[k] = 0;
-    __syncthreads();
-    for (int k = threadIdx.x; k < n; k += blockDim.x) atomicAdd(&sBase[dir[k] + 1], 1);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int c = 0; c < NC; ++c) sBase[c + 1] += sBase[c];
-        for (int c = 0; c <= NC; ++c) boff[c] = sBase[c];
-        if (p.mig_counts) {
-            // particles of the segment by the tile they went to: the
-            // outbox buckets, and the stayers at the centre code (the
-            // segment count before the arrivals are appended)
-            int32_t *mc = p.mig_counts + (int64_t)ts * NC;
-            for (int c = 0; c < NC; ++c) mc[c] = c == centre_code<D>() ? p.seg_cnt[ts] : sBase[c + 1] - sBase[c];
+    for (int k = threadIdx.x; k < nw * NC; k += blockDim.x) sCnt[k] = 0;
+    if (threadIdx.x < 64) {
+        // bucket starts: a scan over the codes by the first wave
+        const int c = threadIdx.x;
+        const int v = c < NC ? sBase[c] : 0;
+        int x = v;
+#pragma unroll
+        for (int o = 1; o < NC; o <<= 1) {
+            const int y = __shfl_up(x, o, 64);
+            if (c >= o) x += y;
+        }
+        if (c < NC) {
+            sBase[c] = x - v;
+            boff[c] = x - v;
+            if (c == NC - 1) boff[NC] = x;
+            // particles of the segment by the tile they went to: the outbox
+            // buckets, and the stayers at the centre code (the segment count
+            // before the arrivals are appended)
+            if (p.mig_counts) p.mig_counts[(int64_t)ts * NC + c] = c == centre_code<D>() ? p.seg_cnt[ts] : v;
         }
     }
     __syncthreads();
     // stable scatter, one work-group-wide chunk at a time
     for (int c0 = 0; c0 < n; c0 += blockDim.x) {
-        for (int k = threadIdx.x; k < nw * NC; k += blockDim.x) sCnt[k] = 0;
-        __syncthreads();
         const int k = c0 + (int)threadIdx.x;
         const bool valid = k < n;
-        const int code = valid ? dir[k] : 0;
-        unsigned long long m = __ballot(valid);
+        const int code = valid ? code_of(k) : 0;
+        unsigned long long m = __builtin_amdgcn_ballot_w64(valid);
 #pragma unroll
-        for (int b = 0; b < 5; ++b) {
-            const unsigned long long bb = __ballot((code >> b) & 1);
-            m &= ((code >> b) & 1) ? bb : ~bb;
+        for (int b = 0; b < BITS; ++b) {
+            const bool bit = (code >> b) & 1;
+            const unsigned long long bb = __builtin_amdgcn_ballot_w64(bit);
+            m &= bit ? bb : ~bb;
         }
         const int rank = lanes_below(m);
         if (valid && rank == 0) sCnt[wave * NC + code] = __popcll(m);
@@ -144,21 +125,18 @@ __device__ __forceinline__ void bucket_outbox(const Params<R> &p, const int ts, 
             for (int w = 0; w < wave; ++w) off += sCnt[w * NC + code];
             idx[off] = k;
         }
+        if (c0 + (int)blockDim.x >= n) break;
         __syncthreads();
         if ((int)threadIdx.x < NC) {
             int add = 0;
-            for (int w = 0; w < nw; ++w) add += sCnt[w * NC + threadIdx.x];
+            for (int w = 0; w < nw; ++w) {
+                add += sCnt[w * NC + threadIdx.x];
+                sCnt[w * NC + threadIdx.x] = 0;
+            }
             sBase[threadIdx.x] += add;
         }
         __syncthreads();
     }
-}
-
-// LDS ints of bucket_outbox's scratch.
-template <int D>
-__host__ __device__ constexpr int bucket_lds_ints()
-{
-    return MAX_WAVES * ncodes<D>() + ncodes<D>() + 1;
 }
 
 template <typename R, int D>
@@ -241,13 +219,32 @@ __device__ __forceinline__ void compact_chunk(const Params<R> &p, int ts, int64_
 // than either under the many-address pattern of the deposit), or R on
 // request; it is converted to R once, at the flush.  With HALFB the
 // kernel applies push_half_b1 to its LDS copy of B itself (global B stays
-// at B^{n-1/2}).  Each thread takes U particles per group (element
-// c0 + j*blockDim + t), so every load and store instruction stays
-// coalesced while U loads per array are in flight; the stable compaction
-// runs once per group.
-template <typename R, int D, bool FUSED, bool HALFB, typename A, int U, int TC, bool WALLS, int PUSHER>
+// at B^{n-1/2}).  One particle per thread and group, the next group's loads
+// in flight: two particles per thread, or a second group in flight, measured
+// slower on the 2D FP32 push (the registers lower occupancy).
+//
+// Direction codes of the first p.dir_lds leavers stay in LDS (the bucketing
+// at the end then reads nothing back from memory); the codes of later ones go
+// to ob_dir.  DIR_LDS covers about twice the leavers of a segment of mean
+// density (5% of 4,096 particles in a 16 x 16 tile, a fifth in an 8^3 tile).
+template <int D>
+__host__ __device__ constexpr int dir_lds()
+{
+    return D == 3 ? 2048 : 1024;
+}
+
+// LDS bytes of the push behind its field and current blocks, without the
+// direction codes.
+template <int D, bool FUSED>
+__host__ __device__ constexpr int push_lds_tail()
+{
+    return (int)sizeof(int) * (2 * MAX_WAVES + 4 + (FUSED ? bucket_lds_ints<D>() : 0));
+}
+
+template <typename R, int D, bool FUSED, bool HALFB, typename A, int TC, bool WALLS, int PUSHER>
 __device__ __forceinline__ void push_tile(const Params<R> &p, const int w, unsigned char *smem)
 {
+    constexpr int NC = ncodes<D>();
     // work item w = one (tile, species) segment
     const int t = w / p.nspecies, s = w - t * p.nspecies;
     if (!((p.species_mask >> s) & 1u)) return;   // species not pushed by this call
@@ -266,317 +263,280 @@ __device__ __forceinline__ void push_tile(const Params<R> &p, const int w, unsig
     }
     const FieldBox<D> fb(T);
     const CurBox<D> cb(T);
-    A *sJ = reinterpret_cast<A *>(smem);
-    R *sE = reinterpret_cast<R *>(sJ + (FUSED ? 3 * cb.n : 0));
-    R *sB = sE + 3 * cb.n;
-    int *sTot = reinterpret_cast<int *>(sB + 3 * fb.n);
-    int *sNF = sTot + 2 * U * MAX_WAVES;   // particles left near a cell face
-    int *sBkt = sNF + 4;                    // bucket_outbox scratch (fused push)
-    if (threadIdx.x == 0) *sNF = 0;
+    const bool planes = D == 3 || (TC == 0 && p.lds_planes);
+    const FieldLds<D> fl(cb, fb, planes);
+    const Strides js = cb.current();
+    // the fields first: the immediate offsets of LDS read pairs (255 elements)
+    // reach them only from a small base, those of the atomics reach 64 KB
+    // (planes have an odd number of elements, so the current comes first)
+    R *sF = reinterpret_cast<R *>(smem);
+    A *sJ = reinterpret_cast<A *>(sF + 6 * cb.n);
+    int *sTot = reinterpret_cast<int *>(sJ + (FUSED ? 3 * cb.n : 0));
+    if (planes) {
+        sJ = reinterpret_cast<A *>(smem);
+        sF = reinterpret_cast<R *>(sJ + (FUSED ? 3 * cb.n : 0));
+        sTot = reinterpret_cast<int *>(sF + 3 * cb.n + 3 * fb.n);
+    }
+    int *sNF = sTot + 2 * MAX_WAVES;             // particles left near a cell face
+    int *sBase = sNF + 4;                        // leavers by direction code, then bucket starts
+    int *sCnt = sBase + NC + 1;
+    unsigned char *sDir = reinterpret_cast<unsigned char *>(sCnt + MAX_WAVES * NC);
+    const int dir_cap = TC > 0 ? dir_lds<D>() : p.dir_lds;
     const int64_t cap = p.cap_total;
-    const int G = U * blockDim.x;
-    // the segment's planes and its first groups of particles.  Segment
+    const int G = blockDim.x, tid = threadIdx.x;
+    // the segment's planes and its first group of particles.  Segment
     // capacities are multiples of the group size, so every lane of a group
     // indexes a slot of the segment (lanes past the count read free slots):
-    // loads need no branch.  FP32 loads the first groups before the fields
+    // loads need no branch.  FP32 loads the first group before the fields
     // are staged, so that both latencies overlap (measured: FP32 step 2 us
     // shorter; FP64 3-6 us longer, so FP64 loads them after the staging).
-    const int ts = w;
-    const int64_t so = p.seg_off[ts];
-    const int cnt = p.seg_cnt[ts];
+    const int64_t so = p.seg_off[w];
+    const int cnt = p.seg_cnt[w];
+    const R q = p.charge[td.box * p.nspecies + s];
+    const R sq = p.qm[td.box * p.nspecies + s];
+    // uniform base pointers of the segment's planes; particle slots are
+    // 32-bit byte offsets from them (segment and outbox capacities are
+    // bounded so that they fit)
     R *X[3], *V[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         X[d] = p.pos + (d < D ? d : 0) * cap + so;
         V[d] = p.u + d * cap + so;
     }
-    constexpr int PF = PUSH_PREFETCH;
     constexpr bool EARLY = sizeof(R) == 4;
-    R nx[PF][U][3], nu[PF][U][3];
-    auto load_first = [&]() {
+    R nx[3] = {0, 0, 0}, nu[3] = {0, 0, 0};
+    auto load_group = [&](int c0, R *gx, R *gu) {
+        const uint32_t o = (uint32_t)(c0 + tid) * (uint32_t)sizeof(R);
 #pragma unroll
-        for (int g = 0; g < PF; ++g) {
+        for (int d = 0; d < D; ++d) gx[d] = ld_off(X[d], o);
 #pragma unroll
-            for (int j = 0; j < U; ++j) {
-#pragma unroll
-                for (int d = 0; d < 3; ++d) nx[g][j][d] = nu[g][j][d] = R(0);
-                if (g * G < cnt) {
-                    const uint32_t o = (uint32_t)(g * G + j * (int)blockDim.x + (int)threadIdx.x) * (uint32_t)sizeof(R);
-#pragma unroll
-                    for (int d = 0; d < D; ++d) nx[g][j][d] = ld_off(X[d], o);
-#pragma unroll
-                    for (int m = 0; m < 3; ++m) nu[g][j][m] = ld_off(V[m], o);
-                }
-            }
-        }
+        for (int m = 0; m < 3; ++m) gu[m] = ld_off(V[m], o);
     };
-    if constexpr (EARLY) load_first();
-    stage_block<R, D>(p.E, p.cells_total, td, T, sE, cb);
-    stage_block<R, D>(p.B, p.cells_total, td, T, sB, fb);
+    if (EARLY && cnt > 0) load_group(0, nx, nu);
+    stage_fields<R, D>(p.E, p.B, p.cells_total, td, T, sF, cb, fl);
+    if (tid < 2 * MAX_WAVES) sTot[tid] = 0;
+    if (tid == 0) *sNF = 0;
     if constexpr (FUSED) {
-        for (int k = threadIdx.x; k < 3 * cb.n; k += blockDim.x) sJ[k] = A(0);
+        for (int k = tid; k < 3 * cb.n; k += G) sJ[k] = A(0);
+        if (tid < NC) sBase[tid] = 0;
     }
     __syncthreads();
     if constexpr (HALFB) {
-        half_b_lds<R, D>(sB, fb, sE, cb, R(0.5) * p.c, td, T, s == 0 ? p.bnext : nullptr, p.cells_total);
+        half_b_lds<R, D>(sF + fl.b0, fl.b, fb, sF, fl.e, R(0.5) * p.c, td, T, s == 0 ? p.bnext : nullptr,
+                         p.cells_total);
         __syncthreads();
     }
     if constexpr (WALLS) {
         if (td.walls) {
-            wall_images<R, D>(sE, cb, sB, fb, T, td.walls);
+            wall_images<R, D>(sF, cb, fb, fl, T, td.walls);
             __syncthreads();
         }
     }
     const R c = p.c, inv_c = p.inv_c;
     int parity = 0;
     int32_t errs = 0;
-    int nfl = 0;         // this thread's particles left near a cell face
+    int nfl = 0;         // this wave's particles left near a cell face
     int fx = 0;          // fixed-point exponent of the current block
-    R qd;
-    {
-        const R q = p.charge[td.box * p.nspecies + s];
-        const R sq = p.qm[td.box * p.nspecies + s];
-        // charge of the deposit: scaled by 2^e for a fixed-point block
-        if constexpr (std::is_same<A, long long>::value) {
-            fx = fixed_exponent(q);
-            qd = ldexp(q, fx);
-        } else {
-            qd = q;
+    R qd = q;            // charge of the deposit: scaled by 2^e for a fixed-point block
+    if constexpr (std::is_same<A, long long>::value) {
+        fx = fixed_exponent(q);
+        qd = ldexp(q, fx);
+    }
+    R *XO[3], *OX[3], *OU[3];
+    const int64_t ob = (int64_t)w * p.ob_cap;
+    const int ob_cap = (int)p.ob_cap;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        XO[d] = p.xold + (d < D ? d : 0) * cap + so;
+        OX[d] = p.ob_pos + ob * D + (d < D ? d : 0) * p.ob_cap;
+        OU[d] = p.ob_u + ob * 3 + d * p.ob_cap;
+    }
+    int32_t *const OD = p.ob_dir + (int64_t)w * p.ob_dir_stride;
+    int keep = 0, nleave = 0;
+    // The fused push writes a group's particles at the top of the next
+    // iteration, before that iteration's prefetch.  The vector-memory
+    // counter retires loads and stores in issue order, and a group's
+    // stores depend on the lane masks (stayers, leavers): a wait for the
+    // prefetched group would otherwise also wait for the stores issued just
+    // before it.  Issued first, they complete under the next group's
+    // compute.  (Stores go to compacted slots below the group just read,
+    // and the prefetch reads beyond it.)
+    struct Pending {
+        bool stay, leave;
+        uint32_t off;          // byte offset of the compacted or outbox slot
+        R x[3], u[3];
+    } pend;
+    pend.stay = pend.leave = false;
+    pend.off = 0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) pend.x[d] = pend.u[d] = R(0);
+    auto flush_pending = [&](int c0) {   // c0: the pending group's first slot
+        if (pend.stay) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) st_off(X[d], pend.off, pend.x[d]);
+#pragma unroll
+            for (int m = 0; m < 3; ++m) st_off(V[m], pend.off, pend.u[m]);
+            if (p.ids) st_off(p.ids + so, pend.off / (uint32_t)sizeof(R) * 4u, (int32_t)(so + c0 + tid));
+        } else if (pend.leave) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) st_off(OX[d], pend.off, pend.x[d]);
+#pragma unroll
+            for (int m = 0; m < 3; ++m) st_off(OU[m], pend.off, pend.u[m]);
+            if (p.ids) st_off(p.ob_ids + ob, pend.off / (uint32_t)sizeof(R) * 4u, (int32_t)(so + c0 + tid));
         }
-        // uniform per-species base pointers (segment and outbox planes);
-        // particle slots are 32-bit byte offsets from them (segment and
-        // outbox capacities are bounded so that they fit)
-        R *XO[3], *OX[3], *OU[3];
-        const int64_t ob = (int64_t)ts * p.ob_cap;
+    };
+    if (!EARLY && cnt > 0) load_group(0, nx, nu);
+    int c0 = 0;
+    for (; c0 < cnt; c0 += G) {
+        const bool valid = c0 + tid < cnt;
+        R x[3], u[3], xr[3];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            XO[d] = p.xold + (d < D ? d : 0) * cap + so;
-            OX[d] = p.ob_pos + ob * D + (d < D ? d : 0) * p.ob_cap;
-            OU[d] = p.ob_u + ob * 3 + d * p.ob_cap;
-        }
-        int32_t *const OD = p.ob_dir + (int64_t)ts * p.ob_dir_stride;
-        int keep = 0, nleave = 0;
-        // The fused push writes a group's particles at the top of the next
-        // iteration, before that iteration's prefetch.  The vector-memory
-        // counter retires loads and stores in issue order, and a group's
-        // stores depend on the lane masks (stayers, leavers): a wait for the
-        // prefetched group would otherwise also wait for the stores issued just
-        // before it.  Issued first, they complete under the next group's
-        // compute.  (Stores go to compacted slots below the group just read,
-        // and the prefetch reads beyond it.)
-        struct Pending {
-            bool stay, leave;
-            uint32_t off;          // byte offset of the compacted or outbox slot
-            int code;
-            int32_t origin;
-            R x2[3], u[3];
-        } pend[U];
-#pragma unroll
-        for (int j = 0; j < U; ++j) pend[j].stay = pend[j].leave = false;
-        auto flush_pending = [&]() {
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                if (pend[j].stay) {
-#pragma unroll
-                    for (int d = 0; d < D; ++d) st_off(X[d], pend[j].off, pend[j].x2[d]);
-#pragma unroll
-                    for (int m = 0; m < 3; ++m) st_off(V[m], pend[j].off, pend[j].u[m]);
-                    if (p.ids) st_off(p.ids + so, pend[j].off / (uint32_t)sizeof(R) * 4u, pend[j].origin);
-                } else if (pend[j].leave) {
-#pragma unroll
-                    for (int d = 0; d < D; ++d) st_off(OX[d], pend[j].off, pend[j].x2[d]);
-#pragma unroll
-                    for (int m = 0; m < 3; ++m) st_off(OU[m], pend[j].off, pend[j].u[m]);
-                    const uint32_t o4 = pend[j].off / (uint32_t)sizeof(R) * 4u;
-                    st_off(OD, o4, pend[j].code);
-                    if (p.ids) st_off(p.ob_ids + ob, o4, pend[j].origin);
-                }
-            }
-        };
-        // the particles of the next PF groups are loaded PF groups ahead
-        if constexpr (!EARLY) load_first();
-        for (int c0 = 0; c0 < cnt; c0 += G) {
-            R x[U][3], u[U][3], x2[U][3];
-            bool valid[U];
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                valid[j] = c0 + j * (int)blockDim.x + (int)threadIdx.x < cnt;
-#pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    x[j][d] = nx[0][j][d];
-                    u[j][d] = nu[0][j][d];
-                    x2[j][d] = x[j][d];
-                }
-            }
-#pragma unroll
-            for (int g = 0; g + 1 < PF; ++g)
-#pragma unroll
-                for (int j = 0; j < U; ++j)
-#pragma unroll
-                    for (int d = 0; d < 3; ++d) {
-                        nx[g][j][d] = nx[g + 1][j][d];
-                        nu[g][j][d] = nu[g + 1][j][d];
-                    }
-            if constexpr (FUSED) {
-                // wait for this group's particles (and the stores issued with
-                // them, a group ago) before issuing the previous group's
-                // stores: s_waitcnt vmcnt(0), other counters untouched
-                __builtin_amdgcn_s_waitcnt(0x0F70);
-                flush_pending();                       // the previous group's stores
-            }
-            // prefetch: later groups lie beyond every element this group
-            // writes (compaction only moves elements down)
-            if (c0 + PF * G < cnt) {
-#pragma unroll
-                for (int j = 0; j < U; ++j) {
-                    const uint32_t o =
-                        (uint32_t)(c0 + PF * G + j * (int)blockDim.x + (int)threadIdx.x) * (uint32_t)sizeof(R);
-#pragma unroll
-                    for (int d = 0; d < D; ++d) nx[PF - 1][j][d] = ld_off(X[d], o);
-#pragma unroll
-                    for (int m = 0; m < 3; ++m) nu[PF - 1][j][m] = ld_off(V[m], o);
-                }
-            }
-            int delta[U][3], code[U];
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                delta[j][0] = delta[j][1] = delta[j][2] = 0;
-                code[j] = centre_code<D>();
-                if (!valid[j]) continue;
-                if (inside_tile<R, D>(x[j], T)) {
-                    R e[3], b[3], dv[3];
-                    interp_all<R, D>(sE, cb, sB, fb, x[j], T, e, b);
-                    push_u<R, PUSHER>(u[j], e, b, c, inv_c, sq);
-                    const R usq = displacement_sq<R>(u[j], c, dv);
-#pragma unroll
-                    for (int d = 0; d < D; ++d) x2[j][d] = x[j][d] + dv[d];
-                    // for finite momenta |dv_d| < c <= 1/sqrt(D), so the end point
-                    // stays in the current halo; 1 + |u|^2 is finite exactly when
-                    // u is.  Only a Courant number close to 1 (1D) can round a
-                    // displacement to a whole cell: then every move is checked.
-                    if (isfinite(usq) && (c < R(0.99) || moved_ok<R, D>(x2[j], dv, T))) {
-                        if constexpr (FUSED) {
-                            bool done = false;
-                            if constexpr (WALLS) done = wall_reflect<R, D, A>(sJ, cb, T, td.walls, x[j], x2[j], u[j], dv, qd);
-                            if (!done) zigzag<R, D, A>(sJ, cb, T, x[j], x2[j], dv, qd);
-                            code[j] = direction_code<R, D>(x2[j], T, delta[j]);
-                        }
-                    } else {
-                        errs |= isfinite(usq) ? ERR_CFL : ERR_NONFINITE;
-#pragma unroll
-                        for (int d = 0; d < D; ++d) x2[j][d] = x[j][d];
-                    }
-                } else {
-                    errs |= ERR_OUT_OF_TILE;
-#pragma unroll
-                    for (int d = 0; d < D; ++d) x2[j][d] = x[j][d];
-                }
-                // rebasing by -delta T (an even integer) is exact and keeps
-                // the distance to the nearest face
-                nfl += near_face<R, D>(x2[j], p.nf_band);
-            }
-            if constexpr (FUSED) {
-                // stable compaction: stayers in place (every destination is at
-                // or below an element this group has already read), leavers to
-                // the outbox rebased by -delta T
-                bool stay[U];
-                int pre[U];
-#pragma unroll
-                for (int j = 0; j < U; ++j) stay[j] = valid[j] && code[j] == centre_code<D>();
-                const int tot = wg_scan_flags<U>(stay, sTot, parity, pre);
-                parity ^= 1;
-#pragma unroll
-                for (int j = 0; j < U; ++j) {
-                    // stayers to their compacted slot, leavers to the outbox
-                    // rebased (written at the top of the next iteration, under
-                    // complementary lane masks; lanes past the count write
-                    // nothing)
-                    const int lane_idx = j * (int)blockDim.x + (int)threadIdx.x;
-                    pend[j].origin = (int32_t)(so + c0 + lane_idx);   // slot read from
-                    pend[j].stay = stay[j];
-                    pend[j].leave = !stay[j] && valid[j];
-                    pend[j].code = code[j];
-#pragma unroll
-                    for (int m = 0; m < 3; ++m) pend[j].u[m] = u[j][m];
-                    if (stay[j]) {
-                        pend[j].off = (uint32_t)(keep + pre[j]) * (uint32_t)sizeof(R);
-#pragma unroll
-                        for (int d = 0; d < 3; ++d) pend[j].x2[d] = x2[j][d];
-                    } else {
-                        int64_t slot = nleave + (lane_idx - pre[j]);
-                        if (valid[j] && slot >= p.ob_cap) {
-                            errs |= ERR_CAPACITY;     // state is invalid from here on
-                            slot = p.ob_cap - 1;
-                        }
-                        pend[j].off = (uint32_t)slot * (uint32_t)sizeof(R);
-#pragma unroll
-                        for (int d = 0; d < 3; ++d) pend[j].x2[d] = x2[j][d] - R(delta[j][d] * T[d]);
-                    }
-                }
-                const int nvalid = min(G, cnt - c0);
-                keep += tot;
-                nleave += nvalid - tot;
-            } else {
-#pragma unroll
-                for (int j = 0; j < U; ++j) {
-                    const int i = c0 + j * blockDim.x + threadIdx.x;   // own slot, free past the count
-#pragma unroll
-                    for (int d = 0; d < D; ++d) {
-                        XO[d][i] = x[j][d];
-                        X[d][i] = x2[j][d];
-                    }
-#pragma unroll
-                    for (int m = 0; m < 3; ++m) V[m][i] = u[j][m];
-                }
-            }
+            x[d] = nx[d];
+            u[d] = nu[d];
         }
         if constexpr (FUSED) {
-            flush_pending();                           // the last group's stores
-            if (threadIdx.x == 0) {
-                p.seg_cnt[ts] = keep;
-                p.ob_cnt[ts] = nleave;
-            }
-            // bucket the outbox by direction code for the migration; the
-            // barrier makes every wave's outbox stores visible to the group
-            __syncthreads();
-            bucket_outbox<R, D>(p, ts, (int)min((int64_t)nleave, p.ob_cap), sBkt,
-                                sBkt + MAX_WAVES * ncodes<D>());
+            // wait for this group's particles (and the stores issued with
+            // them, a group ago) before issuing the previous group's
+            // stores: s_waitcnt vmcnt(0), other counters untouched
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+            flush_pending(c0 - G);
         }
-    }
-    latch_wave(p.err, errs);
-    {
-        int v = nfl;
+        // prefetch: later groups lie beyond every element this group
+        // writes (compaction only moves elements down)
+        if (c0 + G < cnt) load_group(c0 + G, nx, nu);
+        // end point in the tile's frame (unfused: not rebased), direction
+        // code (-1 past the count); a particle with an error stays as it is
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-        if ((threadIdx.x & 63) == 0 && v) atomicAdd(sNF, v);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) p.nf_seg[w] = *sNF;
-    if constexpr (FUSED) {
-        R *blk = p.jblk + (int64_t)w * 3 * cb.n;
-        if constexpr (std::is_same<A, long long>::value) {
-            const double inv = ldexp(1.0, -fx);
-            for (int k = threadIdx.x; k < 3 * cb.n; k += blockDim.x) blk[k] = (R)((double)sJ[k] * inv);
-        } else {
-            for (int k = threadIdx.x; k < 3 * cb.n; k += blockDim.x) blk[k] = (R)sJ[k];
+        for (int d = 0; d < 3; ++d) xr[d] = x[d];
+        int code = -1;
+        R face = R(1);       // distance to the nearest face beyond the near-face band
+        if (valid) {
+            code = centre_code<D>();
+            bool ok = inside_tile<R, D>(x, T);
+            if (!ok) errs |= ERR_OUT_OF_TILE;
+            if (ok) {
+                R e[3], b[3], dv[3], x2[3] = {x[0], x[1], x[2]};
+                interp_all<R, D>(sF, fl, x, T, e, b);
+                push_u<R, PUSHER>(u, e, b, c, inv_c, sq);
+                const R usq = displacement_sq<R>(u, c, dv);
+#pragma unroll
+                for (int d = 0; d < D; ++d) x2[d] = x[d] + dv[d];
+                // for finite momenta |dv_d| < c <= 1/sqrt(D), so the end point
+                // stays in the current halo; 1 + |u|^2 is finite exactly when
+                // u is.  Only a Courant number close to 1 (1D) can round a
+                // displacement to a whole cell: then every move is checked.
+                ok = isfinite(usq) && (c < R(0.99) || moved_ok<R, D>(x2, dv, T));
+                if (!ok) errs |= isfinite(usq) ? ERR_CFL : ERR_NONFINITE;
+                if (ok) {
+                    if constexpr (FUSED) {
+                        bool done = false;
+                        if constexpr (WALLS) done = wall_reflect<R, D, A>(sJ, js, T, td.walls, x, x2, u, dv, qd);
+                        if (!done) zigzag<R, D, A>(sJ, js, T, x, x2, dv, qd);
+                        code = rebase<R, D>(x2, T, xr);
+                    } else {
+#pragma unroll
+                        for (int d = 0; d < D; ++d) xr[d] = x2[d];
+                    }
+                }
+            }
+            // rebasing by -delta T (an even integer) is exact and keeps
+            // the distance to the nearest face
+            face = face_distance<R, D>(xr, p.nf_band);
+        }
+        nfl += __popcll(__builtin_amdgcn_ballot_w64(face <= R(0)));
+        if constexpr (FUSED) {
+            // stable compaction: stayers in place (every destination is at
+            // or below an element this group has already read), leavers to
+            // the outbox rebased by -delta T; written at the top of the next
+            // iteration, under complementary lane masks (lanes past the
+            // count write nothing)
+            const bool stay = code == centre_code<D>();
+            int tot;
+            const int pre = wg_scan_flag(stay, sTot, parity, tot);
+            parity ^= 1;
+            pend.stay = stay;
+            pend.leave = code >= 0 && !stay;
+            int slot = stay ? keep + pre : nleave + (tid - pre);
+            if (pend.leave) {
+                if (slot < ob_cap) {
+                    atomicAdd(&sBase[code], 1);
+                    if (slot < dir_cap) sDir[slot] = (unsigned char)code;
+                    else OD[slot] = code;
+                } else {
+                    errs |= ERR_CAPACITY;     // state is invalid from here on
+                    slot = ob_cap - 1;
+                }
+            }
+            pend.off = (uint32_t)slot * (uint32_t)sizeof(R);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                pend.x[d] = xr[d];
+                pend.u[d] = u[d];
+            }
+            keep += tot;
+            nleave += min(G, cnt - c0) - tot;
+        } else if (valid) {
+            const int i = c0 + tid;
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                XO[d][i] = x[d];
+                X[d][i] = xr[d];
+            }
+#pragma unroll
+            for (int m = 0; m < 3; ++m) V[m][i] = u[m];
         }
     }
+    if constexpr (FUSED) flush_pending(c0 - G);            // the last group's stores
+    latch_wave(p.err, errs);
+    if ((tid & 63) == 0 && nfl) atomicAdd(sNF, nfl);
+    // every wave's current, near-face counts and direction codes are complete
+    __syncthreads();
+    if (tid == 0) {
+        p.nf_seg[w] = *sNF;
+        if constexpr (FUSED) {
+            p.seg_cnt[w] = keep;
+            p.ob_cnt[w] = nleave;
+        }
+    }
+    if constexpr (FUSED) {
+        // the block goes out in its LDS layout, which the fold reads
+        R *blk = p.jblk + (int64_t)w * 3 * cb.n;
+        const double inv = std::is_same<A, long long>::value ? ldexp(1.0, -fx) : 1.0;
+        for (int k = tid; k < 3 * cb.n; k += G) {
+            if constexpr (std::is_same<A, long long>::value) blk[k] = (R)((double)sJ[k] * inv);
+            else blk[k] = (R)sJ[k];
+        }
+        // bucket the outbox by direction code for the migration; codes beyond
+        // the LDS list were stored by other waves of this group (the barrier
+        // above makes them visible to it)
+        bucket_outbox<R, D>(
+            p, w, min(nleave, ob_cap), [&](int k) { return k < dir_cap ? (int)sDir[k] : OD[k]; }, sBase, sCnt);
+    }
+}
+
+// Waves per SIMD the push is compiled for.
+template <typename R, int D>
+__host__ __device__ constexpr int push_waves()
+{
+    return 4;
 }
 
 // One work-group per (tile, species) segment, segments dispatched in the
 // order k_order wrote (largest particle count first).
-template <typename R, int D, bool FUSED, bool HALFB, typename A, int U, int TC, bool WALLS, int PUSHER>
-__global__ void __launch_bounds__(1024) k_push(Params<R> p)
+template <typename R, int D, bool FUSED, bool HALFB, typename A, int TC, bool WALLS, int PUSHER>
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(push_waves<R, D>(), 8))) k_push(Params<R> p)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    push_tile<R, D, FUSED, HALFB, A, U, TC, WALLS, PUSHER>(p, p.order[blockIdx.x], smem);
+    push_tile<R, D, FUSED, HALFB, A, TC, WALLS, PUSHER>(p, p.order[blockIdx.x], smem);
 }
 
 // Persistent walker: a grid sized to the resident work-groups pulls
 // segments (largest first) from an atomic counter until every one is taken;
 // every work-group leaves the loop when the counter passes the segment count.
-template <typename R, int D, bool FUSED, bool HALFB, typename A, int U, int TC, bool WALLS, int PUSHER>
-__global__ void __launch_bounds__(1024) k_push_persistent(Params<R> p)
+template <typename R, int D, bool FUSED, bool HALFB, typename A, int TC, bool WALLS, int PUSHER>
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(push_waves<R, D>(), 8)))
+k_push_persistent(Params<R> p)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int next;
@@ -586,7 +546,7 @@ __global__ void __launch_bounds__(1024) k_push_persistent(Params<R> p)
         const int k = next;
         __syncthreads();
         if (k >= p.ntiles * p.nspecies) break;
-        push_tile<R, D, FUSED, HALFB, A, U, TC, WALLS, PUSHER>(p, p.order[k], smem);
+        push_tile<R, D, FUSED, HALFB, A, TC, WALLS, PUSHER>(p, p.order[k], smem);
         __syncthreads();
     }
 }
@@ -622,7 +582,7 @@ __global__ void __launch_bounds__(1024) k_deposit(Params<R> p)
             for (int m = 0; m < 3; ++m) u[m] = p.u[m * cap + so + i];
             displacement<R>(u, p.c, dv);
             const bool ok = inside_tile<R, D>(x1, p.T) && finite3<R>(u) && moved_ok<R, D>(x2, dv, p.T);
-            if (ok) zigzag<R, D, A>(sJ, cb, p.T, x1, x2, dv, q);
+            if (ok) zigzag<R, D, A>(sJ, cb.current(), p.T, x1, x2, dv, q);
         }
     }
     __syncthreads();
@@ -745,7 +705,7 @@ __device__ __forceinline__ void fold_tile(const Params<R> &p, R h, const int t)
     const int T0 = p.T[0], T1 = D > 1 ? p.T[1] : 1, T2 = D > 2 ? p.T[2] : 1;
     const int ncell = T0 * T1 * T2;
     const float inv0 = 1.0f / T0, inv1 = 1.0f / T1;
-    const int e1 = cb.e0, e2 = cb.e0 * cb.e1;
+    const Strides js = cb.current();
     const int64_t blk_len = 3 * (int64_t)cb.n;
     for (int k = threadIdx.x; k < ncell; k += blockDim.x) {
         const int r = D > 1 ? div_small(k, inv0) : 0, lz = D > 2 ? div_small(r, inv1) : 0;
@@ -762,8 +722,8 @@ __device__ __forceinline__ void fold_tile(const Params<R> &p, R h, const int t)
         R acc[3] = {0, 0, 0};
         // the cell in its own tile's block, and per dimension whether the
         // tile below or above covers it
-        const uint32_t own = (uint32_t)(l[0] + 1 + (D > 1 ? imul24(l[1] + 1, e1) : 0) +
-                                        (D > 2 ? imul24(l[2] + 1, e2) : 0)) * (uint32_t)sizeof(R);
+        const uint32_t own = (uint32_t)(l[0] + 1 + (D > 1 ? imul24(l[1] + 1, js.y) : 0) +
+                                        (D > 2 ? imul24(l[2] + 1, js.z) : 0)) * (uint32_t)sizeof(R);
         bool cov[2][3];
 #pragma unroll
         for (int d = 0; d < (D < 2 ? D : 2); ++d) {
@@ -791,14 +751,14 @@ __device__ __forceinline__ void fold_tile(const Params<R> &p, R h, const int t)
                         const int nid = td.tile0 + nx + td.nt[0] * (ny + td.nt[1] * nz);
                         // the neighbour's block, shifted so that the cell's
                         // entry lies at the same offset as in its own block
-                        const int shift = (ox - 1) * T0 + (D > 1 ? (oy - 1) * T1 * e1 : 0) +
-                                          (D > 2 ? (oz - 1) * T2 * e2 : 0);
+                        const int shift = (ox - 1) * T0 + (D > 1 ? (oy - 1) * T1 * js.y : 0) +
+                                          (D > 2 ? (oz - 1) * T2 * js.z : 0);
                         const R *blk = p.jblk + (((int64_t)nid * p.nspecies + sp) * blk_len - shift);
 #pragma unroll
                         for (int m = 0; m < 3; ++m) v[oy][ox][m] = R(0);
                         if (cov[0][ox] && (D < 2 || cov[1][oy])) {
 #pragma unroll
-                            for (int m = 0; m < 3; ++m) v[oy][ox][m] = ld_off(blk + m * cb.n, own);
+                            for (int m = 0; m < 3; ++m) v[oy][ox][m] = ld_off(blk + m * js.m, own);
                         }
                     }
                 }
@@ -961,6 +921,8 @@ __global__ void __launch_bounds__(1024) k_migrate_out(Params<R> p)
     const int t = xcd_tile(blockIdx.x, gridDim.x);
     const int64_t cap = p.cap_total;
     int parity = 0;
+    if (threadIdx.x < 2 * MAX_WAVES) sTot[threadIdx.x] = 0;
+    __syncthreads();
     for (int s = 0; s < p.nspecies; ++s) {
         if (!((p.species_mask >> s) & 1u)) continue;   // not pushed: every particle stayed
         const int ts = t * p.nspecies + s;
@@ -990,19 +952,42 @@ __global__ void __launch_bounds__(1024) k_migrate_out(Params<R> p)
 }
 
 // Bucket every segment's outbox by direction code (bucket_outbox), one
-// work-group per segment: after an unfused push's k_migrate_out, and for the
-// migration counts (the fused push buckets its own outbox at its end).
+// work-group per segment, after an unfused push's k_migrate_out (the fused
+// push buckets its own outbox at its end).
 template <typename R, int D>
 __global__ void __launch_bounds__(1024) k_migrate_bucket(Params<R> p)
 {
+    constexpr int NC = ncodes<D>();
     __shared__ int sScratch[bucket_lds_ints<D>()];
+    int *sBase = sScratch, *sCnt = sBase + NC + 1;
     // one work-group per (tile, species) segment
     const int ts = xcd_tile(blockIdx.x, gridDim.x);
     // species_mask: the species pushed in this step; the outboxes of the
     // others hold nothing of this step
     const int s = ts % p.nspecies;
     const int n = ((p.species_mask >> s) & 1u) ? (int)min((int64_t)p.ob_cnt[ts], p.ob_cap) : 0;
-    bucket_outbox<R, D>(p, ts, n, sScratch, sScratch + MAX_WAVES * ncodes<D>());
+    const int32_t *dir = p.ob_dir + (int64_t)ts * p.ob_dir_stride;
+    if ((int)threadIdx.x < NC) sBase[threadIdx.x] = 0;
+    __syncthreads();
+    for (int k = threadIdx.x; k < n; k += blockDim.x) atomicAdd(&sBase[dir[k]], 1);
+    __syncthreads();
+    bucket_outbox<R, D>(p, ts, n, [&](int k) { return dir[k]; }, sBase, sCnt);
+}
+
+// Migration counts by direction code after a fused push, from its bucket
+// starts (before the arrivals are appended); species not pushed in the step
+// count as staying.
+template <typename R, int D>
+__global__ void __launch_bounds__(256) k_migration_counts(Params<R> p)
+{
+    constexpr int NC = ncodes<D>();
+    const int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (k >= (int64_t)p.ntiles * p.nspecies * NC) return;
+    const int64_t ts = k / NC;
+    const int c = (int)(k - ts * NC);
+    const bool pushed = (p.species_mask >> (int)(ts % p.nspecies)) & 1u;
+    const int32_t *boff = p.ob_boff + ts * (NC + 1);
+    p.mig_counts[k] = c == centre_code<D>() ? p.seg_cnt[ts] : (pushed ? boff[c + 1] - boff[c] : 0);
 }
 
 // Receive incoming particles: append, per direction code in increasing
@@ -1292,6 +1277,8 @@ __global__ void __launch_bounds__(256) k_flag_list(Params<R> p, const int64_t *p
     const int cnt = p.seg_cnt[ts];
     int64_t run = pre[ts];
     int parity = 0;
+    if (threadIdx.x < 2 * MAX_WAVES) sTot[threadIdx.x] = 0;
+    __syncthreads();
     for (int c0 = 0; c0 < cnt; c0 += blockDim.x) {
         const int i = c0 + threadIdx.x;
         bool f = false;
