@@ -113,7 +113,10 @@ typedef struct {
     int32_t tile[3];      /* tile edge per dimension: even, >= 2, divides
                              every box; 1 for dimensions >= dim             */
     int32_t block;        /* threads per work-group of particle kernels
-                             (64..1024, multiple of 64); 0 = default 256    */
+                             (64..1024, multiple of 64); 0 = default 256.
+                             The push takes 2, 4, ... times as many (up to
+                             1024) where the segments are too few to fill
+                             the device (same results; FP64 to rounding)    */
     double cfl;           /* Courant number c, 0 < c <= 1/sqrt(D)           */
     const int32_t *box_cells;   /* host [n_boxes][3] cells per dimension     */
     const double *charge;       /* host [n_boxes][n_species] q (signed)      */

@@ -187,8 +187,7 @@ pic_status make_layout(const pic_config *c, const int64_t *counts, Layout &L)
     }
     if (L.max_ntb > (int64_t(1) << 24)) return fail(PIC_E_ARG, "a box has %lld tiles; at most 2^24 are supported", (long long)L.max_ntb);
     if (tiles > INT32_MAX / 8) return fail(PIC_E_ARG, "too many tiles");
-    // segment capacities: a multiple of the push kernel's group (its threads),
-    // so every lane of the last group of a segment has a slot to load from
+    // segment capacities: a multiple of the block
     const int64_t group = c->block ? c->block : 256;
     double factor = c->capacity_factor > 0 ? c->capacity_factor : 1.25;
     L.seg_off.assign(tiles * ns, 0);
@@ -313,6 +312,7 @@ struct pic_ctx {
     bool capturing;     // pic_graph_capture is recording steps
     int64_t diag_step;  // steps at the last diagnostics call, or -1
     int n_cu;           // compute units of the device
+    int push_group[2];  // threads per work-group of the unfused / fused push, 0 until its first launch
     hipGraphExec_t graph;   // captured steps, or null
     int graph_steps;
     int T[3];
@@ -460,13 +460,47 @@ struct Impl {
         return PIC_OK;
     }
 
+    // Threads per work-group of the push: the configured block, or 2, 4, ...
+    // times it where that puts more waves on a CU.  A CU holds few groups when
+    // the launch has few segments or LDS limits it; a larger group then fills
+    // it (each group takes whole segments, so nothing else can).  Of equal
+    // wave counts the larger group where every segment is resident at once
+    // (the largest segment ends the launch, and ends sooner), else the smaller
+    // (fewer waves meet at the barrier of each group).  Step with the block of
+    // 256 threads against the choice: 2D 256^2 FP32 (512 segments) 50.4 and
+    // 46.9 us with 512; five steps and diagnostics of 512x384 (1,536 segments)
+    // 615 and 606 us with 512; 3D FP64 box (480 segments, one group per CU)
+    // 107.6 and 83.8 us with 1024; 512^2 FP64 with a block of 128 232 and 215 us
+    // with 256.  1024^2 FP32 (8,192 segments) keeps 256: 512 takes 465 against
+    // 451 us.
+    template <typename K>
+    static pic_status choose_group(pic_ctx *x, K kern, size_t lds, int64_t items, int &group)
+    {
+        if (group) return PIC_OK;
+        int best = x->block;
+        int64_t best_waves = 0;
+        for (int g = x->block; g <= 1024; g *= 2) {
+            int per_cu = 0;
+            HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(kern), g, lds));
+            const int64_t resident = std::max(per_cu, 1);
+            const int64_t waves = std::min(resident, (items + x->n_cu - 1) / x->n_cu) * (g / 64);
+            const bool one_round = items <= (int64_t)std::max(per_cu, 1) * x->n_cu * 2;
+            if (per_cu > 0 && (waves > best_waves || (waves == best_waves && one_round))) {
+                best = g;
+                best_waves = waves;
+            }
+        }
+        group = best;
+        return PIC_OK;
+    }
+
     template <bool FUSED, bool HALFB, typename A, int TC, bool WALLS, int PUSHER>
     static pic_status push_launch(pic_ctx *x)
     {
         Params<R> p = params<R>(x);
         if (x->step_b) p.bnext = reinterpret_cast<R *>(x->ws + x->L.off_jtmp);
         size_t lds = push_lds<TC>(x, p, FUSED, sizeof(A));
-        dim3 b(x->block);
+        int &group = x->push_group[FUSED];
         const int64_t items = x->L.pub.tiles_total * x->ns;
         if (x->capturing || x->order_age >= ORDER_EVERY) {
             pic_status st0 = order_segments(x, p);
@@ -478,18 +512,19 @@ struct Impl {
             auto kern = pic::k_push_persistent<R, D, FUSED, HALFB, A, TC, WALLS, PUSHER>;
             pic_status st = set_lds(kern, lds);
             if (st) return st;
+            if ((st = choose_group(x, kern, lds, items, group))) return st;
             int per_cu = 0;
             HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(kern),
-                                                                x->block, lds));
+                                                                group, lds));
             const int64_t grid = std::min<int64_t>(items, (int64_t)std::max(per_cu, 1) * x->n_cu);
             st = fill<int32_t>(x, p.queue, 1, 0);
             if (st) return st;
-            hipLaunchKernelGGL(kern, dim3((unsigned)grid), b, lds, x->stream, p);
+            hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(group), lds, x->stream, p);
         } else {
             auto kern = pic::k_push<R, D, FUSED, HALFB, A, TC, WALLS, PUSHER>;
             pic_status st = set_lds(kern, lds);
-            if (st) return st;
-            hipLaunchKernelGGL(kern, dim3((unsigned)items), b, lds, x->stream, p);
+            if (st || (st = choose_group(x, kern, lds, items, group))) return st;
+            hipLaunchKernelGGL(kern, dim3((unsigned)items), dim3(group), lds, x->stream, p);
         }
         HIP_OK(hipGetLastError());
         return PIC_OK;
@@ -1026,6 +1061,7 @@ pic_status pic_init_tiles(const pic_config *cfg, const int64_t *counts, void *wo
             return fail(PIC_E_HIP, "cannot query the device");
         }
         x->n_cu = prop.multiProcessorCount;
+        x->push_group[0] = x->push_group[1] = 0;
     }
     for (int d = 0; d < 3; ++d) x->T[d] = cfg->tile[d];
     x->c = cfg->cfl;

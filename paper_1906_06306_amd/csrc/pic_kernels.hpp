@@ -284,10 +284,8 @@ __device__ __forceinline__ void push_tile(const Params<R> &p, const int w, unsig
     const int dir_cap = TC > 0 ? dir_lds<D>() : p.dir_lds;
     const int64_t cap = p.cap_total;
     const int G = blockDim.x, tid = threadIdx.x;
-    // the segment's planes and its first group of particles.  Segment
-    // capacities are multiples of the group size, so every lane of a group
-    // indexes a slot of the segment (lanes past the count read free slots):
-    // loads need no branch.  FP32 loads the first group before the fields
+    // the segment's planes and its first group of particles.  Lanes past the
+    // count read its last particle: loads need no branch.  FP32 loads the first group before the fields
     // are staged, so that both latencies overlap (measured: FP32 step 2 us
     // shorter; FP64 3-6 us longer, so FP64 loads them after the staging).
     const int64_t so = p.seg_off[w];
@@ -306,7 +304,7 @@ __device__ __forceinline__ void push_tile(const Params<R> &p, const int w, unsig
     constexpr bool EARLY = sizeof(R) == 4;
     R nx[3] = {0, 0, 0}, nu[3] = {0, 0, 0};
     auto load_group = [&](int c0, R *gx, R *gu) {
-        const uint32_t o = (uint32_t)(c0 + tid) * (uint32_t)sizeof(R);
+        const uint32_t o = (uint32_t)min(c0 + tid, cnt - 1) * (uint32_t)sizeof(R);
 #pragma unroll
         for (int d = 0; d < D; ++d) gx[d] = ld_off(X[d], o);
 #pragma unroll
