@@ -616,7 +616,8 @@ struct Impl {
         if (need_in) p.species_mask = x->pushed;   // only these species have leavers
         dim3 g((unsigned)x->L.pub.tiles_total);
         if (need_out) {
-            hipLaunchKernelGGL((pic::k_migrate_out<R, D>), g, dim3(x->block), 0, x->stream, p);
+            hipLaunchKernelGGL((pic::k_migrate_out<R, D>), dim3((unsigned)(x->L.pub.tiles_total * x->ns)), dim3(x->block), 0,
+                               x->stream, p);
             HIP_OK(hipGetLastError());
         }
         if (need_in) {
@@ -635,11 +636,19 @@ struct Impl {
             HIP_OK(hipGetLastError());
         }
         if (sort) {
-            int ncell = x->T[0] * x->T[1] * x->T[2];
-            size_t lds = (size_t)(4 + 1) * ncell * sizeof(int);
+            // per-wave cell histograms, and the permutation buffer: room for
+            // SORT_KEEP particles per thread where the LDS has it (two
+            // groups per CU); tiles of very many cells take half the waves
+            const size_t cells = (size_t)x->T[0] * x->T[1] * x->T[2];
+            const int waves = cells * pic::SORT_WAVES * sizeof(int) <= 64 * 1024 ? pic::SORT_WAVES : pic::SORT_WAVES / 2;
+            const size_t hist = cells * waves * sizeof(int);
+            int buf = 64 * waves * pic::SORT_KEEP;
+            while (buf > 0 && hist + buf * sizeof(R) > 80 * 1024) buf /= 2;
+            const size_t lds = hist + buf * sizeof(R);
             pic_status st = set_lds(pic::k_cell_sort<R, D>, lds);
             if (st) return st;
-            hipLaunchKernelGGL((pic::k_cell_sort<R, D>), g, dim3(256), lds, x->stream, p);
+            hipLaunchKernelGGL((pic::k_cell_sort<R, D>), dim3((unsigned)(x->L.pub.tiles_total * x->ns)),
+                               dim3(64 * waves), lds, x->stream, p, buf);
             HIP_OK(hipGetLastError());
         }
         if (flagged) {

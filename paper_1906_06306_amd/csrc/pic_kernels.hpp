@@ -550,7 +550,12 @@ k_push_persistent(Params<R> p)
 }
 
 // comp_curr after an unfused push: ZigZag from (xold, pos) of every
-// particle into the segment's current block.
+// particle into the segment's current block.  A lane takes four consecutive
+// particles, one 16-byte load per plane (two at FP64), and the 16 lanes that
+// the LDS serves together take quads 16 particles apart: particles sorted by
+// cell otherwise send whole waves to one address (512^2, 16 particles per cell
+// and species, sorted, FP32: 320 us with one particle per lane in order,
+// 87 us now).
 template <typename R, int D, typename A>
 __global__ void __launch_bounds__(1024) k_deposit(Params<R> p)
 {
@@ -564,22 +569,38 @@ __global__ void __launch_bounds__(1024) k_deposit(Params<R> p)
     for (int k = threadIdx.x; k < 3 * cb.n; k += blockDim.x) sJ[k] = A(0);
     __syncthreads();
     const int64_t cap = p.cap_total;
-    {
-        const int ts = w;
-        const int64_t so = p.seg_off[ts];
-        const int cnt = p.seg_cnt[ts];
-        const R q = p.charge[td.box * p.nspecies + s];
-        for (int i = threadIdx.x; i < cnt; i += blockDim.x) {
-            R x1[3] = {0, 0, 0}, x2[3] = {0, 0, 0}, u[3], dv[3];
+    const int64_t so = p.seg_off[w];
+    const int cnt = p.seg_cnt[w];
+    const R q = p.charge[td.box * p.nspecies + s];
+    const int lane = threadIdx.x & 63;
+    const int quad = ((lane & 15) << 2) | (lane >> 4);
+    // segments start at multiples of 64 slots and their capacities are
+    // multiples of 64: every quad of a count lies in its segment, aligned
+    struct alignas(16) Quad {
+        R v[4];
+    };
+    for (int i0 = ((threadIdx.x & ~63) + quad) * 4; i0 < cnt; i0 += blockDim.x * 4) {
+        Quad a[D], b[D], u[3];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            a[d] = *reinterpret_cast<const Quad *>(p.xold + d * cap + so + i0);
+            b[d] = *reinterpret_cast<const Quad *>(p.pos + d * cap + so + i0);
+        }
+#pragma unroll
+        for (int m = 0; m < 3; ++m) u[m] = *reinterpret_cast<const Quad *>(p.u + m * cap + so + i0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (i0 + j >= cnt) break;
+            R x1[3] = {0, 0, 0}, x2[3] = {0, 0, 0}, uu[3], dv[3];
 #pragma unroll
             for (int d = 0; d < D; ++d) {
-                x1[d] = p.xold[d * cap + so + i];
-                x2[d] = p.pos[d * cap + so + i];
+                x1[d] = a[d].v[j];
+                x2[d] = b[d].v[j];
             }
 #pragma unroll
-            for (int m = 0; m < 3; ++m) u[m] = p.u[m * cap + so + i];
-            displacement<R>(u, p.c, dv);
-            const bool ok = inside_tile<R, D>(x1, p.T) && finite3<R>(u) && moved_ok<R, D>(x2, dv, p.T);
+            for (int m = 0; m < 3; ++m) uu[m] = u[m].v[j];
+            displacement<R>(uu, p.c, dv);
+            const bool ok = inside_tile<R, D>(x1, p.T) && finite3<R>(uu) && moved_ok<R, D>(x2, dv, p.T);
             if (ok) zigzag<R, D, A>(sJ, cb.current(), p.T, x1, x2, dv, q);
         }
     }
@@ -911,41 +932,49 @@ __global__ void __launch_bounds__(256) k_filter(Params<R> p, const R *__restrict
 
 // ------------------------------------------------------------ migration
 
-// Tag and pack outflowing particles after an unfused push (stable).
+// Tag and pack outflowing particles after an unfused push (stable), one
+// work-group per segment; a group's particles are loaded while the group
+// before it is scanned and stored (stores go to slots below it).
 template <typename R, int D>
 __global__ void __launch_bounds__(1024) k_migrate_out(Params<R> p)
 {
     __shared__ int sTot[2 * MAX_WAVES];
-    const int t = xcd_tile(blockIdx.x, gridDim.x);
+    const int ts = xcd_tile(blockIdx.x, gridDim.x);
+    const int s = ts % p.nspecies;
+    if (!((p.species_mask >> s) & 1u)) return;   // not pushed: every particle stayed
     const int64_t cap = p.cap_total;
     int parity = 0;
     if (threadIdx.x < 2 * MAX_WAVES) sTot[threadIdx.x] = 0;
     __syncthreads();
-    for (int s = 0; s < p.nspecies; ++s) {
-        if (!((p.species_mask >> s) & 1u)) continue;   // not pushed: every particle stayed
-        const int ts = t * p.nspecies + s;
-        const int64_t so = p.seg_off[ts];
-        const int cnt = p.seg_cnt[ts];
-        int keep = 0, nleave = 0;
-        for (int c0 = 0; c0 < cnt; c0 += blockDim.x) {
-            const int i = c0 + threadIdx.x;
-            const bool valid = i < cnt;
-            R x2[3] = {0, 0, 0}, u[3] = {0, 0, 0};
-            int delta[3] = {0, 0, 0}, code = centre_code<D>();
-            if (valid) {
+    const int64_t so = p.seg_off[ts];
+    const int cnt = p.seg_cnt[ts];
+    int keep = 0, nleave = 0;
+    R nx[3] = {0, 0, 0}, nu[3] = {0, 0, 0};
+    auto load = [&](int c0) {
+        const int64_t i = so + min(c0 + (int)threadIdx.x, cnt - 1);
 #pragma unroll
-                for (int d = 0; d < D; ++d) x2[d] = p.pos[d * cap + so + i];
+        for (int d = 0; d < D; ++d) nx[d] = p.pos[d * cap + i];
 #pragma unroll
-                for (int m = 0; m < 3; ++m) u[m] = p.u[m * cap + so + i];
-                code = direction_code<R, D>(x2, p.T, delta);
-            }
-            const int nvalid = min((int)blockDim.x, cnt - c0);
-            compact_chunk<R, D>(p, ts, so, valid, code, delta, x2, u, nvalid, sTot, parity, keep, nleave);
+        for (int m = 0; m < 3; ++m) nu[m] = p.u[m * cap + i];
+    };
+    if (cnt > 0) load(0);
+    for (int c0 = 0; c0 < cnt; c0 += blockDim.x) {
+        const bool valid = c0 + (int)threadIdx.x < cnt;
+        R x2[3], u[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            x2[d] = nx[d];
+            u[d] = nu[d];
         }
-        if (threadIdx.x == 0) {
-            p.seg_cnt[ts] = keep;
-            p.ob_cnt[ts] = nleave;
-        }
+        if (c0 + (int)blockDim.x < cnt) load(c0 + blockDim.x);
+        int delta[3] = {0, 0, 0}, code = centre_code<D>();
+        if (valid) code = direction_code<R, D>(x2, p.T, delta);
+        const int nvalid = min((int)blockDim.x, cnt - c0);
+        compact_chunk<R, D>(p, ts, so, valid, code, delta, x2, u, nvalid, sTot, parity, keep, nleave);
+    }
+    if (threadIdx.x == 0) {
+        p.seg_cnt[ts] = keep;
+        p.ob_cnt[ts] = nleave;
     }
 }
 
@@ -1098,111 +1127,170 @@ __global__ void __launch_bounds__(256) k_finish_step(Params<R> p, R h)
     else receive_segment<R, D>(p, xcd_tile(blockIdx.x - p.ntiles, gridDim.x - p.ntiles));
 }
 
-// Stable sort of every tile segment by cell index (x fastest).  Each wave
-// takes a contiguous quarter (or 1/nwaves) of the segment; per-wave cell
-// histograms are scanned in (cell, wave) order, then each wave scatters its
-// range in order, ranking equal keys among lanes with ballots.  Output goes
-// to the staging arrays and is copied back.
+// Stable sort of every segment by cell index (x fastest), one work-group of up
+// to SORT_WAVES waves per segment.  Each wave takes a contiguous share of the
+// segment; per-wave cell histograms are scanned in (cell, wave) order, then
+// each wave ranks its share in order, 64 particles at a time, equal keys among
+// the lanes by ballots.  A segment of up to SORT_KEEP particles per thread
+// keeps its keys and destinations in registers and is permuted plane by plane
+// through an LDS buffer of buf elements: every plane is read and written once,
+// coalesced, in place.  A larger one is scattered to the staging planes and
+// copied back.  Bound by the planes' traffic (512^2, 16 particles per cell and
+// species, FP32, 336 MB: 356 us with one group per tile, a serial scan and the
+// staging planes for all, 97 us now).
+constexpr int SORT_WAVES = 8;
+constexpr int SORT_KEEP = 16;
+
 template <typename R, int D>
-__global__ void __launch_bounds__(256) k_cell_sort(Params<R> p)
+__global__ void __launch_bounds__(64 * SORT_WAVES) k_cell_sort(Params<R> p, int buf)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int t = xcd_tile(blockIdx.x, gridDim.x);
-    const int nw = blockDim.x >> 6, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    __shared__ int sWave[SORT_WAVES], sNF;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, nw = blockDim.x >> 6;
     const int T0 = p.T[0], T1 = D > 1 ? p.T[1] : 1, T2 = D > 2 ? p.T[2] : 1;
     const int ncell = T0 * T1 * T2;
-    int *hist = reinterpret_cast<int *>(smem);      // [nw][ncell]
-    __shared__ int nf_block;
+    R *sV = reinterpret_cast<R *>(smem);
+    int *hist = reinterpret_cast<int *>(sV + buf);      // [waves][ncell]
+    int *mine = hist + wave * ncell;
     int nbits = 0;
     while ((1 << nbits) < ncell) ++nbits;
     const int64_t cap = p.cap_total;
-    for (int s = 0; s < p.nspecies; ++s) {
-        const int ts = t * p.nspecies + s;
-        const int64_t so = p.seg_off[ts];
-        const int cnt = p.seg_cnt[ts];
-        const int per = (cnt + nw - 1) / nw;
-        if (threadIdx.x == 0) nf_block = 0;
-        const int lo = min(cnt, wave * per), hi = min(cnt, lo + per);
-        for (int k = threadIdx.x; k < nw * ncell; k += blockDim.x) hist[k] = 0;
-        __syncthreads();
-        auto keyof = [&](int64_t idx) -> int {
-            int key = 0, stride = 1;
+    const int ts = xcd_tile(blockIdx.x, gridDim.x);
+    const int64_t so = p.seg_off[ts];
+    const int cnt = p.seg_cnt[ts];
+    const int per = (cnt + (int)blockDim.x - 1) / (int)blockDim.x * 64;   // of a wave
+    const int lo = min(cnt, wave * per), hi = min(cnt, lo + per);
+    const bool keep = per <= 64 * SORT_KEEP && cnt <= buf;
+    if (tid == 0) sNF = 0;
+    for (int k = tid; k < nw * ncell; k += blockDim.x) hist[k] = 0;
+    __syncthreads();
+    int nf = 0;
+    auto key_of = [&](int i) -> int {
+        R x[3] = {0, 0, 0};
+        int key = 0, stride = 1;
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
-                R v = p.pos[d * cap + idx];
-                int c = (int)floor(v) + p.T[d] / 2;
-                c = min(max(c, 0), p.T[d] - 1);
-                key += c * stride;
-                stride *= p.T[d];
-            }
-            return key;
-        };
-        for (int i = lo + lane; i < hi; i += 64) atomicAdd(&hist[wave * ncell + keyof(so + i)], 1);
+        for (int d = 0; d < D; ++d) {
+            x[d] = p.pos[d * cap + so + i];
+            const int c = min(max((int)floor(x[d]) + p.T[d] / 2, 0), p.T[d] - 1);
+            key += c * stride;
+            stride *= p.T[d];
+        }
+        nf += near_face<R, D>(x, p.nf_band);
+        return key;
+    };
+    int key[SORT_KEEP];
+    if (keep) {
+#pragma unroll
+        for (int j = 0; j < SORT_KEEP; ++j) {
+            const int i = lo + j * 64 + lane;
+            key[j] = -1;
+            if (i < hi) key[j] = key_of(i);
+        }
+#pragma unroll
+        for (int j = 0; j < SORT_KEEP; ++j)
+            if (key[j] >= 0) atomicAdd(&mine[key[j]], 1);
+    } else {
+        for (int i = lo + lane; i < hi; i += 64) atomicAdd(&mine[key_of(i)], 1);
+    }
+    for (int o = 32; o > 0; o >>= 1) nf += __shfl_xor(nf, o);
+    if (lane == 0 && nf) atomicAdd(&sNF, nf);
+    __syncthreads();
+    if (tid == 0) p.nf_seg[ts] = sNF;
+    // exclusive scan in (cell, wave) order, a work-group of cells at a time
+    int carry = 0;
+    for (int c0 = 0; c0 < ncell; c0 += blockDim.x) {
+        const int c = c0 + tid;
+        int h[SORT_WAVES], tot = 0;
+#pragma unroll
+        for (int w = 0; w < SORT_WAVES; ++w) {
+            h[w] = w < nw && c < ncell ? hist[w * ncell + c] : 0;
+            tot += h[w];
+        }
+        int incl = tot;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+        if (lane == 63) sWave[wave] = incl;
         __syncthreads();
-        // exclusive scan over (cell, wave): one thread per cell, serial over
-        // waves, then a block scan of the per-cell totals
-        int *tot = hist + nw * ncell;   // [ncell] scratch for cell totals
-        for (int k = threadIdx.x; k < ncell; k += blockDim.x) {
-            int run = 0;
-            for (int w = 0; w < nw; ++w) {
-                int v = hist[w * ncell + k];
-                hist[w * ncell + k] = run;
-                run += v;
-            }
-            tot[k] = run;
+        int run = carry + incl - tot;
+        for (int w = 0; w < nw; ++w) {
+            run += w < wave ? sWave[w] : 0;
+            carry += sWave[w];
+        }
+#pragma unroll
+        for (int w = 0; w < SORT_WAVES; ++w) {
+            if (w < nw && c < ncell) hist[w * ncell + c] = run;
+            run += h[w];
         }
         __syncthreads();
-        if (threadIdx.x == 0) {
-            int run = 0;
-            for (int k = 0; k < ncell; ++k) {
-                int v = tot[k];
-                tot[k] = run;
-                run += v;
+    }
+    // destination of a lane's particle: its cell's next slot for this wave
+    // plus its rank among the equal keys of the 64
+    auto rank_of = [&](int k) -> int {
+        const bool valid = k >= 0;
+        unsigned long long m = __builtin_amdgcn_ballot_w64(valid);
+        for (int b = 0; b < nbits; ++b) {
+            const bool bit = (k >> b) & 1;
+            const unsigned long long bb = __builtin_amdgcn_ballot_w64(bit);
+            m &= bit ? bb : ~bb;
+        }
+        int old = 0;
+        if (valid) old = mine[k];
+        const int below = lanes_below(m);
+        if (valid && below == 0) mine[k] = old + __popcll(m);
+        return old + below;
+    };
+    if (keep) {
+        int dst[SORT_KEEP];
+#pragma unroll
+        for (int j = 0; j < SORT_KEEP; ++j) {
+            dst[j] = -1;
+            if (lo + j * 64 < hi) {                         // uniform in the wave
+                const int r = rank_of(key[j]);
+                if (key[j] >= 0) dst[j] = r;
             }
         }
-        __syncthreads();
-        for (int k = threadIdx.x; k < nw * ncell; k += blockDim.x) hist[k] += tot[k % ncell];
-        __syncthreads();
-        // in-order scatter, 64 particles at a time per wave
-        for (int base = lo; base < hi; base += 64) {
-            const int i = base + lane;
-            const bool valid = i < hi;
-            const int key = valid ? keyof(so + i) : 0;
-            unsigned long long m = __ballot(valid);
-            for (int b = 0; b < nbits; ++b) {
-                unsigned long long bb = __ballot((key >> b) & 1);
-                m &= ((key >> b) & 1) ? bb : ~bb;
-            }
-            int old = 0;
-            if (valid) old = hist[wave * ncell + key];
-            const int rank = lanes_below(m);
-            const int lead = __ffsll((long long)m) - 1;
-            if (valid && lane == lead) hist[wave * ncell + key] = old + __popcll(m);
-            if (valid) {
-                const int64_t dst = so + old + rank;
 #pragma unroll
-                for (int d = 0; d < D; ++d) p.tmp[d * cap + dst] = p.pos[d * cap + so + i];
+        for (int pl = 0; pl < D + 3; ++pl) {
+            R *P = pl < D ? p.pos + pl * cap + so : p.u + (pl - D) * cap + so;
+            R v[SORT_KEEP];
 #pragma unroll
-                for (int mm = 0; mm < 3; ++mm) p.tmp[(D + mm) * cap + dst] = p.u[mm * cap + so + i];
+            for (int j = 0; j < SORT_KEEP; ++j) {
+                v[j] = R(0);
+                if (dst[j] >= 0) v[j] = P[lo + j * 64 + lane];
             }
+#pragma unroll
+            for (int j = 0; j < SORT_KEEP; ++j)
+                if (dst[j] >= 0) sV[dst[j]] = v[j];
+            __syncthreads();
+            for (int i = tid; i < cnt; i += blockDim.x) P[i] = sV[i];
+            __syncthreads();
         }
-        __threadfence_block();
-        __syncthreads();
-        int nf = 0;
-        for (int i = threadIdx.x; i < cnt; i += blockDim.x) {
-            R v[3] = {0, 0, 0};
+        return;
+    }
+    for (int base = lo; base < hi; base += 64) {
+        const int i = base + lane;
+        const int r = rank_of(i < hi ? key_of(i) : -1);
+        if (i < hi) {
+            const int64_t dst = so + r;
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
-                v[d] = p.tmp[d * cap + so + i];
-                p.pos[d * cap + so + i] = v[d];
-            }
+            for (int d = 0; d < D; ++d) p.tmp[d * cap + dst] = p.pos[d * cap + so + i];
 #pragma unroll
-            for (int mm = 0; mm < 3; ++mm) p.u[mm * cap + so + i] = p.tmp[(D + mm) * cap + so + i];
-            nf += near_face<R, D>(v, p.nf_band);
+            for (int mm = 0; mm < 3; ++mm) p.tmp[(D + mm) * cap + dst] = p.u[mm * cap + so + i];
         }
-        if (nf) atomicAdd(&nf_block, nf);
-        __syncthreads();
-        if (threadIdx.x == 0) p.nf_seg[ts] = nf_block;
+    }
+    __threadfence_block();
+    __syncthreads();
+    for (int i = tid; i < cnt; i += blockDim.x) {
+        R v[D + 3];
+#pragma unroll
+        for (int d = 0; d < D + 3; ++d) v[d] = p.tmp[d * cap + so + i];
+#pragma unroll
+        for (int d = 0; d < D; ++d) p.pos[d * cap + so + i] = v[d];
+#pragma unroll
+        for (int mm = 0; mm < 3; ++mm) p.u[mm * cap + so + i] = v[D + mm];
     }
 }
 
