@@ -440,6 +440,25 @@ pic_status pic_adjoint_unpermute(pic_ctx *ctx, const void *lpos_after, const voi
  * adjoint unchanged. */
 pic_status pic_adjoint_step(pic_ctx *ctx, void *lpos, void *lu, void *lE, void *lB);
 
+/* A copy of a tracked state between steps, for reversed windows: E, B,
+ * segment counts, the error word and, of the particle planes and origin ids,
+ * the slots in use.  pic_state_bytes gives the size of the caller's device
+ * buffer (256-byte aligned; its layout is private to a context's
+ * configuration).  Both copies need PIC_OPT_TRACK and only enqueue work;
+ * loading leaves the slots beyond the counts as they are. */
+pic_status pic_state_bytes(pic_ctx *ctx, uint64_t *bytes);
+pic_status pic_state_save(pic_ctx *ctx, void *image);
+pic_status pic_state_load(pic_ctx *ctx, const void *image);
+
+/* pic_adjoint_step from the state in `image` (NULL: the workspace's),
+ * followed by pic_adjoint_unpermute with that state's origin ids, in one pass:
+ * lpos, lu are read at the state's slots (and left as they are), the adjoints
+ * of x^n, u^{n-1/2} go to lpos_before, lu_before ([dim|3][before_stride]) at
+ * the slots the particles came from; lE, lB in place.  before_stride as in
+ * pic_adjoint_unpermute. */
+pic_status pic_adjoint_reverse(pic_ctx *ctx, const void *image, void *lpos, void *lu, void *lE, void *lB,
+                               void *lpos_before, void *lu_before, int64_t before_stride);
+
 /* Release the host context (the workspace stays the caller's). */
 pic_status pic_destroy(pic_ctx *ctx);
 

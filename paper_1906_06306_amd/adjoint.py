@@ -1,15 +1,14 @@
 """Reverse mode over windows of fused steps, with checkpointed recomputation.
 
-The forward run keeps a copy of the state regions of the workspace (fields,
-particle planes, segment counts, origin ids) every ``window`` steps.  The
-reverse sweep visits the windows last to first: it restores the window's
-checkpoint, re-runs the window while keeping every intermediate state, and
-then, step by step backwards, maps the particle adjoints across the step's
-migration (``pic_adjoint_unpermute``, from the origin ids the tracked step
-recorded) and applies the step's transposed Jacobian (``pic_adjoint_step``).
-After the first step the particle adjoints are mapped to the input order
-of ``pic_init_tiles``.  All arithmetic runs in the library's kernels; this
-module only orders the calls and copies workspaces.
+The forward run keeps an image of the state (fields, the particles in use,
+segment counts, origin ids) every ``window`` steps.  The reverse sweep visits
+the windows last to first: it loads the window's checkpoint, re-runs the
+window keeping an image of every state, and then, step by step backwards,
+applies the step's transposed Jacobian from that image and moves the particle
+adjoints across the migration of the step before it
+(``pic_adjoint_reverse``, with the origin ids of the image).  After the first
+step the particle adjoints are in the input order of ``pic_init_tiles``.  All
+arithmetic runs in the library's kernels; this module only orders the calls.
 
 ``PicWindow`` wraps one box as a ``torch.autograd.Function`` of its initial
 state (positions, four-velocities, E, B), so that gradients of any loss of
@@ -27,16 +26,16 @@ STEP_FLAGS = L.PIC_FUSED | L.PIC_PUSH_HALF_B
 
 
 def forward(sim: PicSim, nsteps: int, window: int = 8) -> dict:
-    """Run nsteps tracked fused steps; return {step: state copy} at the
+    """Run nsteps tracked fused steps; return {step: state image} at the
     window starts."""
     if not sim.cfg.options & L.PIC_OPT_TRACK:
         raise ValueError("the simulation needs options=PIC_OPT_TRACK")
     fn = L.lib().pic_step
-    ckpts = {0: sim.snapshot()}
+    ckpts = {0: sim.save_image()}
     for k in range(nsteps):
         L.check(fn(sim.ctx, STEP_FLAGS))
         if (k + 1) % window == 0 and k + 1 < nsteps:
-            ckpts[k + 1] = sim.snapshot()
+            ckpts[k + 1] = sim.save_image()
     return ckpts
 
 
@@ -50,40 +49,39 @@ def backward(sim: PicSim, ckpts: dict, nsteps: int, lE, lB, lpos=None, lu=None, 
     particle adjoints in the concatenated input order.  Leaves the initial
     state in the workspace."""
     fn = L.lib().pic_step
-    la, ua, E_, B_ = sim.adjoint_buffers()
+    la, ua, _, _ = sim.adjoint_buffers()
     lb, ub, _, _ = sim.adjoint_buffers()
     lE = lE.to(sim.dtype).contiguous().clone()
     lB = lB.to(sim.dtype).contiguous().clone()
+    cap = int(sim.layout.capacity_total)
+    n_in = sim.n_input
+    lpos_in = torch.zeros((sim.D, n_in), dtype=sim.dtype, device=sim.device)
+    lu_in = torch.zeros((3, n_in), dtype=sim.dtype, device=sim.device)
+    # particle adjoints at the slots of the last state but one
+    last = (lpos_in, lu_in, n_in) if nsteps == 0 else (lb, ub, cap)
     if lpos is not None:
         la.copy_(lpos)
     if lu is not None:
         ua.copy_(lu)
-    cap = int(sim.layout.capacity_total)
-    starts = sorted(k for k in ckpts if k < nsteps)
-    for w0 in reversed(starts):
+    if lpos is not None or lu is not None:
+        sim.unpermute(la, ua, *last)
+    images = []                            # of the states inside a window
+    for w0 in sorted((k for k in ckpts if k < nsteps), reverse=True):
         w1 = min(w0 + window, nsteps)
-        sim.restore(ckpts[w0])
-        states = [ckpts[w0]]
-        for j in range(w0, w1):
+        sim.load_image(ckpts[w0])
+        for j in range(w0 + 1, w1):
             L.check(fn(sim.ctx, STEP_FLAGS))
-            if j + 1 < w1:                 # the last state stays in the workspace
-                states.append(sim.snapshot())
-        # Neither the unpermute nor the adjoint step writes the state
-        # regions, so the state a reversed step leaves in the workspace (the
-        # one before it) is the one the next reversed step starts from.
+            if len(images) < j - w0:
+                images.append(sim.new_image())
+            sim.save_image(images[j - w0 - 1])
         for k in range(w1 - 1, w0 - 1, -1):
-            lb.zero_()
-            ub.zero_()
-            sim.unpermute(la, ua, lb, ub, cap)      # from the state after step k
-            sim.restore(states[k - w0])
-            sim.adjoint_step(lb, ub, lE, lB)        # from the state before it
+            state = ckpts[w0] if k == w0 else images[k - w0 - 1]
+            out = (lpos_in, lu_in, n_in) if k == 0 else (la, ua, cap)
+            sim.adjoint_reverse(state, lb, ub, lE, lB, *out)
             la, lb = lb, la
             ua, ub = ub, ua
-        del states
-    n_in = sim.n_input
-    lpos_in = torch.zeros((sim.D, n_in), dtype=sim.dtype, device=sim.device)
-    lu_in = torch.zeros((3, n_in), dtype=sim.dtype, device=sim.device)
-    sim.unpermute(la, ua, lpos_in, lu_in, n_in)
+    if 0 in ckpts:
+        sim.load_image(ckpts[0])
     return lpos_in, lu_in, lE, lB
 
 

@@ -768,14 +768,75 @@ struct Impl {
         return count_near_face(x);
     }
 
+    // offsets of a state image (pic_state_save): E, B, pos, u, counts, error, ids
+    static uint64_t image_offsets(pic_ctx *x, uint64_t off[7])
+    {
+        const pic_layout &P = x->L.pub;
+        const uint64_t bytes[7] = {3 * P.cells_total * sizeof(R),  3 * P.cells_total * sizeof(R),
+                                   D * P.capacity_total * sizeof(R), 3 * P.capacity_total * sizeof(R),
+                                   P.tiles_total * x->ns * sizeof(int32_t), sizeof(int32_t),
+                                   P.capacity_total * sizeof(int32_t)};
+        uint64_t o = 0;
+        for (int k = 0; k < 7; ++k) {
+            off[k] = o;
+            o = align256(o + bytes[k]);
+        }
+        return o;
+    }
+
+    static pic_status state_bytes(pic_ctx *x, uint64_t *out)
+    {
+        uint64_t off[7];
+        *out = image_offsets(x, off);
+        return PIC_OK;
+    }
+
+    static pic::StateView<R> image_view(pic_ctx *x, const void *image)
+    {
+        uint64_t o[7];
+        image_offsets(x, o);
+        uint8_t *b = static_cast<uint8_t *>(const_cast<void *>(image));
+        return {reinterpret_cast<R *>(b + o[0]), reinterpret_cast<R *>(b + o[1]), reinterpret_cast<R *>(b + o[2]),
+                reinterpret_cast<R *>(b + o[3]), reinterpret_cast<int32_t *>(b + o[4]),
+                reinterpret_cast<int32_t *>(b + o[5]), reinterpret_cast<int32_t *>(b + o[6])};
+    }
+
+    static pic_status state_copy(pic_ctx *x, void *image, bool save)
+    {
+        const Params<R> p = params<R>(x);
+        const pic::StateView<R> ws = {p.E, p.B, p.pos, p.u, p.seg_cnt, p.err, p.ids}, im = image_view(x, image);
+        const int32_t nseg = (int32_t)(x->L.pub.tiles_total * x->ns);
+        const int64_t cells = x->L.pub.cells_total;
+        const unsigned nf = (unsigned)std::min<int64_t>(std::max<int64_t>(1, (3 * cells + 1023) / 1024), 2048);
+        hipLaunchKernelGGL((pic::k_state_copy<R, D>), dim3((unsigned)nseg + nf), dim3(256), 0, x->stream,
+                           save ? im : ws, save ? ws : im, p.seg_off, nseg, x->L.pub.capacity_total, cells);
+        HIP_OK(hipGetLastError());
+        return PIC_OK;
+    }
+
     // Reverse of one fused step from the current state (Table 1 rows in
     // reverse order; the field rows reuse the forward stencils on the
     // adjoint fields, since (curl+)^T = curl- on the periodic lattice).
-    static pic_status adjoint(pic_ctx *x, void *lpos, void *lu, void *lE, void *lB)
+    // With an image the state is read there; with opos and ou the particle
+    // adjoints go to the slots the particles came from.
+    static pic_status adjoint(pic_ctx *x, void *lpos, void *lu, void *lE, void *lB, const void *image, void *opos,
+                              void *ou, int64_t ostride)
     {
         Params<R> p = params<R>(x);
+        if (image) {
+            const pic::StateView<R> v = image_view(x, image);
+            p.E = v.E;
+            p.B = v.B;
+            p.pos = v.pos;
+            p.u = v.u;
+            p.seg_cnt = v.seg_cnt;
+            p.ids = v.ids;
+        }
         const Layout &L = x->L;
         pic::AdjParams<R> a{};
+        a.opos = reinterpret_cast<R *>(opos);
+        a.ou = reinterpret_cast<R *>(ou);
+        a.ostride = ostride;
         a.lpos = reinterpret_cast<R *>(lpos);
         a.lu = reinterpret_cast<R *>(lu);
         a.lE = reinterpret_cast<R *>(lE);
@@ -801,7 +862,7 @@ struct Impl {
                            (6 * L.jblk_cells + 3 * L.fblk_cells) * sizeof(R);
         pic_status st = set_lds(pic::k_adj_push<R, D>, lds);
         if (st) return st;
-        hipLaunchKernelGGL((pic::k_adj_push<R, D>), g, b, lds, x->stream, p, a);
+        hipLaunchKernelGGL((pic::k_adj_push<R, D>), g, dim3(pic::adj_block<R, D>()), lds, x->stream, p, a);
         hipLaunchKernelGGL((pic::k_adj_fold<R, D>), g, b, 0, x->stream, p, a);
         // push_half_b1: B^n = B^{n-1/2} - (c/2) curl+ E^n  ->  lambda_E -= (c/2) curl- lambda_B^n
         hipLaunchKernelGGL((pic::k_field<R, D, 1>), g, b, 0, x->stream, q, R(-0.5) * c);
@@ -960,7 +1021,12 @@ pic_status do_migrate(pic_ctx *x, bool out, bool in, bool sort, int32_t *mc, int
 }
 pic_status do_diag(pic_ctx *x, pic_diag *o, bool per_box) { PIC_DISPATCH(x, diag(x, o, per_box)); }
 pic_status do_diag_static(pic_ctx *x, pic_diag *o) { PIC_DISPATCH(x, diag_static(x, o)); }
-pic_status do_adjoint(pic_ctx *x, void *a, void *b, void *c, void *d) { PIC_DISPATCH(x, adjoint(x, a, b, c, d)); }
+pic_status do_adjoint(pic_ctx *x, void *a, void *b, void *c, void *d, const void *im, void *op, void *ou, int64_t os)
+{
+    PIC_DISPATCH(x, adjoint(x, a, b, c, d, im, op, ou, os));
+}
+pic_status do_state_bytes(pic_ctx *x, uint64_t *out) { PIC_DISPATCH(x, state_bytes(x, out)); }
+pic_status do_state_copy(pic_ctx *x, void *image, bool save) { PIC_DISPATCH(x, state_copy(x, image, save)); }
 pic_status do_filter(pic_ctx *x, int passes) { PIC_DISPATCH(x, filter(x, passes)); }
 pic_status do_inject(pic_ctx *x, int b, int s, int64_t n, const double *pos, const double *u)
 {
@@ -1365,7 +1431,7 @@ pic_status pic_adjoint_unpermute(pic_ctx *x, const void *lpos_after, const void 
     return do_unpermute(x, lpos_after, lu_after, lpos_before, lu_before, before_stride);
 }
 
-pic_status pic_adjoint_step(pic_ctx *x, void *lpos, void *lu, void *lE, void *lB)
+static pic_status adjoint_checks(pic_ctx *x, const void *lpos, const void *lu, const void *lE, const void *lB)
 {
     if (!x) return fail(PIC_E_ARG, "null context");
     if (!x->track) return fail(PIC_E_STATE, "the context was created without PIC_OPT_TRACK");
@@ -1374,7 +1440,51 @@ pic_status pic_adjoint_step(pic_ctx *x, void *lpos, void *lu, void *lE, void *lB
         return fail(PIC_E_ARG, "the adjoint step covers the Boris pusher and FDTD2 without current filter");
     if (!lpos || !lu || !lE || !lB) return fail(PIC_E_ARG, "adjoint buffers are required");
     if (x->state != 0) return fail(PIC_E_STATE, "the adjoint step must start between steps");
-    return do_adjoint(x, lpos, lu, lE, lB);
+    return PIC_OK;
+}
+
+pic_status pic_adjoint_step(pic_ctx *x, void *lpos, void *lu, void *lE, void *lB)
+{
+    pic_status st = adjoint_checks(x, lpos, lu, lE, lB);
+    return st ? st : do_adjoint(x, lpos, lu, lE, lB, nullptr, nullptr, nullptr, 0);
+}
+
+pic_status pic_adjoint_reverse(pic_ctx *x, const void *image, void *lpos, void *lu, void *lE, void *lB,
+                               void *lpos_before, void *lu_before, int64_t before_stride)
+{
+    pic_status st = adjoint_checks(x, lpos, lu, lE, lB);
+    if (st) return st;
+    if (!lpos_before || !lu_before || before_stride < 1)
+        return fail(PIC_E_ARG, "the adjoints' destination and a positive before_stride are required");
+    if (reinterpret_cast<uintptr_t>(image) & 255) return fail(PIC_E_ARG, "a state image must be 256-byte aligned");
+    return do_adjoint(x, lpos, lu, lE, lB, image, lpos_before, lu_before, before_stride);
+}
+
+static pic_status image_checks(pic_ctx *x, const void *image)
+{
+    if (!x) return fail(PIC_E_ARG, "null context");
+    if (!x->track) return fail(PIC_E_STATE, "the context was created without PIC_OPT_TRACK");
+    if (x->state != 0) return fail(PIC_E_STATE, "states are saved and loaded between steps");
+    if (!image || (reinterpret_cast<uintptr_t>(image) & 255)) return fail(PIC_E_ARG, "a state image must be 256-byte aligned");
+    return PIC_OK;
+}
+
+pic_status pic_state_bytes(pic_ctx *x, uint64_t *bytes)
+{
+    if (!x || !bytes) return fail(PIC_E_ARG, "null argument");
+    return do_state_bytes(x, bytes);
+}
+
+pic_status pic_state_save(pic_ctx *x, void *image)
+{
+    pic_status st = image_checks(x, image);
+    return st ? st : do_state_copy(x, image, true);
+}
+
+pic_status pic_state_load(pic_ctx *x, const void *image)
+{
+    pic_status st = image_checks(x, image);
+    return st ? st : do_state_copy(x, const_cast<void *>(image), false);
 }
 
 pic_status pic_destroy(pic_ctx *x)

@@ -5,8 +5,7 @@
 // The per-particle part mirrors the push: one work-group per tile stages E,
 // B (then B^n in LDS) and the current adjoint lambda_J with their halos,
 // recomputes each particle's push, and runs it backwards: ZigZag adjoint
-// (forward-mode dual numbers through the same segment-value code as the
-// deposit), position and displacement adjoints, Boris adjoint (hand-derived
+// (hand-derived reverse of its segment values), position and displacement adjoints, Boris adjoint (hand-derived
 // reverse of App. C) and the interpolation adjoint, whose scatter into the
 // field adjoints goes to FP64 LDS blocks that are flushed and folded like the
 // current.
@@ -16,121 +15,111 @@
 
 namespace pic {
 
-// ------------------------------------------------------------ dual numbers
-
-template <typename R, int N>
-struct Dual {
-    R v;
-    R d[N];
-    __device__ Dual() : v(0)
-    {
-#pragma unroll
-        for (int k = 0; k < N; ++k) d[k] = R(0);
-    }
-    __device__ Dual(R x) : v(x)
-    {
-#pragma unroll
-        for (int k = 0; k < N; ++k) d[k] = R(0);
-    }
-    __device__ static Dual seed(R x, int k)
-    {
-        Dual r(x);
-        r.d[k] = R(1);
-        return r;
-    }
-};
-
-template <typename R, int N>
-__device__ __forceinline__ Dual<R, N> operator+(const Dual<R, N> &a, const Dual<R, N> &b)
-{
-    Dual<R, N> r;
-    r.v = a.v + b.v;
-#pragma unroll
-    for (int k = 0; k < N; ++k) r.d[k] = a.d[k] + b.d[k];
-    return r;
-}
-template <typename R, int N>
-__device__ __forceinline__ Dual<R, N> operator-(const Dual<R, N> &a, const Dual<R, N> &b)
-{
-    Dual<R, N> r;
-    r.v = a.v - b.v;
-#pragma unroll
-    for (int k = 0; k < N; ++k) r.d[k] = a.d[k] - b.d[k];
-    return r;
-}
-template <typename R, int N>
-__device__ __forceinline__ Dual<R, N> operator*(const Dual<R, N> &a, const Dual<R, N> &b)
-{
-    Dual<R, N> r;
-    r.v = a.v * b.v;
-#pragma unroll
-    for (int k = 0; k < N; ++k) r.d[k] = a.d[k] * b.v + a.v * b.d[k];
-    return r;
-}
-
 // ------------------------------------------------------ ZigZag adjoint
 
+// Reverse of one product-weighted group of four values of segment_values,
+// f ((1-a)(1-b) + c, a (1-b) - c, (1-a) b - c, a b + c): from the adjoints l
+// of the four points, the adjoints of f (returned), a, b and c.
+template <typename R>
+__device__ __forceinline__ R bilinear_adjoint(const R l[4], R f, R a, R b, R c, R &la, R &lb, R &lc)
+{
+    const R e0 = l[1] - l[0], e1 = l[3] - l[2];
+    const R g0 = l[0] + a * e0, g1 = l[2] + a * e1;      // along a, at b = 0 and 1
+    const R t = e1 - e0;                                 // l0 - l1 - l2 + l3
+    la += f * (e0 + b * t);
+    lb += f * (g1 - g0);
+    lc = f * t;
+    return g0 + b * (g1 - g0) + c * t;
+}
+
+// Reverse of segment_values: from the adjoints l of its values, those of the
+// flux F, the weights W and the displacement d (the path-average term).
+template <typename R, int D>
+__device__ __forceinline__ void segment_adjoint(const R l[seg_values<D>()], const R F[3], const R W[3], const R d[3],
+                                                R lF[3], R lW[3], R ld[3])
+{
+    if constexpr (D == 1) {
+        lF[0] = l[0];
+        lF[1] = l[1] + W[0] * (l[2] - l[1]);
+        lF[2] = l[3] + W[0] * (l[4] - l[3]);
+        lW[0] += F[1] * (l[2] - l[1]) + F[2] * (l[4] - l[3]);
+    } else if constexpr (D == 2) {
+        lF[0] = l[0] + W[1] * (l[1] - l[0]);
+        lF[1] = l[2] + W[0] * (l[3] - l[2]);
+        lW[1] += F[0] * (l[1] - l[0]);
+        lW[0] += F[1] * (l[3] - l[2]);
+        R lc;
+        lF[2] = bilinear_adjoint<R>(l + 4, F[2], W[0], W[1], d[0] * d[1] * R(1.0 / 12.0), lW[0], lW[1], lc);
+        ld[0] += lc * d[1] * R(1.0 / 12.0);
+        ld[1] += lc * d[0] * R(1.0 / 12.0);
+    } else {
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            const int a = m == 0 ? 1 : 0, b = m == 2 ? 1 : 2;
+            R lc;
+            lF[m] = bilinear_adjoint<R>(l + 4 * m, F[m], W[a], W[b], d[a] * d[b] * R(1.0 / 12.0), lW[a], lW[b], lc);
+            ld[a] += lc * d[b] * R(1.0 / 12.0);
+            ld[b] += lc * d[a] * R(1.0 / 12.0);
+        }
+    }
+}
+
 // d(sum_points lambda_J . J)/d(x1, x2, dv_nongrid) of one particle's ZigZag
-// deposit.  Inputs k: x1_d (k = d), x2_d (k = D + d), dv_m for m >= D
-// (k = 2D + m - D).  The relay point and cells are taken on the branch of the
-// forward value; sLJ is the staged lambda_J block (local cells -1..T+1).
+// deposit.  The relay point and cells are taken on the branch of the forward
+// value; sLJ is the staged lambda_J block (local cells -1..T+1).
 template <typename R, int D, typename LA>
-__device__ __forceinline__ void zigzag_adjoint(const LA *sLJ, const CurBox<D> &cb, const int32_t T[3], const R x1[3],
+__device__ __forceinline__ void zigzag_adjoint(const LA *sLJ, const Strides st, const int32_t T[3], const R x1[3],
                                                const R x2[3], const R dv[3], R q, R lx1[3], R lx2[3], R ldv[3])
 {
-    constexpr int NI = 2 * D + (3 - D);
-    using DD = Dual<R, NI>;
-    DD F1[3], F2[3], W1[3], W2[3], d1[3], d2[3];
+    R F1[3], F2[3], W1[3] = {0, 0, 0}, W2[3] = {0, 0, 0}, d1[3], d2[3];
     int l1[3] = {0, 0, 0}, l2[3] = {0, 0, 0};
+    bool mid[3] = {false, false, false};
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         if (d < D) {
-            const DD a = DD::seed(x1[d], d), b = DD::seed(x2[d], D + d);
-            const R fa = floor(a.v), fb = floor(b.v);
-            const R lo = fmin(fa, fb), hi = fmax(fa, fb);
-            const DD mid = DD(R(0.5)) * (a + b);
-            const DD inner = hi > mid.v ? DD(hi) : mid;
-            const DD xr = (lo + R(1)) < inner.v ? DD(lo + R(1)) : inner;
+            const R a = x1[d], b = x2[d];
+            const R fa = floor(a), fb = floor(b);
+            // the relay point is the midpoint (also where that lies on the
+            // face), else the face between the cells
+            const R half = R(0.5) * (a + b), face = fa > fb ? fa : fb;
+            mid[d] = fa == fb || half == face;
+            const R xr = mid[d] ? half : face;
             d1[d] = xr - a;
             d2[d] = b - xr;
-            F1[d] = DD(q) * d1[d];
-            F2[d] = DD(q) * d2[d];
-            W1[d] = DD(R(0.5)) * (a + xr) - DD(fa);
-            W2[d] = DD(R(0.5)) * (b + xr) - DD(fb);
+            W1[d] = R(0.5) * (a + xr) - fa;
+            W2[d] = R(0.5) * (b + xr) - fb;
             l1[d] = (int)fa + T[d] / 2 + 1;
             l2[d] = (int)fb + T[d] / 2 + 1;
         } else {
-            const DD h = DD(R(0.5)) * DD::seed(dv[d], 2 * D + d - D);
-            d1[d] = h;
-            d2[d] = h;
-            F1[d] = DD(q) * h;
-            F2[d] = DD(q) * h;
+            d1[d] = d2[d] = R(0.5) * dv[d];
         }
+        F1[d] = q * d1[d];
+        F2[d] = q * d2[d];
     }
     constexpr int NV = seg_values<D>();
-    DD v1[NV], v2[NV];
-    segment_values<DD, D>(F1, W1, d1, v1);
-    segment_values<DD, D>(F2, W2, d2, v2);
-    const int s1 = cb.e0, s2 = cb.e0 * cb.e1;
-    const int b1 = l1[0] + (D > 1 ? l1[1] * s1 : 0) + (D > 2 ? l1[2] * s2 : 0);
-    const int b2 = l2[0] + (D > 1 ? l2[1] * s1 : 0) + (D > 2 ? l2[2] * s2 : 0);
-    R lin[NI];
-#pragma unroll
-    for (int k = 0; k < NI; ++k) lin[k] = R(0);
+    const int b1 = l1[0] + (D > 1 ? imul24(l1[1], st.y) : 0) + (D > 2 ? imul24(l1[2], st.z) : 0);
+    const int b2 = l2[0] + (D > 1 ? imul24(l2[1], st.y) : 0) + (D > 2 ? imul24(l2[2], st.z) : 0);
+    R la[NV], lb[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const R la = (R)sLJ[b1 + seg_offset<D>(cb.planes(), v)];
-        const R lb = (R)sLJ[b2 + seg_offset<D>(cb.planes(), v)];
-#pragma unroll
-        for (int k = 0; k < NI; ++k) lin[k] += la * v1[v].d[k] + lb * v2[v].d[k];
+        la[v] = (R)sLJ[b1 + seg_offset<D>(st, v)];
+        lb[v] = (R)sLJ[b2 + seg_offset<D>(st, v)];
     }
+    R lF1[3], lF2[3], lW1[3] = {0, 0, 0}, lW2[3] = {0, 0, 0}, ld1[3] = {0, 0, 0}, ld2[3] = {0, 0, 0};
+    segment_adjoint<R, D>(la, F1, W1, d1, lF1, lW1, ld1);
+    segment_adjoint<R, D>(lb, F2, W2, d2, lF2, lW2, ld2);
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        lx1[d] += lin[d];
-        lx2[d] += lin[D + d];
+    for (int d = 0; d < 3; ++d) {
+        const R e1 = ld1[d] + q * lF1[d], e2 = ld2[d] + q * lF2[d];
+        if (d < D) {
+            const R w1 = R(0.5) * lW1[d], w2 = R(0.5) * lW2[d];
+            const R lr = mid[d] ? R(0.5) * (e1 - e2 + w1 + w2) : R(0);   // through the midpoint
+            lx1[d] += lr - e1 + w1;
+            lx2[d] += lr + e2 + w2;
+        } else {
+            ldv[d] += R(0.5) * (e1 + e2);
+        }
     }
-#pragma unroll
-    for (int m = D; m < 3; ++m) ldv[m] += lin[2 * D + m - D];
 }
 
 // --------------------------------------------------- interpolation adjoint
@@ -271,7 +260,17 @@ struct AdjParams {
     R *lE, *lB;               // [3][cells_total]
     R *lJ;                    // [3][cells_total] scratch: lambda of J = -lambda_E
     R *eblk, *bblk;           // per tile [3][(T+3)^D], [3][(T+2)^D] adjoint blocks
+    R *opos, *ou;             // [D|3][ostride] particle adjoints at the slots the particles
+    int64_t ostride;          // came from (Params::ids), or null: in place
 };
+
+// Threads of k_adj_push: 512 (16 waves per CU at the shear window's 1,024
+// tiles of 8^2) where its registers allow them without spilling.
+template <typename R, int D>
+__host__ __device__ constexpr int adj_block()
+{
+    return sizeof(R) == 4 && D < 3 ? 512 : 256;
+}
 
 // Per tile: the particle part of the adjoint step.  State in p (particles
 // x^n, u^{n-1/2}; E^n, B^{n-1/2}); on entry a.lpos/a.lu hold the adjoints of
@@ -279,7 +278,7 @@ struct AdjParams {
 // interpolation adjoints go to the per-tile blocks a.eblk (for E^n) and
 // a.bblk (for B^n).
 template <typename R, int D>
-__global__ void __launch_bounds__(256) k_adj_push(Params<R> p, AdjParams<R> a)
+__global__ void __launch_bounds__((adj_block<R, D>())) k_adj_push(Params<R> p, AdjParams<R> a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int t = blockIdx.x;
@@ -320,7 +319,31 @@ __global__ void __launch_bounds__(256) k_adj_push(Params<R> p, AdjParams<R> a)
                 u0[m] = p.u[m * cap + so + i];
                 lu[m] = a.lu[m * cap + so + i];
             }
-            if (!inside_tile<R, D>(x, p.T)) continue;
+            // where the adjoint goes: the particle's own slot, or the one it
+            // came from in the step before (its state's origin ids), which
+            // saves a pass over the adjoints per reversed step
+            int64_t dst = so + i, stride = cap;
+            R *opos = a.lpos, *ou = a.lu;
+            if (a.opos) {
+                dst = p.ids[so + i];
+                stride = a.ostride;
+                opos = a.opos;
+                ou = a.ou;
+                if (dst < 0 || dst >= stride) {
+                    latch(p.err, ERR_ADJ_MAP);
+                    continue;
+                }
+            }
+            auto store = [&](const R px[3], const R pu[3]) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) opos[d * stride + dst] = px[d];
+#pragma unroll
+                for (int m = 0; m < 3; ++m) ou[m * stride + dst] = pu[m];
+            };
+            if (!inside_tile<R, D>(x, p.T)) {
+                if (a.opos) store(lx, lu);
+                continue;
+            }
             // forward recomputation of this particle's push
             Stencil<R, D> st;
             make_stencil<R, D>(x, p.T, st);
@@ -333,13 +356,16 @@ __global__ void __launch_bounds__(256) k_adj_push(Params<R> p, AdjParams<R> a)
             b[2] = interp_comp_adj<R, D, 5>(sB + 2 * fb.n, nullptr, f1, f2, st, R(0), g[5]);
             R u1[3] = {u0[0], u0[1], u0[2]}, dv[3], x2[3] = {0, 0, 0};
             boris<R>(u1, e, b, c, inv_c, sq);
-            displacement<R>(u1, c, dv);
-#pragma unroll
-            for (int d = 0; d < D; ++d) x2[d] = x[d] + dv[d];
-            if (!(finite3<R>(u1) && moved_ok<R, D>(x2, dv, p.T))) continue;
+            R r;
+            displacement<R>(u1, c, dv, r);
+            end_point<R, D>(x, u1, r, x2);
+            if (!(finite3<R>(u1) && moved_ok<R, D>(x2, dv, p.T))) {
+                if (a.opos) store(lx, lu);
+                continue;
+            }
             // reverse: comp_curr
             R ldv[3] = {0, 0, 0}, lx1[3] = {0, 0, 0};
-            zigzag_adjoint<R, D, R>(sLJ, cb, p.T, x, x2, dv, q, lx1, lx, ldv);
+            zigzag_adjoint<R, D, R>(sLJ, cb.planes(), p.T, x, x2, dv, q, lx1, lx, ldv);
             // x2 = x + dv
 #pragma unroll
             for (int d = 0; d < D; ++d) {
@@ -366,10 +392,7 @@ __global__ void __launch_bounds__(256) k_adj_push(Params<R> p, AdjParams<R> a)
             for (int d = 0; d < D; ++d)
                 lx1[d] += lEp[0] * g[0][d] + lEp[1] * g[1][d] + lEp[2] * g[2][d] + lBp[0] * g[3][d] +
                           lBp[1] * g[4][d] + lBp[2] * g[5][d];
-#pragma unroll
-            for (int d = 0; d < D; ++d) a.lpos[d * cap + so + i] = lx1[d];
-#pragma unroll
-            for (int m = 0; m < 3; ++m) a.lu[m * cap + so + i] = lu0[m];
+            store(lx1, lu0);
         }
     }
     __syncthreads();
@@ -442,6 +465,59 @@ __global__ void k_adj_neg(R *dst, const R *src, int64_t n)
 {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         dst[i] = -src[i];
+}
+
+// The state regions that a reversed window keeps of every step, in the
+// workspace or in a state image.
+template <typename R>
+struct StateView {
+    R *E, *B, *pos, *u;
+    int32_t *seg_cnt, *err, *ids;
+};
+
+// Copy a state: fields, counts, the error word, and of the particle planes
+// the slots in use (planes have room for the densest the plasma gets: copying
+// them whole moved 2.1 times the bytes on the shear window).  The first
+// work-groups take a segment each, 16 (32 at FP64) bytes a lane; the rest
+// the fields.
+template <typename R, int D>
+__global__ void __launch_bounds__(256) k_state_copy(StateView<R> dst, StateView<R> src, const int64_t *seg_off,
+                                                    int32_t nseg, int64_t cap, int64_t cells)
+{
+    struct alignas(16) Quad {
+        R v[4];
+    };
+    struct alignas(16) Quad4 {
+        int32_t v[4];
+    };
+    if ((int)blockIdx.x >= nseg) {
+        const int64_t step = (int64_t)(gridDim.x - nseg) * blockDim.x;
+        for (int64_t i = (int64_t)(blockIdx.x - nseg) * blockDim.x + threadIdx.x; i < 3 * cells; i += step) {
+            const R e = src.E[i], b = src.B[i];
+            dst.E[i] = e;
+            dst.B[i] = b;
+        }
+        if ((int)blockIdx.x == nseg && threadIdx.x == 0) *dst.err = *src.err;
+        return;
+    }
+    const int ts = blockIdx.x;
+    const int64_t so = seg_off[ts];
+    const int cnt = src.seg_cnt[ts];
+    if (threadIdx.x == 0) dst.seg_cnt[ts] = cnt;
+    // segments start at multiples of 64 slots and hold a multiple of 64
+    for (int i = threadIdx.x * 4; i < cnt; i += blockDim.x * 4) {
+        Quad v[D + 3];
+#pragma unroll
+        for (int d = 0; d < D; ++d) v[d] = *reinterpret_cast<const Quad *>(src.pos + d * cap + so + i);
+#pragma unroll
+        for (int m = 0; m < 3; ++m) v[D + m] = *reinterpret_cast<const Quad *>(src.u + m * cap + so + i);
+        const Quad4 id = *reinterpret_cast<const Quad4 *>(src.ids + so + i);
+#pragma unroll
+        for (int d = 0; d < D; ++d) *reinterpret_cast<Quad *>(dst.pos + d * cap + so + i) = v[d];
+#pragma unroll
+        for (int m = 0; m < 3; ++m) *reinterpret_cast<Quad *>(dst.u + m * cap + so + i) = v[D + m];
+        *reinterpret_cast<Quad4 *>(dst.ids + so + i) = id;
+    }
 }
 
 // Move particle adjoints from the slots of the current state to the slots

@@ -506,24 +506,25 @@ __device__ __forceinline__ double rsqrt_w<double>(double x) { return 1.0 / sqrt(
 // (inv_c = 1/c): u1 = c u + s E/2, gamma1 = sqrt(1 + |u1|^2/c^2),
 // t = s B/(2 c gamma1), f = 2/(1+|t|^2), u2 = f (u1 + u1 x t),
 // u3 = u1 + u2 x t + s E/2, u = u3/c.
+// The multiply-adds are written out: the push and the adjoint's recomputation
+// of it must round alike, or a particle within rounding of a face takes
+// another branch of the deposit in one of them.
 template <typename R>
 __device__ __forceinline__ void boris(R u[3], const R e[3], const R b[3], R c, R inv_c, R s)
 {
     const R hs = R(0.5) * s;
-    R ex = hs * e[0], ey = hs * e[1], ez = hs * e[2];
-    R u1x = c * u[0] + ex, u1y = c * u[1] + ey, u1z = c * u[2] + ez;
-    R k = (hs * inv_c) * rsqrt_w<R>(R(1) + (u1x * u1x + u1y * u1y + u1z * u1z) * (inv_c * inv_c));
-    R tx = k * b[0], ty = k * b[1], tz = k * b[2];
-    R f = R(2) * rcp_w<R>(R(1) + (tx * tx + ty * ty + tz * tz));
-    R u2x = f * (u1x + (u1y * tz - u1z * ty));
-    R u2y = f * (u1y + (u1z * tx - u1x * tz));
-    R u2z = f * (u1z + (u1x * ty - u1y * tx));
-    R u3x = u1x + (u2y * tz - u2z * ty) + ex;
-    R u3y = u1y + (u2z * tx - u2x * tz) + ey;
-    R u3z = u1z + (u2x * ty - u2y * tx) + ez;
-    u[0] = u3x * inv_c;
-    u[1] = u3y * inv_c;
-    u[2] = u3z * inv_c;
+    auto norm2 = [](R x, R y, R z) -> R { return fma(z, z, fma(x, x, y * y)); };
+    auto cross = [](R a, R d, R g, R h) -> R { return fma(a, d, -(g * h)); };   // a d - g h
+    const R u1x = fma(c, u[0], hs * e[0]), u1y = fma(c, u[1], hs * e[1]), u1z = fma(c, u[2], hs * e[2]);
+    const R k = (hs * inv_c) * rsqrt_w<R>(fma(inv_c * inv_c, norm2(u1x, u1y, u1z), R(1)));
+    const R tx = k * b[0], ty = k * b[1], tz = k * b[2];
+    const R f = R(2) * rcp_w<R>(R(1) + norm2(tx, ty, tz));
+    const R u2x = f * (u1x + cross(u1y, tz, u1z, ty));
+    const R u2y = f * (u1y + cross(u1z, tx, u1x, tz));
+    const R u2z = f * (u1z + cross(u1x, ty, u1y, tx));
+    u[0] = fma(hs, e[0], u1x + cross(u2y, tz, u2z, ty)) * inv_c;
+    u[1] = fma(hs, e[1], u1y + cross(u2z, tx, u2x, tz)) * inv_c;
+    u[2] = fma(hs, e[2], u1z + cross(u2x, ty, u2y, tx)) * inv_c;
 }
 
 // Lorentz factor of the implicit magnetic rotation: the gamma that solves
@@ -603,26 +604,27 @@ __device__ __forceinline__ void push_u(R u[3], const R e[3], const R b[3], R c, 
     else boris<R>(u, e, b, c, inv_c, s);
 }
 
-// Eq. (fdX): displacement c u / gamma of u^{n+1/2}, all three components.
+// Eq. (fdX): displacement c u / gamma of u^{n+1/2}, all three components, and
+// r = c / gamma, from which end_point forms x + u r in one rounding.  Returns
+// gamma^2 = 1 + |u|^2 (finite exactly when u is).  As boris, with the
+// multiply-adds written out, so that every kernel puts a particle on the same
+// side of a face.
 template <typename R>
-__device__ __forceinline__ void displacement(const R u[3], R c, R dv[3])
+__device__ __forceinline__ R displacement(const R u[3], R c, R dv[3], R &r)
 {
-    R r = c * rsqrt_w<R>(R(1) + u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
-    dv[0] = u[0] * r;
-    dv[1] = u[1] * r;
-    dv[2] = u[2] * r;
-}
-
-// The same, returning gamma^2 = 1 + |u|^2 (finite exactly when u is).
-template <typename R>
-__device__ __forceinline__ R displacement_sq(const R u[3], R c, R dv[3])
-{
-    const R g2 = R(1) + u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-    const R r = c * rsqrt_w<R>(g2);
+    const R g2 = fma(u[2], u[2], fma(u[1], u[1], fma(u[0], u[0], R(1))));
+    r = c * rsqrt_w<R>(g2);
     dv[0] = u[0] * r;
     dv[1] = u[1] * r;
     dv[2] = u[2] * r;
     return g2;
+}
+
+template <typename R, int D>
+__device__ __forceinline__ void end_point(const R x[3], const R u[3], R r, R x2[3])
+{
+#pragma unroll
+    for (int d = 0; d < D; ++d) x2[d] = fma(u[d], r, x[d]);
 }
 
 // ----------------------------------------------------------------- ZigZag

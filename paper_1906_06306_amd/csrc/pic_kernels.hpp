@@ -417,9 +417,9 @@ __device__ __forceinline__ void push_tile(const Params<R> &p, const int w, unsig
                 R e[3], b[3], dv[3], x2[3] = {x[0], x[1], x[2]};
                 interp_all<R, D>(sF, fl, x, T, e, b);
                 push_u<R, PUSHER>(u, e, b, c, inv_c, sq);
-                const R usq = displacement_sq<R>(u, c, dv);
-#pragma unroll
-                for (int d = 0; d < D; ++d) x2[d] = x[d] + dv[d];
+                R r;
+                const R usq = displacement<R>(u, c, dv, r);
+                end_point<R, D>(x, u, r, x2);
                 // for finite momenta |dv_d| < c <= 1/sqrt(D), so the end point
                 // stays in the current halo; 1 + |u|^2 is finite exactly when
                 // u is.  Only a Courant number close to 1 (1D) can round a
@@ -591,7 +591,7 @@ __global__ void __launch_bounds__(1024) k_deposit(Params<R> p)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if (i0 + j >= cnt) break;
-            R x1[3] = {0, 0, 0}, x2[3] = {0, 0, 0}, uu[3], dv[3];
+            R x1[3] = {0, 0, 0}, x2[3] = {0, 0, 0}, uu[3], dv[3], r;
 #pragma unroll
             for (int d = 0; d < D; ++d) {
                 x1[d] = a[d].v[j];
@@ -599,7 +599,7 @@ __global__ void __launch_bounds__(1024) k_deposit(Params<R> p)
             }
 #pragma unroll
             for (int m = 0; m < 3; ++m) uu[m] = u[m].v[j];
-            displacement<R>(uu, p.c, dv);
+            displacement<R>(uu, p.c, dv, r);
             const bool ok = inside_tile<R, D>(x1, p.T) && finite3<R>(uu) && moved_ok<R, D>(x2, dv, p.T);
             if (ok) zigzag<R, D, A>(sJ, cb.current(), p.T, x1, x2, dv, q);
         }

@@ -286,6 +286,34 @@ class PicSim:
         for (a, n), t in zip(self._state_ranges(), snap):
             self.ws[a:a + n].copy_(t)
 
+    def new_image(self) -> torch.Tensor:
+        """An uninitialised device buffer for save_image (256-byte aligned)."""
+        n = ctypes.c_uint64()
+        L.check(L.lib().pic_state_bytes(self.ctx, ctypes.byref(n)))
+        buf = torch.empty(int(n.value) + 256, dtype=torch.uint8, device=self.device)
+        off = (-buf.data_ptr()) % 256
+        return buf[off:off + int(n.value)]
+
+    def save_image(self, image: torch.Tensor | None = None) -> torch.Tensor:
+        """The tracked state copied to an image: snapshot() without the slots
+        beyond the counts."""
+        image = self.new_image() if image is None else image
+        L.check(L.lib().pic_state_save(self.ctx, image.data_ptr()))
+        return image
+
+    def load_image(self, image: torch.Tensor):
+        L.check(L.lib().pic_state_load(self.ctx, image.data_ptr()))
+
+    def adjoint_reverse(self, image, lpos, lu, lE, lB, lpos_before, lu_before, stride: int):
+        """adjoint_step from the state in `image`, the particle adjoints
+        unpermuted to the slots before that state's step."""
+        for t in (lpos, lu, lE, lB, lpos_before, lu_before):
+            assert t.dtype == self.dtype and t.is_contiguous() and t.device == self.device
+        assert lpos_before.shape[-1] == stride and lu_before.shape[-1] == stride
+        L.check(L.lib().pic_adjoint_reverse(self.ctx, image.data_ptr(), lpos.data_ptr(), lu.data_ptr(),
+                                            lE.data_ptr(), lB.data_ptr(), lpos_before.data_ptr(),
+                                            lu_before.data_ptr(), int(stride)))
+
     def adjoint_buffers(self):
         """Zeroed particle and field adjoint arrays in the state layout."""
         cap = int(self.layout.capacity_total)
