@@ -870,17 +870,40 @@ struct Impl {
         return PIC_OK;
     }
 
+    static size_t filter_lds(pic_ctx *x, int passes)
+    {
+        size_t n = 1;
+        for (int d = 0; d < D; ++d) n *= x->T[d] + 2 * passes;
+        return 2 * 3 * n * sizeof(R);
+    }
+
+    // The passes in an even number of launches (each reads one of J and the
+    // scratch planes and writes the other), up to MOST passes a launch: the
+    // halo's share of the work grows with them, and in 3D with its cube.
     static pic_status filter(pic_ctx *x, int passes)
     {
+        constexpr int MOST = D == 1 ? 8 : (D == 2 ? 4 : 2);
         Params<R> p = params<R>(x);
         R *tmp = reinterpret_cast<R *>(x->ws + x->L.off_jtmp);
         dim3 g((unsigned)x->L.pub.tiles_total), b(256);
-        for (int k = 0; k < passes; ++k) {
+        int most = MOST;
+        while (most > 0 && filter_lds(x, most) > 64 * 1024) --most;
+        int launches = passes;
+        if (most > 0 && passes > 1) launches = std::min(passes, 2 * ((passes + 2 * most - 1) / (2 * most)));
+        for (int k = 0; k < launches; ++k) {
             const R *src = k % 2 ? tmp : p.J;
             R *dst = k % 2 ? p.J : tmp;
-            hipLaunchKernelGGL((pic::k_filter<R, D>), g, b, 0, x->stream, p, src, dst);
+            const int now = passes / launches + (k < passes % launches);
+            if (most > 0) {
+                const size_t lds = filter_lds(x, now);
+                pic_status st = set_lds(pic::k_filter<R, D>, lds);
+                if (st) return st;
+                hipLaunchKernelGGL((pic::k_filter<R, D>), g, b, lds, x->stream, p, src, dst, now);
+            } else {
+                hipLaunchKernelGGL((pic::k_filter_direct<R, D>), g, b, 0, x->stream, p, src, dst);
+            }
         }
-        if (passes % 2) {
+        if (launches % 2) {
             const int64_t n = 3 * x->L.pub.cells_total;
             hipLaunchKernelGGL((pic::k_copy<R>), dim3((unsigned)std::min<int64_t>((n + 255) / 256, 8192)), b, 0,
                                x->stream, p.J, tmp, n);

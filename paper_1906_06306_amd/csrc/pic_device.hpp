@@ -81,6 +81,15 @@ __device__ __forceinline__ int wrapi(int i, int n)
     return r < 0 ? r + n : r;
 }
 
+// The same for a reach of a few cells, without the division: one turn, or a
+// few where the box is shorter than the reach.
+__device__ __forceinline__ int wrap_near(int i, int n)
+{
+    while (i < 0) i += n;
+    while (i >= n) i -= n;
+    return i;
+}
+
 // Tile (or (tile, species) segment) of this work-group in launches with one
 // work-group per tile (or segment), out of n.  The
 // dispatcher hands consecutive work-groups to the eight dies (XCDs, each
