@@ -819,6 +819,16 @@ struct Impl {
     // adjoint fields, since (curl+)^T = curl- on the periodic lattice).
     // With an image the state is read there; with opos and ou the particle
     // adjoints go to the slots the particles came from.
+    template <int TC>
+    static pic_status adj_push(pic_ctx *x, const Params<R> &p, const pic::AdjParams<R> &a, size_t lds)
+    {
+        pic_status st = set_lds(pic::k_adj_push<R, D, TC>, lds);
+        if (st) return st;
+        hipLaunchKernelGGL((pic::k_adj_push<R, D, TC>), dim3((unsigned)x->L.pub.tiles_total),
+                           dim3(pic::adj_block<R, D>()), lds, x->stream, p, a);
+        return PIC_OK;
+    }
+
     static pic_status adjoint(pic_ctx *x, void *lpos, void *lu, void *lE, void *lB, const void *image, void *opos,
                               void *ou, int64_t ostride)
     {
@@ -860,9 +870,11 @@ struct Impl {
         // comp_curr, position update, Boris, interp_em per particle
         const size_t lds = 3 * (L.jblk_cells + L.fblk_cells) * sizeof(double) +
                            (6 * L.jblk_cells + 3 * L.fblk_cells) * sizeof(R);
-        pic_status st = set_lds(pic::k_adj_push<R, D>, lds);
+        bool cubic = true;
+        for (int d = 1; d < D; ++d) cubic = cubic && x->T[d] == x->T[0];
+        const int edge = cubic ? x->T[0] : 0;
+        pic_status st = edge == 8 ? adj_push<8>(x, p, a, lds) : edge == 16 ? adj_push<16>(x, p, a, lds) : adj_push<0>(x, p, a, lds);
         if (st) return st;
-        hipLaunchKernelGGL((pic::k_adj_push<R, D>), g, dim3(pic::adj_block<R, D>()), lds, x->stream, p, a);
         hipLaunchKernelGGL((pic::k_adj_fold<R, D>), g, b, 0, x->stream, p, a);
         // push_half_b1: B^n = B^{n-1/2} - (c/2) curl+ E^n  ->  lambda_E -= (c/2) curl- lambda_B^n
         hipLaunchKernelGGL((pic::k_field<R, D, 1>), g, b, 0, x->stream, q, R(-0.5) * c);

@@ -5,8 +5,8 @@
 // The per-particle part mirrors the push: one work-group per tile stages E,
 // B (then B^n in LDS) and the current adjoint lambda_J with their halos,
 // recomputes each particle's push, and runs it backwards: ZigZag adjoint
-// (hand-derived reverse of its segment values), position and displacement adjoints, Boris adjoint (hand-derived
-// reverse of App. C) and the interpolation adjoint, whose scatter into the
+// (derivatives of its segment values), position and displacement adjoints,
+// Boris adjoint (hand-derived reverse of App. C) and the interpolation adjoint, whose scatter into the
 // field adjoints goes to FP64 LDS blocks that are flushed and folded like the
 // current.
 #pragma once
@@ -17,117 +17,169 @@ namespace pic {
 
 // ------------------------------------------------------ ZigZag adjoint
 
-// Reverse of one product-weighted group of four values of segment_values,
-// f ((1-a)(1-b) + c, a (1-b) - c, (1-a) b - c, a b + c): from the adjoints l
-// of the four points, the adjoints of f (returned), a, b and c.
-template <typename R>
-__device__ __forceinline__ R bilinear_adjoint(const R l[4], R f, R a, R b, R c, R &la, R &lb, R &lc)
-{
-    const R e0 = l[1] - l[0], e1 = l[3] - l[2];
-    const R g0 = l[0] + a * e0, g1 = l[2] + a * e1;      // along a, at b = 0 and 1
-    const R t = e1 - e0;                                 // l0 - l1 - l2 + l3
-    la += f * (e0 + b * t);
-    lb += f * (g1 - g0);
-    lc = f * t;
-    return g0 + b * (g1 - g0) + c * t;
-}
-
-// Reverse of segment_values: from the adjoints l of its values, those of the
-// flux F, the weights W and the displacement d (the path-average term).
-template <typename R, int D>
-__device__ __forceinline__ void segment_adjoint(const R l[seg_values<D>()], const R F[3], const R W[3], const R d[3],
-                                                R lF[3], R lW[3], R ld[3])
-{
-    if constexpr (D == 1) {
-        lF[0] = l[0];
-        lF[1] = l[1] + W[0] * (l[2] - l[1]);
-        lF[2] = l[3] + W[0] * (l[4] - l[3]);
-        lW[0] += F[1] * (l[2] - l[1]) + F[2] * (l[4] - l[3]);
-    } else if constexpr (D == 2) {
-        lF[0] = l[0] + W[1] * (l[1] - l[0]);
-        lF[1] = l[2] + W[0] * (l[3] - l[2]);
-        lW[1] += F[0] * (l[1] - l[0]);
-        lW[0] += F[1] * (l[3] - l[2]);
-        R lc;
-        lF[2] = bilinear_adjoint<R>(l + 4, F[2], W[0], W[1], d[0] * d[1] * R(1.0 / 12.0), lW[0], lW[1], lc);
-        ld[0] += lc * d[1] * R(1.0 / 12.0);
-        ld[1] += lc * d[0] * R(1.0 / 12.0);
-    } else {
+// Value j of one component of a straight segment (segment_values) is F w; its
+// derivatives are dF w along the component and F da, F db along the NT
+// transverse grid dimensions a (and b).  i = 0, 1: with respect to x1, x2.
+template <typename R, int NT>
+struct SegmentGrad {
+    R Wa, Wb, ma, mb, c, dWa[2], dWb[2], ca[2], cb[2];
+    R w, da[2], db[2];
+    __device__ __forceinline__ SegmentGrad(const R W[3], const R d[3], const R dW[3][2], const R dd[3][2], int a, int b)
+    {
+#pragma clang fp contract(off)
+        if constexpr (NT > 0) {
+            Wa = W[a];
+            ma = R(1) - Wa;
+            dWa[0] = dW[a][0];
+            dWa[1] = dW[a][1];
+        }
+        if constexpr (NT > 1) {
+            Wb = W[b];
+            mb = R(1) - Wb;
+            dWb[0] = dW[b][0];
+            dWb[1] = dW[b][1];
+            const R k = R(1.0 / 12.0);
+            c = d[a] * d[b] * k;
 #pragma unroll
-        for (int m = 0; m < 3; ++m) {
-            const int a = m == 0 ? 1 : 0, b = m == 2 ? 1 : 2;
-            R lc;
-            lF[m] = bilinear_adjoint<R>(l + 4 * m, F[m], W[a], W[b], d[a] * d[b] * R(1.0 / 12.0), lW[a], lW[b], lc);
-            ld[a] += lc * d[b] * R(1.0 / 12.0);
-            ld[b] += lc * d[a] * R(1.0 / 12.0);
+            for (int i = 0; i < 2; ++i) {
+                ca[i] = dd[a][i] * d[b] * k;
+                cb[i] = d[a] * dd[b][i] * k;
+            }
         }
     }
-}
+    __device__ __forceinline__ void value(int j)
+    {
+#pragma clang fp contract(off)
+        const bool ja = j & 1, jb = j & 2;
+        if constexpr (NT == 0) {
+            w = R(1);
+        } else if constexpr (NT == 1) {
+            w = ja ? Wa : ma;
+            da[0] = ja ? dWa[0] : -dWa[0];
+            da[1] = ja ? dWa[1] : -dWa[1];
+        } else {
+            const R wa = ja ? Wa : ma, wb = jb ? Wb : mb;
+            const bool plus = ja == jb;
+            w = fma(wa, wb, plus ? c : -c);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                da[i] = (ja ? dWa[i] : -dWa[i]) * wb + (plus ? ca[i] : -ca[i]);
+                db[i] = wa * (jb ? dWb[i] : -dWb[i]) + (plus ? cb[i] : -cb[i]);
+            }
+        }
+    }
+};
 
 // d(sum_points lambda_J . J)/d(x1, x2, dv_nongrid) of one particle's ZigZag
 // deposit.  The relay point and cells are taken on the branch of the forward
-// value; sLJ is the staged lambda_J block (local cells -1..T+1).
+// value; sLJ is the staged lambda_J block (local cells -1..T+1).  Derivatives
+// run forward through the segment values, two ends per grid dimension, with
+// the products that are zero for every particle left out (dual numbers of
+// 2D + (3 - D) parts: 1,545 vector instructions per 64 particles of the 2D FP32
+// kernel, 193 registers, 186 us per step of a shear layer of 256^2 cells, 32
+// particles each; this: 1,125, 110 and 142 us).  Multiply-adds are written out and
+// nothing else is contracted: the results are those of the dual numbers, bit
+// for bit.
 template <typename R, int D, typename LA>
 __device__ __forceinline__ void zigzag_adjoint(const LA *sLJ, const Strides st, const int32_t T[3], const R x1[3],
                                                const R x2[3], const R dv[3], R q, R lx1[3], R lx2[3], R ldv[3])
 {
-    R F1[3], F2[3], W1[3] = {0, 0, 0}, W2[3] = {0, 0, 0}, d1[3], d2[3];
-    int l1[3] = {0, 0, 0}, l2[3] = {0, 0, 0};
-    bool mid[3] = {false, false, false};
+#pragma clang fp contract(off)
+    R F[2][3], W[2][3], d[2][3], dF[2][3][2], dW[2][3][2], dd[2][3][2];
+    int base[2] = {0, 0};
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        if (d < D) {
-            const R a = x1[d], b = x2[d];
+    for (int m = 0; m < 3; ++m) {
+        if (m < D) {
+            const R a = x1[m], b = x2[m];
             const R fa = floor(a), fb = floor(b);
             // the relay point is the midpoint (also where that lies on the
             // face), else the face between the cells
             const R half = R(0.5) * (a + b), face = fa > fb ? fa : fb;
-            mid[d] = fa == fb || half == face;
-            const R xr = mid[d] ? half : face;
-            d1[d] = xr - a;
-            d2[d] = b - xr;
-            W1[d] = R(0.5) * (a + xr) - fa;
-            W2[d] = R(0.5) * (b + xr) - fb;
-            l1[d] = (int)fa + T[d] / 2 + 1;
-            l2[d] = (int)fb + T[d] / 2 + 1;
+            const bool mid = fa == fb || half == face;
+            const R xr = mid ? half : face, h = mid ? R(0.5) : R(0);   // h: d xr / d x1 = d xr / d x2
+            d[0][m] = xr - a;
+            d[1][m] = b - xr;
+            dd[0][m][0] = h - R(1);
+            dd[0][m][1] = h;
+            dd[1][m][0] = -h;
+            dd[1][m][1] = R(1) - h;
+            W[0][m] = R(0.5) * (a + xr) - fa;
+            W[1][m] = R(0.5) * (b + xr) - fb;
+            dW[0][m][0] = dW[1][m][1] = R(0.5) * (R(1) + h);
+            dW[0][m][1] = dW[1][m][0] = R(0.5) * h;
+            const int sm = m == 0 ? 1 : (m == 1 ? st.y : st.z);
+            base[0] += imul24((int)fa + T[m] / 2 + 1, sm);
+            base[1] += imul24((int)fb + T[m] / 2 + 1, sm);
         } else {
-            d1[d] = d2[d] = R(0.5) * dv[d];
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                d[g][m] = R(0.5) * dv[m];
+                dd[g][m][0] = R(0.5);
+                dd[g][m][1] = R(0);
+            }
         }
-        F1[d] = q * d1[d];
-        F2[d] = q * d2[d];
-    }
-    constexpr int NV = seg_values<D>();
-    const int b1 = l1[0] + (D > 1 ? imul24(l1[1], st.y) : 0) + (D > 2 ? imul24(l1[2], st.z) : 0);
-    const int b2 = l2[0] + (D > 1 ? imul24(l2[1], st.y) : 0) + (D > 2 ? imul24(l2[2], st.z) : 0);
-    R la[NV], lb[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        la[v] = (R)sLJ[b1 + seg_offset<D>(st, v)];
-        lb[v] = (R)sLJ[b2 + seg_offset<D>(st, v)];
-    }
-    R lF1[3], lF2[3], lW1[3] = {0, 0, 0}, lW2[3] = {0, 0, 0}, ld1[3] = {0, 0, 0}, ld2[3] = {0, 0, 0};
-    segment_adjoint<R, D>(la, F1, W1, d1, lF1, lW1, ld1);
-    segment_adjoint<R, D>(lb, F2, W2, d2, lF2, lW2, ld2);
+        for (int g = 0; g < 2; ++g) {
+            F[g][m] = q * d[g][m];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const R e1 = ld1[d] + q * lF1[d], e2 = ld2[d] + q * lF2[d];
-        if (d < D) {
-            const R w1 = R(0.5) * lW1[d], w2 = R(0.5) * lW2[d];
-            const R lr = mid[d] ? R(0.5) * (e1 - e2 + w1 + w2) : R(0);   // through the midpoint
-            lx1[d] += lr - e1 + w1;
-            lx2[d] += lr + e2 + w2;
+            for (int i = 0; i < 2; ++i) dF[g][m][i] = q * dd[g][m][i];
+        }
+    }
+    R lin[3][2] = {};
+    auto component = [&](auto nt, int m, int a, int b, int v0) {
+#pragma clang fp contract(off)
+        constexpr int NT = decltype(nt)::value;
+        SegmentGrad<R, NT> s0(W[0], d[0], dW[0], dd[0], a, b), s1(W[1], d[1], dW[1], dd[1], a, b);
+#pragma unroll
+        for (int j = 0; j < (1 << NT); ++j) {
+            s0.value(j);
+            s1.value(j);
+            const R la = (R)sLJ[base[0] + seg_offset<D>(st, v0 + j)];
+            const R lb = (R)sLJ[base[1] + seg_offset<D>(st, v0 + j)];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                if (m < D || i == 0) lin[m][i] = lin[m][i] + fma(la, dF[0][m][i] * s0.w, lb * (dF[1][m][i] * s1.w));
+                if constexpr (NT > 0)
+                    lin[a][i] = lin[a][i] + fma(la, F[0][m] * s0.da[i], lb * (F[1][m] * s1.da[i]));
+                if constexpr (NT > 1)
+                    lin[b][i] = lin[b][i] + fma(la, F[0][m] * s0.db[i], lb * (F[1][m] * s1.db[i]));
+            }
+            __builtin_amdgcn_sched_barrier(0);   // one value at a time: fewer registers
+        }
+    };
+    using N0 = std::integral_constant<int, 0>;
+    using N1 = std::integral_constant<int, 1>;
+    using N2 = std::integral_constant<int, 2>;
+    if constexpr (D == 1) {
+        component(N0(), 0, 0, 0, 0);
+        component(N1(), 1, 0, 0, 1);
+        component(N1(), 2, 0, 0, 3);
+    } else if constexpr (D == 2) {
+        component(N1(), 0, 1, 0, 0);
+        component(N1(), 1, 0, 0, 2);
+        component(N2(), 2, 0, 1, 4);
+    } else {
+        component(N2(), 0, 1, 2, 0);
+        component(N2(), 1, 0, 2, 4);
+        component(N2(), 2, 0, 1, 8);
+    }
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+        if (m < D) {
+            lx1[m] += lin[m][0];
+            lx2[m] += lin[m][1];
         } else {
-            ldv[d] += R(0.5) * (e1 + e2);
+            ldv[m] += lin[m][0];
         }
     }
 }
 
 // --------------------------------------------------- interpolation adjoint
 
-// Value, gradient with respect to the particle position, and (when L is not
-// null) the scatter lam * weight into the FP64 adjoint block L of one
+// Value, gradient with respect to the particle position, and (with SCATTER)
+// the scatter lam * weight into the FP64 adjoint block L of one
 // staggered component (same stencil as interp_comp).
-template <typename R, int D, int COMP>
+template <typename R, int D, int COMP, bool SCATTER>
 __device__ __forceinline__ R interp_comp_adj(const R *__restrict__ F, double *L, int s1, int s2,
                                              const Stencil<R, D> &st, R lam, R g[3])
 {
@@ -138,7 +190,7 @@ __device__ __forceinline__ R interp_comp_adj(const R *__restrict__ F, double *L,
     const R w0 = h0 ? st.wh[0] : st.wn[0];
     if constexpr (D == 1) {
         g[0] = F[b + 1] - F[b];
-        if (L) {
+        if constexpr (SCATTER) {
             lds_add(L + b, lam * (R(1) - w0));
             lds_add(L + b + 1, lam * w0);
         }
@@ -150,7 +202,7 @@ __device__ __forceinline__ R interp_comp_adj(const R *__restrict__ F, double *L,
         const R a0 = f00 * (R(1) - w0) + f10 * w0, a1 = f01 * (R(1) - w0) + f11 * w0;
         g[0] = (f10 - f00) * (R(1) - w1) + (f11 - f01) * w1;
         g[1] = a1 - a0;
-        if (L) {
+        if constexpr (SCATTER) {
             lds_add(L + b, lam * (R(1) - w0) * (R(1) - w1));
             lds_add(L + b + 1, lam * w0 * (R(1) - w1));
             lds_add(L + b + s1, lam * (R(1) - w0) * w1);
@@ -175,7 +227,7 @@ __device__ __forceinline__ R interp_comp_adj(const R *__restrict__ F, double *L,
             g[0] += f[cn] * (c0 ? R(1) : R(-1)) * p1 * p2;
             g[1] += f[cn] * p0 * (c1 ? R(1) : R(-1)) * p2;
             g[2] += f[cn] * p0 * p1 * (c2 ? R(1) : R(-1));
-            if (L) lds_add(L + b + c0 + c1 * s1 + c2 * s2, lam * p0 * p1 * p2);
+            if constexpr (SCATTER) lds_add(L + b + c0 + c1 * s1 + c2 * s2, lam * p0 * p1 * p2);
         }
         return val;
     }
@@ -277,36 +329,38 @@ __host__ __device__ constexpr int adj_block()
 // x^{n+1}, u^{n+1/2} (same slots), on exit those of x^n, u^{n-1/2}; the
 // interpolation adjoints go to the per-tile blocks a.eblk (for E^n) and
 // a.bblk (for B^n).
-template <typename R, int D>
+template <typename R, int D, int TC>
 __global__ void __launch_bounds__((adj_block<R, D>())) k_adj_push(Params<R> p, AdjParams<R> a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int t = blockIdx.x;
     const TileDesc td = p.tiles[t];
-    const FieldBox<D> fb(p.T);
-    const CurBox<D> cb(p.T);
+    // tile edge: a compile-time constant when TC > 0, as in the push
+    const int32_t T[3] = {TC > 0 ? TC : p.T[0], D > 1 ? (TC > 0 ? TC : p.T[1]) : 1, D > 2 ? (TC > 0 ? TC : p.T[2]) : 1};
+    const FieldBox<D> fb(T);
+    const CurBox<D> cb(T);
     double *aE = reinterpret_cast<double *>(smem);           // [3][cb.n]
     double *aB = aE + 3 * cb.n;                              // [3][fb.n]
     R *sLJ = reinterpret_cast<R *>(aB + 3 * fb.n);           // [3][cb.n]
     R *sE = sLJ + 3 * cb.n;                                  // [3][cb.n]
     R *sB = sE + 3 * cb.n;                                   // [3][fb.n]
-    stage_block<R, D>(p.E, p.cells_total, td, p.T, sE, cb);
-    stage_block<R, D>(p.B, p.cells_total, td, p.T, sB, fb);
-    stage_block<R, D>(a.lJ, p.cells_total, td, p.T, sLJ, cb);
+    stage_block<R, D>(p.E, p.cells_total, td, T, sE, cb);
+    stage_block<R, D>(p.B, p.cells_total, td, T, sB, fb);
+    stage_block<R, D>(a.lJ, p.cells_total, td, T, sLJ, cb);
     for (int k = threadIdx.x; k < 3 * cb.n; k += blockDim.x) aE[k] = 0.0;
     for (int k = threadIdx.x; k < 3 * fb.n; k += blockDim.x) aB[k] = 0.0;
     __syncthreads();
-    half_b_lds<R, D>(sB, fb.planes(), fb, sE, cb.planes(), R(0.5) * p.c, td, p.T, nullptr, 0);   // B^n, as the push saw it
+    half_b_lds<R, D>(sB, fb.planes(), fb, sE, cb.planes(), R(0.5) * p.c, td, T, nullptr, 0);   // B^n, as the push saw it
     __syncthreads();
     const R c = p.c, inv_c = p.inv_c;
     const int64_t cap = p.cap_total;
     const int e1 = cb.e0, e2 = cb.e0 * cb.e1, f1 = fb.e0, f2 = fb.e0 * fb.e1;
     for (int s = 0; s < p.nspecies; ++s) {
         const int ts = t * p.nspecies + s;
-        const int64_t so = p.seg_off[ts];
-        const int cnt = p.seg_cnt[ts];
-        const R q = p.charge[td.box * p.nspecies + s];
-        const R sq = p.qm[td.box * p.nspecies + s];
+        const int64_t so = uniform(p.seg_off[ts]);
+        const int cnt = uniform(p.seg_cnt[ts]);
+        const R q = uniform(p.charge[td.box * p.nspecies + s]);
+        const R sq = uniform(p.qm[td.box * p.nspecies + s]);
         for (int i = threadIdx.x; i < cnt; i += blockDim.x) {
             R x[3] = {0, 0, 0}, u0[3], lx[3] = {0, 0, 0}, lu[3];
 #pragma unroll
@@ -340,32 +394,33 @@ __global__ void __launch_bounds__((adj_block<R, D>())) k_adj_push(Params<R> p, A
 #pragma unroll
                 for (int m = 0; m < 3; ++m) ou[m * stride + dst] = pu[m];
             };
-            if (!inside_tile<R, D>(x, p.T)) {
+            if (!inside_tile<R, D>(x, T)) {
                 if (a.opos) store(lx, lu);
                 continue;
             }
             // forward recomputation of this particle's push
             Stencil<R, D> st;
-            make_stencil<R, D>(x, p.T, st);
+            make_stencil<R, D>(x, T, st);
             R e[3], b[3], g[6][3];
-            e[0] = interp_comp_adj<R, D, 0>(sE + 0 * cb.n, nullptr, e1, e2, st, R(0), g[0]);
-            e[1] = interp_comp_adj<R, D, 1>(sE + 1 * cb.n, nullptr, e1, e2, st, R(0), g[1]);
-            e[2] = interp_comp_adj<R, D, 2>(sE + 2 * cb.n, nullptr, e1, e2, st, R(0), g[2]);
-            b[0] = interp_comp_adj<R, D, 3>(sB + 0 * fb.n, nullptr, f1, f2, st, R(0), g[3]);
-            b[1] = interp_comp_adj<R, D, 4>(sB + 1 * fb.n, nullptr, f1, f2, st, R(0), g[4]);
-            b[2] = interp_comp_adj<R, D, 5>(sB + 2 * fb.n, nullptr, f1, f2, st, R(0), g[5]);
+            e[0] = interp_comp_adj<R, D, 0, false>(sE + 0 * cb.n, nullptr, e1, e2, st, R(0), g[0]);
+            e[1] = interp_comp_adj<R, D, 1, false>(sE + 1 * cb.n, nullptr, e1, e2, st, R(0), g[1]);
+            e[2] = interp_comp_adj<R, D, 2, false>(sE + 2 * cb.n, nullptr, e1, e2, st, R(0), g[2]);
+            b[0] = interp_comp_adj<R, D, 3, false>(sB + 0 * fb.n, nullptr, f1, f2, st, R(0), g[3]);
+            b[1] = interp_comp_adj<R, D, 4, false>(sB + 1 * fb.n, nullptr, f1, f2, st, R(0), g[4]);
+            b[2] = interp_comp_adj<R, D, 5, false>(sB + 2 * fb.n, nullptr, f1, f2, st, R(0), g[5]);
             R u1[3] = {u0[0], u0[1], u0[2]}, dv[3], x2[3] = {0, 0, 0};
             boris<R>(u1, e, b, c, inv_c, sq);
             R r;
             displacement<R>(u1, c, dv, r);
             end_point<R, D>(x, u1, r, x2);
-            if (!(finite3<R>(u1) && moved_ok<R, D>(x2, dv, p.T))) {
+            if (!(finite3<R>(u1) && moved_ok<R, D>(x2, dv, T))) {
                 if (a.opos) store(lx, lu);
                 continue;
             }
+            __builtin_amdgcn_sched_barrier(0);
             // reverse: comp_curr
             R ldv[3] = {0, 0, 0}, lx1[3] = {0, 0, 0};
-            zigzag_adjoint<R, D, R>(sLJ, cb.planes(), p.T, x, x2, dv, q, lx1, lx, ldv);
+            zigzag_adjoint<R, D, R>(sLJ, cb.planes(), T, x, x2, dv, q, lx1, lx, ldv);
             // x2 = x + dv
 #pragma unroll
             for (int d = 0; d < D; ++d) {
@@ -382,12 +437,12 @@ __global__ void __launch_bounds__((adj_block<R, D>())) k_adj_push(Params<R> p, A
             boris_adjoint<R>(u0, e, b, c, inv_c, sq, lu, lu0, lEp, lBp);
             // interpolation: scatter into the field adjoints, gradient in x
             R gg[3];
-            interp_comp_adj<R, D, 0>(sE + 0 * cb.n, aE + 0 * cb.n, e1, e2, st, lEp[0], gg);
-            interp_comp_adj<R, D, 1>(sE + 1 * cb.n, aE + 1 * cb.n, e1, e2, st, lEp[1], gg);
-            interp_comp_adj<R, D, 2>(sE + 2 * cb.n, aE + 2 * cb.n, e1, e2, st, lEp[2], gg);
-            interp_comp_adj<R, D, 3>(sB + 0 * fb.n, aB + 0 * fb.n, f1, f2, st, lBp[0], gg);
-            interp_comp_adj<R, D, 4>(sB + 1 * fb.n, aB + 1 * fb.n, f1, f2, st, lBp[1], gg);
-            interp_comp_adj<R, D, 5>(sB + 2 * fb.n, aB + 2 * fb.n, f1, f2, st, lBp[2], gg);
+            interp_comp_adj<R, D, 0, true>(sE + 0 * cb.n, aE + 0 * cb.n, e1, e2, st, lEp[0], gg);
+            interp_comp_adj<R, D, 1, true>(sE + 1 * cb.n, aE + 1 * cb.n, e1, e2, st, lEp[1], gg);
+            interp_comp_adj<R, D, 2, true>(sE + 2 * cb.n, aE + 2 * cb.n, e1, e2, st, lEp[2], gg);
+            interp_comp_adj<R, D, 3, true>(sB + 0 * fb.n, aB + 0 * fb.n, f1, f2, st, lBp[0], gg);
+            interp_comp_adj<R, D, 4, true>(sB + 1 * fb.n, aB + 1 * fb.n, f1, f2, st, lBp[1], gg);
+            interp_comp_adj<R, D, 5, true>(sB + 2 * fb.n, aB + 2 * fb.n, f1, f2, st, lBp[2], gg);
 #pragma unroll
             for (int d = 0; d < D; ++d)
                 lx1[d] += lEp[0] * g[0][d] + lEp[1] * g[1][d] + lEp[2] * g[2][d] + lBp[0] * g[3][d] +

@@ -90,6 +90,19 @@ __device__ __forceinline__ int wrap_near(int i, int n)
     return i;
 }
 
+// A value that every lane of the wave holds, in scalar registers (a load after
+// stores stays a vector load, even from one address).
+template <typename V>
+__device__ __forceinline__ V uniform(V v)
+{
+    int w[sizeof(V) / 4];
+    __builtin_memcpy(w, &v, sizeof(V));
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(V) / 4); ++k) w[k] = __builtin_amdgcn_readfirstlane(w[k]);
+    __builtin_memcpy(&v, w, sizeof(V));
+    return v;
+}
+
 // Tile (or (tile, species) segment) of this work-group in launches with one
 // work-group per tile (or segment), out of n.  The
 // dispatcher hands consecutive work-groups to the eight dies (XCDs, each

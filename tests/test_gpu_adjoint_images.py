@@ -12,8 +12,10 @@ pytestmark = pytest.mark.gpu
 CASES = [
     (1, (40,), (8,), 13),
     (2, (24, 16), (8, 8), 5),
+    (2, (32, 48), (16, 16), 3),
     (2, (20, 36), (10, 12), 3),
     (3, (8, 8, 12), (4, 8, 6), 2),
+    (3, (16, 8, 8), (8, 8, 8), 2),
 ]
 
 
