@@ -460,8 +460,8 @@ struct Impl {
         return PIC_OK;
     }
 
-    // Threads per work-group of the push: the configured block, or 2, 4, ...
-    // times it where that puts more waves on a CU.  A CU holds few groups when
+    // Threads per work-group of the push: the configured block, or a multiple of
+    // it (to 1,024) where that puts more waves on a CU.  A CU holds few groups when
     // the launch has few segments or LDS limits it; a larger group then fills
     // it (each group takes whole segments, so nothing else can).  Of equal
     // wave counts the larger group where every segment is resident at once
@@ -473,19 +473,26 @@ struct Impl {
     // 107.6 and 83.8 us with 1024; 512^2 FP64 with a block of 128 232 and 215 us
     // with 256.  1024^2 FP32 (8,192 segments) keeps 256: 512 takes 465 against
     // 451 us.
+    // Three times 256 only where it fills a CU that the LDS leaves short of waves
+    // (two groups of 8^3 FP32 tiles, 24 waves against 16: shock of 256x64x64 732
+    // and 705 us); of few segments it would take room that other streams' launches
+    // use (four boxes of 128^2 by graph replay on three streams: 103 us with 512,
+    // 119 us with 768).
     template <typename K>
     static pic_status choose_group(pic_ctx *x, K kern, size_t lds, int64_t items, int &group)
     {
         if (group) return PIC_OK;
         int best = x->block;
-        int64_t best_waves = 0;
-        for (int g = x->block; g <= 1024; g *= 2) {
+        int64_t best_waves = 0, most = 0;
+        for (int g = x->block; g <= 1024; g = g < 256 ? 2 * g : (g / 256 + 1) * 256) {
             int per_cu = 0;
             HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(kern), g, lds));
             const int64_t resident = std::max(per_cu, 1);
             const int64_t waves = std::min(resident, (items + x->n_cu - 1) / x->n_cu) * (g / 64);
-            const bool one_round = items <= (int64_t)std::max(per_cu, 1) * x->n_cu * 2;
-            if (per_cu > 0 && (waves > best_waves || (waves == best_waves && one_round))) {
+            const bool one_round = items <= resident * x->n_cu * 2;
+            const bool odd = (g & (g - 1)) && g != x->block && resident * (g / 64) <= most;
+            most = std::max(most, resident * (g / 64));
+            if (per_cu > 0 && !odd && (waves > best_waves || (waves == best_waves && one_round))) {
                 best = g;
                 best_waves = waves;
             }

@@ -513,17 +513,18 @@ __device__ __forceinline__ void push_tile(const Params<R> &p, const int w, unsig
     }
 }
 
-// Waves per SIMD the push is compiled for.
-template <typename R, int D>
+// Waves per SIMD the push is compiled for.  Two work-groups of 8^3 tiles fill
+// the LDS; with 80 registers (walls need 89 unasked) they can hold 12 waves each.
+template <typename R, int D, int TC>
 __host__ __device__ constexpr int push_waves()
 {
-    return 4;
+    return D == 3 && sizeof(R) == 4 && TC == 8 ? 6 : 4;
 }
 
 // One work-group per (tile, species) segment, segments dispatched in the
 // order k_order wrote (largest particle count first).
 template <typename R, int D, bool FUSED, bool HALFB, typename A, int TC, bool WALLS, int PUSHER>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(push_waves<R, D>(), 8))) k_push(Params<R> p)
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(push_waves<R, D, TC>(), 8))) k_push(Params<R> p)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     push_tile<R, D, FUSED, HALFB, A, TC, WALLS, PUSHER>(p, p.order[blockIdx.x], smem);
@@ -533,7 +534,7 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(push_
 // segments (largest first) from an atomic counter until every one is taken;
 // every work-group leaves the loop when the counter passes the segment count.
 template <typename R, int D, bool FUSED, bool HALFB, typename A, int TC, bool WALLS, int PUSHER>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(push_waves<R, D>(), 8)))
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(push_waves<R, D, TC>(), 8)))
 k_push_persistent(Params<R> p)
 {
     extern __shared__ __align__(16) unsigned char smem[];
