@@ -648,8 +648,12 @@ struct Impl {
         if (need_in) p.species_mask = x->pushed;   // only these species have leavers
         dim3 g((unsigned)x->L.pub.tiles_total);
         if (need_out) {
-            hipLaunchKernelGGL((pic::k_migrate_out<R, D>), dim3((unsigned)(x->L.pub.tiles_total * x->ns)), dim3(x->block), 0,
-                               x->stream, p);
+            // every group of particles ends in a scan: segments with room for
+            // many take the largest work-group (512^2, 16 particles per cell
+            // and species, FP32: 80 us with 256 threads, 70 with 512, 60)
+            const int64_t segs = x->L.pub.tiles_total * x->ns;
+            const int group = (int64_t)x->L.pub.capacity_total >= segs * 2048 ? 1024 : x->block;
+            hipLaunchKernelGGL((pic::k_migrate_out<R, D>), dim3((unsigned)segs), dim3(group), 0, x->stream, p);
             HIP_OK(hipGetLastError());
         }
         if (need_in) {
