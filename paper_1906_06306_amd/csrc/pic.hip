@@ -498,6 +498,8 @@ struct Impl {
     // 107.6 and 83.8 us with 1024; 512^2 FP64 with a block of 128 232 and 215 us
     // with 256.  1024^2 FP32 (8,192 segments) keeps 256: 512 takes 465 against
     // 451 us.
+    // No larger than the particles a segment starts with (1D, 384 segments of 192
+    // particles, FP32: push 7.7 us with 256 threads, 10.5 us with 1,024).
     // Three times 256 only where it fills a CU that the LDS leaves short of waves
     // (two groups of 8^3 FP32 tiles, 24 waves against 16: shock of 256x64x64 732
     // and 705 us); of few segments it would take room that other streams' launches
@@ -517,6 +519,7 @@ struct Impl {
             const bool one_round = items <= resident * x->n_cu * 2;
             const bool odd = (g & (g - 1)) && g != x->block && resident * (g / 64) <= most;
             most = std::max(most, resident * (g / 64));
+            if (g > x->block && (int64_t)g * items > x->L.n_input) break;
             if (per_cu > 0 && !odd && (waves > best_waves || (waves == best_waves && one_round))) {
                 best = g;
                 best_waves = waves;
@@ -648,11 +651,11 @@ struct Impl {
         if (need_in) p.species_mask = x->pushed;   // only these species have leavers
         dim3 g((unsigned)x->L.pub.tiles_total);
         if (need_out) {
-            // every group of particles ends in a scan: segments with room for
-            // many take the largest work-group (512^2, 16 particles per cell
-            // and species, FP32: 80 us with 256 threads, 70 with 512, 60)
+            // every group of particles ends in a scan: segments of many take
+            // the largest work-group (512^2, 16 particles per cell and
+            // species, FP32: 80 us with 256 threads, 70 with 512, 60)
             const int64_t segs = x->L.pub.tiles_total * x->ns;
-            const int group = (int64_t)x->L.pub.capacity_total >= segs * 2048 ? 1024 : x->block;
+            const int group = x->L.n_input >= segs * 1024 ? 1024 : x->block;
             hipLaunchKernelGGL((pic::k_migrate_out<R, D>), dim3((unsigned)segs), dim3(group), 0, x->stream, p);
             HIP_OK(hipGetLastError());
         }

@@ -81,8 +81,13 @@ __device__ __forceinline__ int wrapi(int i, int n)
     return r < 0 ? r + n : r;
 }
 
-// The same for a reach of a few cells, without the division: one turn, or a
-// few where the box is shorter than the reach.
+// The same for a reach below one box length, without the division.
+__device__ __forceinline__ int wrap_once(int i, int n)
+{
+    return i < 0 ? i + n : (i >= n ? i - n : i);
+}
+
+// The same for a halo that may be longer than a short box.
 __device__ __forceinline__ int wrap_near(int i, int n)
 {
     while (i < 0) i += n;

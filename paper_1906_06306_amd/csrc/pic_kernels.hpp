@@ -834,7 +834,7 @@ __global__ void __launch_bounds__(256) k_field(Params<R> p, R h)
         const int64_t g = at(gx, gy, gz);
         // neighbour along axis a at offset o (periodic), and the differences
         auto nb = [&](int a, int o) -> int64_t {
-            return a == 0 ? at(wrap_near(gx + o, n0), gy, gz) : a == 1 ? at(gx, wrap_near(gy + o, n1), gz) : at(gx, gy, wrap_near(gz + o, n2));
+            return a == 0 ? at(wrap_once(gx + o, n0), gy, gz) : a == 1 ? at(gx, wrap_once(gy + o, n1), gz) : at(gx, gy, wrap_once(gz + o, n2));
         };
         auto dfw = [&](const R *F, int a) -> R {
             if (a >= D) return R(0);
@@ -983,8 +983,8 @@ __global__ void __launch_bounds__(256) k_filter_direct(Params<R> p, const R *__r
                 for (int ox = -1; ox <= 1; ++ox) {
                     const R w = (ox ? R(0.25) : R(0.5)) * (D > 1 ? (oy ? R(0.25) : R(0.5)) : R(1)) *
                                 (D > 2 ? (oz ? R(0.25) : R(0.5)) : R(1));
-                    const int64_t g = td.cell0 + wrap_near(gx + ox, n0) +
-                                      (int64_t)n0 * (wrap_near(gy + oy, n1) + (int64_t)n1 * wrap_near(gz + oz, n2));
+                    const int64_t g = td.cell0 + wrap_once(gx + ox, n0) +
+                                      (int64_t)n0 * (wrap_once(gy + oy, n1) + (int64_t)n1 * wrap_once(gz + oz, n2));
                     acc[0] += w * src[g];
                     acc[1] += w * src[N + g];
                     acc[2] += w * src[2 * N + g];
