@@ -893,19 +893,7 @@ struct Impl {
         a.lJ = reinterpret_cast<R *>(x->ws + L.off_adj_lj);
         a.eblk = reinterpret_cast<R *>(x->ws + L.off_adj_eblk);
         a.bblk = reinterpret_cast<R *>(x->ws + L.off_adj_bblk);
-        const R c = (R)x->c;
-        const int64_t n3 = 3 * L.pub.cells_total;
         dim3 g((unsigned)L.pub.tiles_total), b(256);
-        // add_cur: E^{n+1} = ... - J  ->  lambda_J = -lambda_E
-        hipLaunchKernelGGL((pic::k_adj_neg<R>), dim3((unsigned)std::min<int64_t>((n3 + 255) / 256, 8192)), b, 0,
-                           x->stream, a.lJ, a.lE, n3);
-        // push_e: E^{n+1} = E^n + c curl- B^{n+1/2}  ->  lambda_B += c curl+ lambda_E
-        Params<R> q = p;
-        q.E = a.lE;
-        q.B = a.lB;
-        hipLaunchKernelGGL((pic::k_field<R, D, 0>), g, b, 0, x->stream, q, -c);
-        // push_half_b2: B^{n+1/2} = B^n - (c/2) curl+ E^n  ->  lambda_E -= (c/2) curl- lambda_B
-        hipLaunchKernelGGL((pic::k_field<R, D, 1>), g, b, 0, x->stream, q, R(-0.5) * c);
         // comp_curr, position update, Boris, interp_em per particle
         const size_t lds = 3 * (L.jblk_cells + L.fblk_cells) * sizeof(double) +
                            (6 * L.jblk_cells + 3 * L.fblk_cells) * sizeof(R);
@@ -914,9 +902,8 @@ struct Impl {
         const int edge = cubic ? x->T[0] : 0;
         pic_status st = edge == 8 ? adj_push<8>(x, p, a, lds) : edge == 16 ? adj_push<16>(x, p, a, lds) : adj_push<0>(x, p, a, lds);
         if (st) return st;
-        hipLaunchKernelGGL((pic::k_adj_fold<R, D>), g, b, 0, x->stream, p, a);
-        // push_half_b1: B^n = B^{n-1/2} - (c/2) curl+ E^n  ->  lambda_E -= (c/2) curl- lambda_B^n
-        hipLaunchKernelGGL((pic::k_field<R, D, 1>), g, b, 0, x->stream, q, R(-0.5) * c);
+        hipLaunchKernelGGL((pic::k_adj_fields<R, D, true>), g, b, 0, x->stream, p, a);
+        hipLaunchKernelGGL((pic::k_adj_fields<R, D, false>), g, b, 0, x->stream, p, a);
         HIP_OK(hipGetLastError());
         return PIC_OK;
     }

@@ -310,7 +310,7 @@ template <typename R>
 struct AdjParams {
     R *lpos, *lu;             // [D|3][cap_total], layout of the state
     R *lE, *lB;               // [3][cells_total]
-    R *lJ;                    // [3][cells_total] scratch: lambda of J = -lambda_E
+    R *lJ;                    // [3][cells_total] scratch: lambda_B between the two halves of k_adj_fields
     R *eblk, *bblk;           // per tile [3][(T+3)^D], [3][(T+2)^D] adjoint blocks
     R *opos, *ou;             // [D|3][ostride] particle adjoints at the slots the particles
     int64_t ostride;          // came from (Params::ids), or null: in place
@@ -346,7 +346,8 @@ __global__ void __launch_bounds__((adj_block<R, D>())) k_adj_push(Params<R> p, A
     R *sB = sE + 3 * cb.n;                                   // [3][fb.n]
     stage_block<R, D>(p.E, p.cells_total, td, T, sE, cb);
     stage_block<R, D>(p.B, p.cells_total, td, T, sB, fb);
-    stage_block<R, D>(a.lJ, p.cells_total, td, T, sLJ, cb);
+    // add_cur: E^{n+1} = ... - J, so lambda_J = -lambda_E
+    stage_block<R, D, true>(a.lE, p.cells_total, td, T, sLJ, cb);
     for (int k = threadIdx.x; k < 3 * cb.n; k += blockDim.x) aE[k] = 0.0;
     for (int k = threadIdx.x; k < 3 * fb.n; k += blockDim.x) aB[k] = 0.0;
     __syncthreads();
@@ -457,69 +458,89 @@ __global__ void __launch_bounds__((adj_block<R, D>())) k_adj_push(Params<R> p, A
     for (int k = threadIdx.x; k < 3 * fb.n; k += blockDim.x) bb[k] = (R)aB[k];
 }
 
-// Add the folded adjoint blocks into the field adjoints: the E-type block
-// covers local cells -1..T+1, the B-type block -1..T.
-template <typename R, int D>
-__global__ void __launch_bounds__(256) k_adj_fold(Params<R> p, AdjParams<R> a)
+// Sum over the neighbours' blocks of the adjoint entries of component m at the
+// tile's cell l: blocks of edges T + HI per dimension from local cell -1 (E:
+// HI = 3, B: HI = 2).
+template <typename R, int D, int HI>
+__device__ __forceinline__ R adj_block_sum(const R *blk, const TileDesc &td, const int32_t T[3], const int l[3], int m)
 {
-    const int t = blockIdx.x;
-    const TileDesc td = p.tiles[t];
-    const CurBox<D> cb(p.T);
-    const FieldBox<D> fb(p.T);
-    const int T0 = p.T[0], T1 = D > 1 ? p.T[1] : 1, T2 = D > 2 ? p.T[2] : 1;
-    const int ncell = T0 * T1 * T2;
-    for (int k = threadIdx.x; k < ncell; k += blockDim.x) {
-        const int l[3] = {k % T0, (k / T0) % T1, k / (T0 * T1)};
-        R acc[6] = {0, 0, 0, 0, 0, 0};
-        for (int oz = (D > 2 ? -1 : 0); oz <= (D > 2 ? 1 : 0); ++oz)
-            for (int oy = (D > 1 ? -1 : 0); oy <= (D > 1 ? 1 : 0); ++oy)
-                for (int ox = -1; ox <= 1; ++ox) {
-                    const int o[3] = {ox, oy, oz};
-                    int bi[3] = {0, 0, 0}, nc[3] = {0, 0, 0};
-                    bool inE = true, inB = true;
+    const int e0 = T[0] + HI, e1 = D > 1 ? T[1] + HI : 1, n = e0 * e1 * (D > 2 ? T[2] + HI : 1);
+    R acc = R(0);
 #pragma unroll
-                    for (int d = 0; d < 3; ++d) {
-                        if (d < D) {
-                            bi[d] = l[d] - o[d] * p.T[d] + 1;
-                            inE = inE && bi[d] >= 0 && bi[d] < p.T[d] + 3;
-                            inB = inB && bi[d] >= 0 && bi[d] < p.T[d] + 2;
-                            nc[d] = wrapi(td.tc[d] + o[d], td.nt[d]);
-                        }
-                    }
-                    if (!inE) continue;
-                    const int nid = td.tile0 + nc[0] + td.nt[0] * (nc[1] + td.nt[1] * nc[2]);
-                    const R *eb = a.eblk + (int64_t)nid * 3 * cb.n;
-                    const int ie = bi[0] + cb.e0 * (bi[1] + cb.e1 * bi[2]);
-                    acc[0] += eb[ie];
-                    acc[1] += eb[cb.n + ie];
-                    acc[2] += eb[2 * cb.n + ie];
-                    if (inB) {
-                        const R *bb = a.bblk + (int64_t)nid * 3 * fb.n;
-                        const int ib = bi[0] + fb.e0 * (bi[1] + fb.e1 * bi[2]);
-                        acc[3] += bb[ib];
-                        acc[4] += bb[fb.n + ib];
-                        acc[5] += bb[2 * fb.n + ib];
-                    }
+    for (int oz = (D > 2 ? -1 : 0); oz <= (D > 2 ? 1 : 0); ++oz)
+#pragma unroll
+        for (int oy = (D > 1 ? -1 : 0); oy <= (D > 1 ? 1 : 0); ++oy)
+#pragma unroll
+            for (int ox = -1; ox <= 1; ++ox) {
+                const int o[3] = {ox, oy, oz};
+                int bi[3] = {0, 0, 0}, nc[3] = {0, 0, 0};
+                bool in = true;
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    bi[d] = l[d] - o[d] * T[d] + 1;
+                    in = in && bi[d] >= 0 && bi[d] < T[d] + HI;
+                    nc[d] = wrap_once(td.tc[d] + o[d], td.nt[d]);
                 }
-        const int gx = td.tc[0] * T0 + l[0];
-        const int gy = D > 1 ? td.tc[1] * T1 + l[1] : 0;
-        const int gz = D > 2 ? td.tc[2] * T2 + l[2] : 0;
-        const int64_t g = td.cell0 + gx + (int64_t)td.n[0] * (gy + (int64_t)td.n[1] * gz);
-        const int64_t N = p.cells_total;
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-            a.lE[m * N + g] += acc[m];
-            a.lB[m * N + g] += acc[3 + m];
-        }
-    }
+                const int64_t nid = td.tile0 + nc[0] + td.nt[0] * (nc[1] + (int64_t)td.nt[1] * nc[2]);
+                if (in) acc += blk[(nid * 3 + m) * n + bi[0] + e0 * (bi[1] + e1 * bi[2])];
+            }
+    return acc;
 }
 
-// lambda_J = -lambda_E (the current enters E^{n+1} with a minus sign).
-template <typename R>
-__global__ void k_adj_neg(R *dst, const R *src, int64_t n)
+// The field rows of the reversed step, from its end, after k_adj_push (which
+// reads lambda_E as it enters the step).  Two launches in place of five: each
+// is one or two memory latencies, a launch costs as much (a step of the 256^2
+// shear layer: 31 us in five launches, 12 us in two).
+//
+// FIRST: push_e, E^{n+1} = E^n + c curl- B^{n+1/2}: lambda_B += c curl+
+// lambda_E, kept in lJ for the other launch; then the particles' part of
+// lambda_B.
+// Second: push_half_b2 and push_half_b1, B -= (c/2) curl+ E^n: lambda_E -= (c/2)
+// curl- lambda_B with lambda_B before and after the particles' part, which for
+// lambda_E comes in between.
+// One thread per cell and component.
+template <typename R, int D, bool FIRST>
+__global__ void __launch_bounds__(256) k_adj_fields(Params<R> p, AdjParams<R> a)
 {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        dst[i] = -src[i];
+    const int t = xcd_tile(blockIdx.x, gridDim.x);
+    const TileDesc td = p.tiles[t];
+    const int32_t T[3] = {p.T[0], D > 1 ? p.T[1] : 1, D > 2 ? p.T[2] : 1};
+    const int ncell = T[0] * T[1] * T[2];
+    const float inv0 = 1.0f / T[0], inv1 = 1.0f / T[1], invc = 1.0f / ncell;
+    const int64_t N = p.cells_total;
+    const R h = R(-0.5) * p.c;
+    for (int k = threadIdx.x; k < 3 * ncell; k += blockDim.x) {
+        const int m = div_small(k, invc);
+        int l[3];
+        cell_of<D>(k - m * ncell, T[0], T[1], inv0, inv1, l[0], l[1], l[2]);
+        const int i = m == 2 ? 0 : m + 1, j = m == 0 ? 2 : m - 1;   // curl_m F = d_i F_j - d_j F_i
+        int g3[3] = {0, 0, 0};
+#pragma unroll
+        for (int d = 0; d < D; ++d) g3[d] = td.tc[d] * T[d] + l[d];
+        auto at = [&](int axis, int o) -> int64_t {
+            const int x = axis == 0 ? wrap_once(g3[0] + o, td.n[0]) : g3[0];
+            const int y = D > 1 && axis == 1 ? wrap_once(g3[1] + o, td.n[1]) : g3[1];
+            const int z = D > 2 && axis == 2 ? wrap_once(g3[2] + o, td.n[2]) : g3[2];
+            return td.cell0 + x + (int64_t)td.n[0] * (y + (int64_t)td.n[1] * z);
+        };
+        const int64_t g = at(0, 0);
+        // neighbours along i and j; the cell itself along axes that are no grid dimension
+        const int64_t gi = at(i, FIRST ? 1 : -1), gj = at(j, FIRST ? 1 : -1);
+        if constexpr (FIRST) {
+            const R *Fi = a.lE + i * N, *Fj = a.lE + j * N;
+            const R curl = (Fj[gi] - Fj[g]) - (Fi[gj] - Fi[g]);
+            const R b = fma(p.c, curl, a.lB[m * N + g]);
+            a.lJ[m * N + g] = b;
+            a.lB[m * N + g] = b + adj_block_sum<R, D, 2>(a.bblk, td, T, l, m);
+        } else {
+            auto curl = [&](const R *F) -> R {
+                const R *Fi = F + i * N, *Fj = F + j * N;
+                return (Fj[g] - Fj[gi]) - (Fi[g] - Fi[gj]);
+            };
+            const R e = fma(h, curl(a.lJ), a.lE[m * N + g]) + adj_block_sum<R, D, 3>(a.eblk, td, T, l, m);
+            a.lE[m * N + g] = fma(h, curl(a.lB), e);
+        }
+    }
 }
 
 // The state regions that a reversed window keeps of every step, in the

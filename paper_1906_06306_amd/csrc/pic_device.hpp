@@ -326,8 +326,8 @@ __device__ __forceinline__ int64_t halo_cell(const TileDesc &td, const int32_t T
 }
 
 // Copy three planes of the tile's halo block into LDS, periodic wrap; dst
-// layout [3][bx.n].
-template <typename R, int D, typename BoxT>
+// layout [3][bx.n].  NEG: with the opposite sign.
+template <typename R, int D, bool NEG = false, typename BoxT>
 __device__ __forceinline__ void stage_block(const R *__restrict__ src, int64_t N, const TileDesc &td,
                                             const int32_t T[3], R *dst, const BoxT &bx)
 {
@@ -337,7 +337,7 @@ __device__ __forceinline__ void stage_block(const R *__restrict__ src, int64_t N
         cell_of<D>(k, bx.e0, bx.e1, inv0, inv1, lx, ly, lz);
         const int64_t g = halo_cell<D>(td, T, lx, ly, lz);
 #pragma unroll
-        for (int m = 0; m < 3; ++m) dst[m * bx.n + k] = src[m * N + g];
+        for (int m = 0; m < 3; ++m) dst[m * bx.n + k] = NEG ? -src[m * N + g] : src[m * N + g];
     }
 }
 
