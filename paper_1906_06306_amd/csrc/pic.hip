@@ -751,7 +751,7 @@ struct Impl {
         if (!st) st = set_lds(pic::k_bin_hist, lds);
         if (st) return st;
         hipLaunchKernelGGL(pic::k_bin_hist, dim3(g.nchunks), dim3(256), lds, x->stream, g, key, hist);
-        hipLaunchKernelGGL(pic::k_bin_scan, dim3((g.ntb + 255) / 256), dim3(256), 0, x->stream, g, hist, p.seg_cnt,
+        hipLaunchKernelGGL(pic::k_bin_scan, dim3((g.ntb + 63) / 64), dim3(64), 0, x->stream, g, hist, p.seg_cnt,
                            p.seg_cap, (int)L.box_tile0[b], x->ns, s, p.err);
         st = set_lds(pic::k_bin_scatter<R, D>, lds);
         if (st) return st;

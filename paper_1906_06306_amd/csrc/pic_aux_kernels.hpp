@@ -173,16 +173,27 @@ __global__ void k_bin_hist(BinGeom g, const int32_t *key, int32_t *hist)
 }
 
 // Chunk start offsets per tile, in (tile, chunk) order, and segment counts.
-__global__ void k_bin_scan(BinGeom g, int32_t *hist, int32_t *seg_cnt, const int32_t *seg_cap, int tile0,
+// One thread per tile; SCAN_AHEAD chunks are loaded before the first of them is
+// overwritten (one by one, each load waits for the store before it: 1,024
+// tiles and 1,024 chunks 241 us, now 41 us).
+constexpr int SCAN_AHEAD = 32;
+
+__global__ void __launch_bounds__(64) k_bin_scan(BinGeom g, int32_t *hist, int32_t *seg_cnt, const int32_t *seg_cap, int tile0,
                            int nspecies, int species, int32_t *err)
 {
     for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < g.ntb; k += gridDim.x * blockDim.x) {
         const int ts = (tile0 + k) * nspecies + species;
         int run = seg_cnt[ts];
-        for (int c = 0; c < g.nchunks; ++c) {
-            int v = hist[(int64_t)c * g.ntb + k];
-            hist[(int64_t)c * g.ntb + k] = run;
-            run += v;
+        for (int c0 = 0; c0 < g.nchunks; c0 += SCAN_AHEAD) {
+            int v[SCAN_AHEAD];
+#pragma unroll
+            for (int j = 0; j < SCAN_AHEAD; ++j) v[j] = hist[(int64_t)min(c0 + j, g.nchunks - 1) * g.ntb + k];
+#pragma unroll
+            for (int j = 0; j < SCAN_AHEAD; ++j) {
+                if (c0 + j >= g.nchunks) break;
+                hist[(int64_t)(c0 + j) * g.ntb + k] = run;
+                run += v[j];
+            }
         }
         if (run > seg_cap[ts]) {
             latch(err, ERR_CAPACITY);
@@ -193,7 +204,9 @@ __global__ void k_bin_scan(BinGeom g, int32_t *hist, int32_t *seg_cnt, const int
 }
 
 // Stable scatter: one wave per chunk walks its particles in order, 64 at a
-// time; equal keys among the 64 lanes are ranked with ballots.
+// time; equal keys among the 64 lanes are ranked with ballots.  The next 64 are
+// loaded before the stores of the present ones (4.2 million particles of 512^2
+// cells, FP32: 168 us in turn, 128 us).
 template <typename R, int D>
 __global__ void __launch_bounds__(64) k_bin_scatter(BinGeom g, const int32_t *key, const R *xl, const double *u64,
                                                     const int32_t *hist, Params<R> p, int tile0, int species)
@@ -212,9 +225,30 @@ __global__ void __launch_bounds__(64) k_bin_scatter(BinGeom g, const int32_t *ke
     const int64_t lo = (int64_t)blockIdx.x * g.chunk, hi = min(g.count, lo + g.chunk);
     const int lane = threadIdx.x;
     const int64_t cap = p.cap_total;
+    int nk = -1;
+    R nx[D];
+    double nu[3];
+    auto load = [&](int64_t i) {
+        nk = -1;
+        if (i < hi) {
+            nk = key[i];
+#pragma unroll
+            for (int d = 0; d < D; ++d) nx[d] = xl[d * g.count + i];
+#pragma unroll
+            for (int mm = 0; mm < 3; ++mm) nu[mm] = u64[mm * g.count + i];
+        }
+    };
+    load(lo + lane);
     for (int64_t base = lo; base < hi; base += 64) {
         const int64_t i = base + lane;
-        const int k = i < hi ? key[i] : -1;
+        const int k = nk;
+        R x[D];
+        double u[3];
+#pragma unroll
+        for (int d = 0; d < D; ++d) x[d] = nx[d];
+#pragma unroll
+        for (int mm = 0; mm < 3; ++mm) u[mm] = nu[mm];
+        load(i + 64);
         const bool valid = k >= 0;
         unsigned long long m = __ballot(valid);
         for (int b = 0; b < nbits; ++b) {
@@ -239,9 +273,9 @@ __global__ void __launch_bounds__(64) k_bin_scatter(BinGeom g, const int32_t *ke
             if (slot < p.seg_cap[ts]) {
                 const int64_t dst = p.seg_off[ts] + slot;
 #pragma unroll
-                for (int d = 0; d < D; ++d) p.pos[d * cap + dst] = xl[d * g.count + i];
+                for (int d = 0; d < D; ++d) p.pos[d * cap + dst] = x[d];
 #pragma unroll
-                for (int mm = 0; mm < 3; ++mm) p.u[mm * cap + dst] = (R)u64[mm * g.count + i];
+                for (int mm = 0; mm < 3; ++mm) p.u[mm * cap + dst] = (R)u[mm];
                 if (p.ids) p.ids[dst] = g.id_base < 0 ? -1 : (int32_t)(g.id_base + i);   // index in the concatenated input
             }
         }
