@@ -1352,8 +1352,9 @@ pic_status pic_step(pic_ctx *x, uint32_t flags)
     if (!x) return fail(PIC_E_ARG, "null context");
     if (x->order == 4) flags &= ~PIC_PUSH_HALF_B;   // the in-LDS half update is second order
     flags &= ~PIC_DEPOSIT_CURL_E;                    // chosen below
+    const bool untracked_sort = x->track && (flags & PIC_SORT_CELLS);   // refused by pic_sort_migrate
     if (flags & PIC_PUSH_HALF_B) {
-        if ((flags & PIC_FUSED) && x->order == 2 && !x->filter_passes && x->state == 0) {
+        if ((flags & PIC_FUSED) && x->order == 2 && !x->filter_passes && x->state == 0 && !untracked_sort) {
             // two launches: the push, which also leaves B after both half
             // updates in the filter's scratch planes, and the rest of the
             // step.  After the push, half B, fold with E and migration as

@@ -94,3 +94,16 @@ def test_field_layouts_match_oracle(D, n, T, ppc, prec):
     for x, y in zip(sim.fields_host(0), (st.E, st.B, st.J)):
         assert np.linalg.norm(x - y) <= tol * np.linalg.norm(y)
     sim.close()
+
+
+@pytest.mark.parametrize("kw", [{}, dict(fdtd_order=4), dict(filter_passes=2)])
+def test_whole_step_refuses_cell_sort_with_tracking(kw):
+    """The cell sort does not record origins: a tracked step with it is an
+    error however the step is launched."""
+    from paper_1906_06306_amd import _lib as L
+    from paper_1906_06306_amd.sim import PicSim
+    sim = PicSim(synth.small_random(2, (32, 16), 3, seed=5), tile=(8, 8), precision="fp32", options=L.PIC_OPT_TRACK,
+                 **kw)
+    flags = L.PIC_FUSED | L.PIC_PUSH_HALF_B | L.PIC_SORT_CELLS
+    assert L.lib().pic_step(sim.ctx, flags) == L.PIC_E_ARG
+    sim.close()
