@@ -643,6 +643,32 @@ struct Impl {
         return PIC_OK;
     }
 
+    // The rest of a fused step with FDTD4 or the current filter, after the
+    // push: fold with the B update, filter, E update with the arrivals (two
+    // launches fewer than one by one: 500x336, eight passes, FDTD4, FP32
+    // 79.5 and 72.8 us).  two_halves: B after both half updates (the push took the
+    // first in LDS).
+    template <int ORDER>
+    static pic_status finish_rows_order(pic_ctx *x, bool two_halves)
+    {
+        Params<R> p = params<R>(x);
+        const R c = (R)x->c;
+        const dim3 g((unsigned)(2 * x->L.pub.tiles_total)), b(256);
+        if (two_halves) hipLaunchKernelGGL((pic::k_fold_b<R, D, 4, ORDER>), g, b, 0, x->stream, p, R(0.5) * c);
+        else hipLaunchKernelGGL((pic::k_fold_b<R, D, 0, ORDER>), g, b, 0, x->stream, p, R(0.5) * c);
+        pic_status st = x->filter_passes ? filter(x, x->filter_passes) : PIC_OK;
+        if (st) return st;
+        const dim3 ga((unsigned)(x->L.pub.tiles_total * (1 + x->ns)));
+        hipLaunchKernelGGL((pic::k_e_arrivals<R, D, ORDER>), ga, b, 0, x->stream, p, c);
+        HIP_OK(hipGetLastError());
+        return PIC_OK;
+    }
+
+    static pic_status finish_rows(pic_ctx *x, bool two_halves)
+    {
+        return x->order == 4 ? finish_rows_order<4>(x, two_halves) : finish_rows_order<2>(x, two_halves);
+    }
+
     static pic_status migrate(pic_ctx *x, bool need_out, bool need_in, bool sort, int32_t *mig_counts,
                               int64_t *flagged, int64_t flagged_cap)
     {
@@ -1088,6 +1114,7 @@ pic_status do_migrate(pic_ctx *x, bool out, bool in, bool sort, int32_t *mc, int
 {
     PIC_DISPATCH(x, migrate(x, out, in, sort, mc, fl, fcap));
 }
+pic_status do_finish_rows(pic_ctx *x, bool two_halves) { PIC_DISPATCH(x, finish_rows(x, two_halves)); }
 pic_status do_diag(pic_ctx *x, pic_diag *o, bool per_box, int32_t *bits) { PIC_DISPATCH(x, diag(x, o, per_box, bits)); }
 pic_status do_diag_static(pic_ctx *x, pic_diag *o) { PIC_DISPATCH(x, diag_static(x, o)); }
 pic_status do_adjoint(pic_ctx *x, void *a, void *b, void *c, void *d, const void *im, void *op, void *ou, int64_t os)
@@ -1346,6 +1373,15 @@ static pic_status current_and_e(pic_ctx *x, uint32_t flags)
     return pic_fdtd_step(x, PIC_CURL_E_ADD_J);
 }
 
+// After the last row of a fused step: the arrivals are in.
+static pic_status end_step(pic_ctx *x, uint32_t flags)
+{
+    x->state = 0;
+    x->pushed = 0;
+    ++x->steps;
+    return flags & PIC_SORT_CELLS ? do_migrate(x, false, false, true, nullptr, nullptr, 0) : PIC_OK;
+}
+
 pic_status pic_step(pic_ctx *x, uint32_t flags)
 {
     pic_status st;
@@ -1353,6 +1389,8 @@ pic_status pic_step(pic_ctx *x, uint32_t flags)
     if (x->order == 4) flags &= ~PIC_PUSH_HALF_B;   // the in-LDS half update is second order
     flags &= ~PIC_DEPOSIT_CURL_E;                    // chosen below
     const bool untracked_sort = x->track && (flags & PIC_SORT_CELLS);   // refused by pic_sort_migrate
+    const bool rows =
+        (flags & PIC_FUSED) && (x->order == 4 || x->filter_passes) && x->state == 0 && !untracked_sort;
     if (flags & PIC_PUSH_HALF_B) {
         if ((flags & PIC_FUSED) && x->order == 2 && !x->filter_passes && x->state == 0 && !untracked_sort) {
             // two launches: the push, which also leaves B after both half
@@ -1361,26 +1399,24 @@ pic_status pic_step(pic_ctx *x, uint32_t flags)
             // launches of their own took 12.6 us (1D, 512 cells FP64), 17 us
             // (2D 256^2 FP32), 69 us (2D 1024^2 FP32) and 126 us (3D
             // 256x64x64 with walls FP32), the one launch 4.0, 5.9, 54.6 and
-            // 89 us.  FDTD4 and the current filter, whose rows come between,
-            // keep the separate launches.
+            // 89 us.
             x->step_b = true;
             st = pic_push_interp(x, PIC_ALL_SPECIES, flags);
             x->step_b = false;
             if (st || (st = do_finish_step(x))) return st;
-            x->state = 0;
-            x->pushed = 0;
-            ++x->steps;
-            return flags & PIC_SORT_CELLS ? do_migrate(x, false, false, true, nullptr, nullptr, 0) : PIC_OK;
+            return end_step(x, flags);
         }
         // push_half_b1 happens inside the push on its LDS copy of B; both
         // half updates are then applied to the stored B in one pass
         if ((st = pic_push_interp(x, PIC_ALL_SPECIES, flags))) return st;
+        if (rows) return (st = do_finish_rows(x, true)) ? st : end_step(x, flags);
         if ((st = pic_fdtd_step(x, PIC_TWO_HALF_B))) return st;
         if ((st = current_and_e(x, flags))) return st;
         return pic_sort_migrate(x, flags, nullptr, nullptr, 0);
     }
     if ((st = pic_fdtd_step(x, PIC_HALF_B))) return st;
     if ((st = pic_push_interp(x, PIC_ALL_SPECIES, flags))) return st;
+    if (rows) return (st = do_finish_rows(x, false)) ? st : end_step(x, flags);
     if ((st = pic_fdtd_step(x, PIC_HALF_B))) return st;
     if ((st = current_and_e(x, flags))) return st;
     return pic_sort_migrate(x, flags, nullptr, nullptr, 0);

@@ -815,10 +815,9 @@ __global__ void __launch_bounds__(256) k_fold(Params<R> p, R h)
 // PHASE 3: E += h curl- B - J.  PHASE 4: B -= h curl+ E twice (both half
 // updates of Table 1 in one pass, same arithmetic as two PHASE 0 passes).
 // (Eqs. fdB/fdE with the differences of App. B.)
-template <typename R, int D, int PHASE, int ORDER = 2>
-__global__ void __launch_bounds__(256) k_field(Params<R> p, R h)
+template <typename R, int D, int PHASE, int ORDER>
+__device__ __forceinline__ void field_tile(const Params<R> &p, R h, const int t)
 {
-    const int t = xcd_tile(blockIdx.x, gridDim.x);
     const TileDesc td = p.tiles[t];
     const int T0 = p.T[0], T1 = D > 1 ? p.T[1] : 1, T2 = D > 2 ? p.T[2] : 1;
     const int ncell = T0 * T1 * T2;
@@ -893,6 +892,21 @@ __global__ void __launch_bounds__(256) k_field(Params<R> p, R h)
             curl_b_update_e<R, D, PHASE == 3>(p, td, gx, gy, gz, g, h, j);
         }
     }
+}
+
+template <typename R, int D, int PHASE, int ORDER = 2>
+__global__ void __launch_bounds__(256) k_field(Params<R> p, R h)
+{
+    field_tile<R, D, PHASE, ORDER>(p, h, xcd_tile(blockIdx.x, gridDim.x));
+}
+
+// Fold of the current and, by the launch's second half of work-groups, the B
+// update (PHASE 0 or 4) of a fused step: neither reads what the other writes.
+template <typename R, int D, int PHASE, int ORDER>
+__global__ void __launch_bounds__(256) k_fold_b(Params<R> p, R h)
+{
+    if ((int)blockIdx.x < p.ntiles) fold_tile<R, D, false, false>(p, R(0), xcd_tile(blockIdx.x, p.ntiles));
+    else field_tile<R, D, PHASE, ORDER>(p, h, xcd_tile(blockIdx.x - p.ntiles, p.ntiles));
 }
 
 // Binomial current filter (the solver table's 3-point digital filter): one
@@ -1190,6 +1204,14 @@ template <typename R, int D>
 __global__ void __launch_bounds__(256) k_finish_step(Params<R> p, R h)
 {
     if ((int)blockIdx.x < p.ntiles) fold_tile<R, D, true, true>(p, h, xcd_tile(blockIdx.x, p.ntiles));
+    else receive_segment<R, D>(p, xcd_tile(blockIdx.x - p.ntiles, gridDim.x - p.ntiles));
+}
+
+// E update with the folded (and filtered) current, and the arrivals, likewise.
+template <typename R, int D, int ORDER>
+__global__ void __launch_bounds__(256) k_e_arrivals(Params<R> p, R h)
+{
+    if ((int)blockIdx.x < p.ntiles) field_tile<R, D, 3, ORDER>(p, h, xcd_tile(blockIdx.x, p.ntiles));
     else receive_segment<R, D>(p, xcd_tile(blockIdx.x - p.ntiles, gridDim.x - p.ntiles));
 }
 
