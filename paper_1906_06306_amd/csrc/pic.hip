@@ -32,7 +32,9 @@ constexpr int64_t MAX_SLOTS = int64_t(1) << 28;
 // the segments' visiting order (largest first) only balances the push: any
 // permutation gives the same results, and counts change by a few percent a
 // step, so it is recomputed every ORDER_EVERY pushes, at the first push after
-// init or an injection, and at every push captured into a graph
+// init or an injection, and likewise inside a captured graph from its first push
+// on (a replay of four steps on one stream, four boxes of 256 tiles in all, FP32:
+// 179 us with an order at every captured push, 170 us)
 constexpr int ORDER_EVERY = 8;
 
 // text of the last error on this thread (a fixed buffer: reporting an
@@ -309,7 +311,6 @@ struct pic_ctx {
     int order;          // FDTD order: 2 (App. B) or 4 (FDTD4)
     int64_t steps;      // completed steps
     int order_age;      // pushes since the visiting order was recomputed
-    bool capturing;     // pic_graph_capture is recording steps
     int64_t diag_step;  // steps at the last diagnostics call, or -1
     int n_cu;           // compute units of the device
     int push_group[2];  // threads per work-group of the unfused / fused push, 0 until its first launch
@@ -537,7 +538,7 @@ struct Impl {
         size_t lds = push_lds<TC>(x, p, FUSED, sizeof(A));
         int &group = x->push_group[FUSED];
         const int64_t items = x->L.pub.tiles_total * x->ns;
-        if (x->capturing || x->order_age >= ORDER_EVERY) {
+        if (x->order_age >= ORDER_EVERY) {
             pic_status st0 = order_segments(x, p);
             if (st0) return st0;
             x->order_age = 0;
@@ -1222,7 +1223,6 @@ pic_status pic_init_tiles(const pic_config *cfg, const int64_t *counts, void *wo
     x->order = cfg->fdtd_order == 4 ? 4 : 2;
     x->steps = 0;
     x->order_age = ORDER_EVERY;
-    x->capturing = false;
     x->diag_step = -1;
     x->pin = nullptr;
     for (int b = 0; cfg->box_walls && b < cfg->n_boxes; ++b) x->walls = x->walls || (cfg->box_walls[b] & PIC_WALL_X);
@@ -1459,9 +1459,11 @@ pic_status pic_graph_capture(pic_ctx *x, int32_t nsteps, uint32_t flags)
     HIP_OK(hipStreamSynchronize(x->stream));
     const int64_t steps_before = x->steps;   // captured steps do not run now
     HIP_OK(hipStreamBeginCapture(x->stream, hipStreamCaptureModeThreadLocal));
-    x->capturing = true;
+    // the first captured push takes a new order, a later eager one too (replays
+    // change the counts)
+    x->order_age = ORDER_EVERY;
     for (int k = 0; k < nsteps && !st; ++k) st = pic_step(x, flags);
-    x->capturing = false;
+    x->order_age = ORDER_EVERY;
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(x->stream, &g);
     x->steps = steps_before;
