@@ -523,6 +523,12 @@ __host__ __device__ constexpr int push_waves()
 
 // One work-group per (tile, species) segment, segments dispatched in the
 // order k_order wrote (largest particle count first).
+// 1024^2 cells, 33.5 million particles, FP32: 390-397 us for 1.38 GB that it cannot
+// do without (1.65 GB moved), bound by the particle stream and its compaction:
+// without gathers and deposit it takes as long, without compaction 340 us, and a
+// plain copy of the bytes 292 us.  8^3 tiles with walls, 29 million particles:
+// 598 us (606 us with 512 threads and launches of their own for B and the arrivals), vector
+// ALU 73% and LDS 69% busy.
 template <typename R, int D, bool FUSED, bool HALFB, typename A, int TC, bool WALLS, int PUSHER>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(push_waves<R, D, TC>(), 8))) k_push(Params<R> p)
 {
