@@ -38,6 +38,7 @@ METRIC = "particle-steps/sec (push+deposit+FDTD) FP32 vs FP64 at 1 GPU; % HBM ro
 # particles per cell: any other kernel code reports no traffic.
 MEASURED_PUSH_TRAFFIC = {
     ("78bcdb30f7e1fc3e", "fp32", 16, 1024, 16): 1654027904,
+    ("78bcdb30f7e1fc3e", "fp32", 32, 1024, 16): 1543251135,
     ("78bcdb30f7e1fc3e", "fp64", 16, 1024, 16): 3154948140,
 }
 
@@ -47,6 +48,7 @@ MEASURED_PUSH_TRAFFIC = {
 # clocks per SIMD (16 lanes; FP32 not packed) at 2.4 GHz
 MEASURED_PUSH_VALU_PER_64 = {
     ("78bcdb30f7e1fc3e", "fp32", 16, 1024, 16): 341.5,
+    ("78bcdb30f7e1fc3e", "fp32", 32, 1024, 16): 338.2,
     ("78bcdb30f7e1fc3e", "fp64", 16, 1024, 16): 388.7,
 }
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4
