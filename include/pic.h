@@ -445,7 +445,8 @@ pic_status pic_adjoint_step(pic_ctx *ctx, void *lpos, void *lu, void *lE, void *
  * the slots in use.  pic_state_bytes gives the size of the caller's device
  * buffer (256-byte aligned; its layout is private to a context's
  * configuration).  Both copies need PIC_OPT_TRACK and only enqueue work;
- * loading leaves the slots beyond the counts as they are. */
+ * loading leaves the slots beyond the counts as they are and adds the image's
+ * error bits to the latched ones, of which it clears none. */
 pic_status pic_state_bytes(pic_ctx *ctx, uint64_t *bytes);
 pic_status pic_state_save(pic_ctx *ctx, void *image);
 pic_status pic_state_load(pic_ctx *ctx, const void *image);

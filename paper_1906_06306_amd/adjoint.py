@@ -47,7 +47,8 @@ def backward(sim: PicSim, ckpts: dict, nsteps: int, lE, lB, lpos=None, lu=None, 
     simulation must hold the final state on entry.  Returns (lpos_in (D,
     n_input), lu_in (3, n_input), lE0, lB0) in the working precision, the
     particle adjoints in the concatenated input order.  Leaves the initial
-    state in the workspace."""
+    state in the workspace, and every error bit that the sweep latched: with
+    one of them (``sim.error()``) the adjoints are not valid."""
     fn = L.lib().pic_step
     la, ua, _, _ = sim.adjoint_buffers()
     lb, ub, _, _ = sim.adjoint_buffers()

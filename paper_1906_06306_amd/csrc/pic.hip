@@ -875,7 +875,8 @@ struct Impl {
         const int64_t cells = x->L.pub.cells_total;
         const unsigned nf = (unsigned)std::min<int64_t>(std::max<int64_t>(1, (3 * cells + 1023) / 1024), 2048);
         hipLaunchKernelGGL((pic::k_state_copy<R, D>), dim3((unsigned)nseg + nf), dim3(256), 0, x->stream,
-                           save ? im : ws, save ? ws : im, p.seg_off, nseg, x->L.pub.capacity_total, cells);
+                           save ? im : ws, save ? ws : im, p.seg_off, nseg, x->L.pub.capacity_total, cells,
+                           save ? 0 : 1);
         HIP_OK(hipGetLastError());
         return PIC_OK;
     }

@@ -555,10 +555,11 @@ struct StateView {
 // the slots in use (planes have room for the densest the plasma gets: copying
 // them whole moved 2.1 times the bytes on the shear window).  The first
 // work-groups take a segment each, 16 (32 at FP64) bytes a lane; the rest
-// the fields.
+// the fields.  With merge the source's error bits are added to the
+// destination's: a load clears none that was latched since.
 template <typename R, int D>
 __global__ void __launch_bounds__(256) k_state_copy(StateView<R> dst, StateView<R> src, const int64_t *seg_off,
-                                                    int32_t nseg, int64_t cap, int64_t cells)
+                                                    int32_t nseg, int64_t cap, int64_t cells, int32_t merge)
 {
     struct alignas(16) Quad {
         R v[4];
@@ -573,7 +574,10 @@ __global__ void __launch_bounds__(256) k_state_copy(StateView<R> dst, StateView<
             dst.E[i] = e;
             dst.B[i] = b;
         }
-        if ((int)blockIdx.x == nseg && threadIdx.x == 0) *dst.err = *src.err;
+        if ((int)blockIdx.x == nseg && threadIdx.x == 0) {
+            if (merge) latch(dst.err, *src.err);
+            else *dst.err = *src.err;
+        }
         return;
     }
     const int ts = blockIdx.x;

@@ -1,0 +1,67 @@
+"""Errors latched during a reverse sweep reach the caller: loading a state
+image adds the image's error bits to the workspace's and clears none."""
+import numpy as np
+import pytest
+
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def tracked(n=(24, 16), **kw):
+    from paper_1906_06306_amd import _lib as L
+    from paper_1906_06306_amd.sim import PicSim
+    plasma = synth.small_random(2, n, 5, theta=0.4, seed=9, field_amp=0.05, q=0.01)
+    return PicSim(plasma, tile=(8, 8), precision="fp64", capacity_factor=4.0, options=L.PIC_OPT_TRACK, **kw)
+
+
+@pytest.mark.parametrize("bad", [0, 2])
+def test_backward_reports_a_rejected_origin(bad):
+    """One origin id of a checkpoint is out of range: the sweep leaves that
+    particle's adjoint out and reports it, whichever window it lies in."""
+    from paper_1906_06306_amd import _lib as L
+    from paper_1906_06306_amd import adjoint
+    sim = tracked()
+    ck = adjoint.forward(sim, 4, window=2)
+    E, B, _ = (t.clone() for t in sim.field_views())
+    sim.load_image(ck[bad])
+    sim.ids_view()[int(sim.particle_views()[3][3, 0])] = -1
+    sim.save_image(ck[bad])
+    assert sim.error() == 0
+    adjoint.backward(sim, ck, 4, E, B, window=2)
+    assert sim.error() == L.PIC_E_ADJ_MAP
+    assert sim.error() == 0                    # read once, then cleared
+    sim.close()
+
+
+def test_backward_reports_injected_particles():
+    """The reverse sweep does not cover creation: a particle injected before
+    the window has no place in the input."""
+    from paper_1906_06306_amd import _lib as L
+    from paper_1906_06306_amd import adjoint
+    sim = tracked(inject_max=64)
+    x = np.array([[3.25], [4.5]])
+    for s in range(2):
+        sim.inject(0, s, x, np.zeros((3, 1)))
+    ck = adjoint.forward(sim, 3, window=2)
+    E, B, _ = (t.clone() for t in sim.field_views())
+    assert sim.error() == 0
+    adjoint.backward(sim, ck, 3, E, B, window=2)
+    assert sim.error() == L.PIC_E_ADJ_MAP
+    sim.close()
+
+
+def test_loading_an_image_keeps_and_adds_error_bits():
+    from paper_1906_06306_amd import _lib as L
+    sim = tracked()
+    word = sim._view(sim.layout.off_error, 1, torch.int32)
+    clean = sim.save_image()
+    word.fill_(L.PIC_E_CFL >> 8)
+    flagged = sim.save_image()
+    sim.load_image(clean)
+    assert int(word) == L.PIC_E_CFL >> 8
+    word.fill_(L.PIC_E_CAPACITY >> 8)
+    sim.load_image(flagged)
+    assert sim.error() == L.PIC_E_CFL | L.PIC_E_CAPACITY
+    sim.close()
