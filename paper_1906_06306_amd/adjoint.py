@@ -44,11 +44,12 @@ def backward(sim: PicSim, ckpts: dict, nsteps: int, lE, lB, lpos=None, lu=None, 
 
     lE, lB: (3, cells_total) adjoints of E^N, B^{N-1/2}; lpos, lu: adjoints
     of the final particles in the final state's slots (zero if None).  The
-    simulation must hold the final state on entry.  Returns (lpos_in (D,
-    n_input), lu_in (3, n_input), lE0, lB0) in the working precision, the
-    particle adjoints in the concatenated input order.  Leaves the initial
-    state in the workspace, and every error bit that the sweep latched: with
-    one of them (``sim.error()``) the adjoints are not valid."""
+    simulation may hold any state on entry (for nsteps = 0 the final one).
+    Returns (lpos_in (D, n_input), lu_in (3, n_input), lE0, lB0) in the
+    working precision, the particle adjoints in the concatenated input order.
+    Leaves the initial state in the workspace, and every error bit that the
+    sweep latched: with one of them (``sim.error()``) the adjoints are not
+    valid."""
     fn = L.lib().pic_step
     la, ua, _, _ = sim.adjoint_buffers()
     lb, ub, _, _ = sim.adjoint_buffers()
@@ -58,14 +59,13 @@ def backward(sim: PicSim, ckpts: dict, nsteps: int, lE, lB, lpos=None, lu=None, 
     n_in = sim.n_input
     lpos_in = torch.zeros((sim.D, n_in), dtype=sim.dtype, device=sim.device)
     lu_in = torch.zeros((3, n_in), dtype=sim.dtype, device=sim.device)
-    # particle adjoints at the slots of the last state but one
-    last = (lpos_in, lu_in, n_in) if nsteps == 0 else (lb, ub, cap)
+    particles = lpos is not None or lu is not None
     if lpos is not None:
         la.copy_(lpos)
     if lu is not None:
         ua.copy_(lu)
-    if lpos is not None or lu is not None:
-        sim.unpermute(la, ua, *last)
+    if particles and nsteps == 0:
+        sim.unpermute(la, ua, lpos_in, lu_in, n_in)
     images = []                            # of the states inside a window
     for w0 in sorted((k for k in ckpts if k < nsteps), reverse=True):
         w1 = min(w0 + window, nsteps)
@@ -75,6 +75,13 @@ def backward(sim: PicSim, ckpts: dict, nsteps: int, lE, lB, lpos=None, lu=None, 
             if len(images) < j - w0:
                 images.append(sim.new_image())
             sim.save_image(images[j - w0 - 1])
+        if particles:
+            # to the slots of the state before the last step, by the origin
+            # ids of the state after it: that step is run again, since the
+            # workspace may hold any state on entry
+            L.check(fn(sim.ctx, STEP_FLAGS))
+            sim.unpermute(la, ua, lb, ub, cap)
+            particles = False
         for k in range(w1 - 1, w0 - 1, -1):
             state = ckpts[w0] if k == w0 else images[k - w0 - 1]
             out = (lpos_in, lu_in, n_in) if k == 0 else (la, ua, cap)
