@@ -39,9 +39,23 @@ def forward(sim: PicSim, nsteps: int, window: int = 8) -> dict:
     return ckpts
 
 
+def _load(sim: PicSim, ckpt) -> torch.Tensor:
+    """Load a checkpoint, keeping the error bits latched so far; its image."""
+    if isinstance(ckpt, torch.Tensor):
+        sim.load_image(ckpt)
+        return ckpt
+    word = sim.error_view()
+    bits = word.clone()
+    sim.restore(ckpt)
+    word |= bits
+    return sim.save_image()
+
+
 def backward(sim: PicSim, ckpts: dict, nsteps: int, lE, lB, lpos=None, lu=None, window: int = 8):
     """Adjoints of the initial state from those of the state after nsteps.
 
+    ckpts: {step: checkpoint} as from ``forward``, each a state image or a
+    ``PicSim.snapshot()``.
     lE, lB: (3, cells_total) adjoints of E^N, B^{N-1/2}; lpos, lu: adjoints
     of the final particles in the final state's slots (zero if None).  The
     simulation may hold any state on entry (for nsteps = 0 the final one).
@@ -69,7 +83,7 @@ def backward(sim: PicSim, ckpts: dict, nsteps: int, lE, lB, lpos=None, lu=None, 
     images = []                            # of the states inside a window
     for w0 in sorted((k for k in ckpts if k < nsteps), reverse=True):
         w1 = min(w0 + window, nsteps)
-        sim.load_image(ckpts[w0])
+        start = _load(sim, ckpts[w0])
         for j in range(w0 + 1, w1):
             L.check(fn(sim.ctx, STEP_FLAGS))
             if len(images) < j - w0:
@@ -83,13 +97,13 @@ def backward(sim: PicSim, ckpts: dict, nsteps: int, lE, lB, lpos=None, lu=None, 
             sim.unpermute(la, ua, lb, ub, cap)
             particles = False
         for k in range(w1 - 1, w0 - 1, -1):
-            state = ckpts[w0] if k == w0 else images[k - w0 - 1]
+            state = start if k == w0 else images[k - w0 - 1]
             out = (lpos_in, lu_in, n_in) if k == 0 else (la, ua, cap)
             sim.adjoint_reverse(state, lb, ub, lE, lB, *out)
             la, lb = lb, la
             ua, ub = ub, ua
-    if 0 in ckpts:
-        sim.load_image(ckpts[0])
+    if nsteps and 0 in ckpts:
+        sim.load_image(start)
     return lpos_in, lu_in, lE, lB
 
 

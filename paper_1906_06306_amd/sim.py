@@ -282,7 +282,10 @@ class PicSim:
         """Copy of the state regions of the workspace (see _state_ranges)."""
         return [self.ws[a:a + n].clone() for a, n in self._state_ranges()]
 
-    def restore(self, snap: list):
+    def restore(self, snap):
+        """The state of a snapshot() or of an image (save_image)."""
+        if isinstance(snap, torch.Tensor):
+            return self.load_image(snap)
         for (a, n), t in zip(self._state_ranges(), snap):
             self.ws[a:a + n].copy_(t)
 
@@ -359,6 +362,10 @@ class PicSim:
     def ids_host(self):
         torch.cuda.synchronize(self.device)
         return self.ids_view().cpu().numpy()
+
+    def error_view(self) -> torch.Tensor:
+        """The word of latched device error bits (int32), as a device view."""
+        return self._view(self.layout.off_error, 1, torch.int32)
 
     def error(self) -> int:
         code = L.lib().pic_error(self.ctx)

@@ -55,7 +55,7 @@ def test_backward_reports_injected_particles():
 def test_loading_an_image_keeps_and_adds_error_bits():
     from paper_1906_06306_amd import _lib as L
     sim = tracked()
-    word = sim._view(sim.layout.off_error, 1, torch.int32)
+    word = sim.error_view()
     clean = sim.save_image()
     word.fill_(L.PIC_E_CFL >> 8)
     flagged = sim.save_image()
