@@ -441,12 +441,13 @@ pic_status pic_adjoint_unpermute(pic_ctx *ctx, const void *lpos_after, const voi
 pic_status pic_adjoint_step(pic_ctx *ctx, void *lpos, void *lu, void *lE, void *lB);
 
 /* A copy of a tracked state between steps, for reversed windows: E, B,
- * segment counts, the error word and, of the particle planes and origin ids,
- * the slots in use.  pic_state_bytes gives the size of the caller's device
+ * segment and near-face counts, the error word and, of the particle planes
+ * and origin ids, the slots in use.  pic_state_bytes gives the size of the caller's device
  * buffer (256-byte aligned; its layout is private to a context's
  * configuration).  Both copies need PIC_OPT_TRACK and only enqueue work;
  * loading leaves the slots beyond the counts as they are and adds the image's
- * error bits to the latched ones, of which it clears none. */
+ * error bits to the latched ones, of which it clears none; the next
+ * diagnostics then have no continuity_max (-1). */
 pic_status pic_state_bytes(pic_ctx *ctx, uint64_t *bytes);
 pic_status pic_state_save(pic_ctx *ctx, void *image);
 pic_status pic_state_load(pic_ctx *ctx, const void *image);

@@ -834,16 +834,18 @@ struct Impl {
         return count_near_face(x);
     }
 
-    // offsets of a state image (pic_state_save): E, B, pos, u, counts, error, ids
-    static uint64_t image_offsets(pic_ctx *x, uint64_t off[7])
+    // offsets of a state image (pic_state_save): E, B, pos, u, counts, error,
+    // near-face counts, ids
+    static uint64_t image_offsets(pic_ctx *x, uint64_t off[8])
     {
         const pic_layout &P = x->L.pub;
-        const uint64_t bytes[7] = {3 * P.cells_total * sizeof(R),  3 * P.cells_total * sizeof(R),
+        const uint64_t nseg = P.tiles_total * x->ns;
+        const uint64_t bytes[8] = {3 * P.cells_total * sizeof(R),  3 * P.cells_total * sizeof(R),
                                    D * P.capacity_total * sizeof(R), 3 * P.capacity_total * sizeof(R),
-                                   P.tiles_total * x->ns * sizeof(int32_t), sizeof(int32_t),
+                                   nseg * sizeof(int32_t), sizeof(int32_t), nseg * sizeof(int32_t),
                                    P.capacity_total * sizeof(int32_t)};
         uint64_t o = 0;
-        for (int k = 0; k < 7; ++k) {
+        for (int k = 0; k < 8; ++k) {
             off[k] = o;
             o = align256(o + bytes[k]);
         }
@@ -852,25 +854,26 @@ struct Impl {
 
     static pic_status state_bytes(pic_ctx *x, uint64_t *out)
     {
-        uint64_t off[7];
+        uint64_t off[8];
         *out = image_offsets(x, off);
         return PIC_OK;
     }
 
     static pic::StateView<R> image_view(pic_ctx *x, const void *image)
     {
-        uint64_t o[7];
+        uint64_t o[8];
         image_offsets(x, o);
         uint8_t *b = static_cast<uint8_t *>(const_cast<void *>(image));
         return {reinterpret_cast<R *>(b + o[0]), reinterpret_cast<R *>(b + o[1]), reinterpret_cast<R *>(b + o[2]),
                 reinterpret_cast<R *>(b + o[3]), reinterpret_cast<int32_t *>(b + o[4]),
-                reinterpret_cast<int32_t *>(b + o[5]), reinterpret_cast<int32_t *>(b + o[6])};
+                reinterpret_cast<int32_t *>(b + o[5]), reinterpret_cast<int32_t *>(b + o[6]),
+                reinterpret_cast<int32_t *>(b + o[7])};
     }
 
     static pic_status state_copy(pic_ctx *x, void *image, bool save)
     {
         const Params<R> p = params<R>(x);
-        const pic::StateView<R> ws = {p.E, p.B, p.pos, p.u, p.seg_cnt, p.err, p.ids}, im = image_view(x, image);
+        const pic::StateView<R> ws = {p.E, p.B, p.pos, p.u, p.seg_cnt, p.err, p.nf_seg, p.ids}, im = image_view(x, image);
         const int32_t nseg = (int32_t)(x->L.pub.tiles_total * x->ns);
         const int64_t cells = x->L.pub.cells_total;
         const unsigned nf = (unsigned)std::min<int64_t>(std::max<int64_t>(1, (3 * cells + 1023) / 1024), 2048);
@@ -1595,7 +1598,9 @@ pic_status pic_state_save(pic_ctx *x, void *image)
 pic_status pic_state_load(pic_ctx *x, const void *image)
 {
     pic_status st = image_checks(x, image);
-    return st ? st : do_state_copy(x, const_cast<void *>(image), false);
+    if (st || (st = do_state_copy(x, const_cast<void *>(image), false))) return st;
+    x->diag_step = -1;   // the last diagnostics were of another state: no continuity from them
+    return PIC_OK;
 }
 
 pic_status pic_destroy(pic_ctx *x)

@@ -548,7 +548,7 @@ __global__ void __launch_bounds__(256) k_adj_fields(Params<R> p, AdjParams<R> a)
 template <typename R>
 struct StateView {
     R *E, *B, *pos, *u;
-    int32_t *seg_cnt, *err, *ids;
+    int32_t *seg_cnt, *err, *nf_seg, *ids;
 };
 
 // Copy a state: fields, counts, the error word, and of the particle planes
@@ -583,7 +583,10 @@ __global__ void __launch_bounds__(256) k_state_copy(StateView<R> dst, StateView<
     const int ts = blockIdx.x;
     const int64_t so = seg_off[ts];
     const int cnt = src.seg_cnt[ts];
-    if (threadIdx.x == 0) dst.seg_cnt[ts] = cnt;
+    if (threadIdx.x == 0) {
+        dst.seg_cnt[ts] = cnt;
+        dst.nf_seg[ts] = src.nf_seg[ts];
+    }
     // segments start at multiples of 64 slots and hold a multiple of 64
     for (int i = threadIdx.x * 4; i < cnt; i += blockDim.x * 4) {
         Quad v[D + 3];
