@@ -457,7 +457,7 @@ pic_status pic_state_load(pic_ctx *ctx, const void *image);
  * lpos, lu are read at the state's slots (and left as they are), the adjoints
  * of x^n, u^{n-1/2} go to lpos_before, lu_before ([dim|3][before_stride]) at
  * the slots the particles came from; lE, lB in place.  before_stride as in
- * pic_adjoint_unpermute. */
+ * pic_adjoint_unpermute.  PIC_E_ARG if the four particle buffers overlap. */
 pic_status pic_adjoint_reverse(pic_ctx *ctx, const void *image, void *lpos, void *lu, void *lE, void *lB,
                                void *lpos_before, void *lu_before, int64_t before_stride);
 

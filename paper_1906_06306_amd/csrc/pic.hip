@@ -1570,6 +1570,16 @@ pic_status pic_adjoint_reverse(pic_ctx *x, const void *image, void *lpos, void *
     if (st) return st;
     if (!lpos_before || !lu_before || before_stride < 1)
         return fail(PIC_E_ARG, "the adjoints' destination and a positive before_stride are required");
+    // tiles store to the destination while others still read lpos and lu
+    const uint64_t w = x->prec == PIC_FP64 ? 8 : 4, cap = (uint64_t)x->L.pub.capacity_total * w, out = (uint64_t)before_stride * w;
+    auto overlap = [](const void *a, uint64_t na, const void *b, uint64_t nb) {
+        const uint64_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+        return p < q + nb && q < p + na;
+    };
+    if (overlap(lpos, x->D * cap, lpos_before, x->D * out) || overlap(lpos, x->D * cap, lu_before, 3 * out) ||
+        overlap(lu, 3 * cap, lpos_before, x->D * out) || overlap(lu, 3 * cap, lu_before, 3 * out) ||
+        overlap(lpos_before, x->D * out, lu_before, 3 * out))
+        return fail(PIC_E_ARG, "the particle adjoints and their destination must not overlap");
     if (reinterpret_cast<uintptr_t>(image) & 255) return fail(PIC_E_ARG, "a state image must be 256-byte aligned");
     return do_adjoint(x, lpos, lu, lE, lB, image, lpos_before, lu_before, before_stride);
 }

@@ -297,15 +297,23 @@ class PicSim:
         off = (-buf.data_ptr()) % 256
         return buf[off:off + int(n.value)]
 
+    def _image_ptr(self, image: torch.Tensor) -> int:
+        n = ctypes.c_uint64()
+        L.check(L.lib().pic_state_bytes(self.ctx, ctypes.byref(n)))
+        if (image.dtype != torch.uint8 or not image.is_contiguous() or image.device != self.ws.device
+                or image.numel() < n.value):
+            raise L.PicError(L.PIC_E_ARG, f"a state image is a contiguous uint8 tensor of {n.value} bytes on {self.device}")
+        return image.data_ptr()
+
     def save_image(self, image: torch.Tensor | None = None) -> torch.Tensor:
         """The tracked state copied to an image: snapshot() without the slots
         beyond the counts."""
         image = self.new_image() if image is None else image
-        L.check(L.lib().pic_state_save(self.ctx, image.data_ptr()))
+        L.check(L.lib().pic_state_save(self.ctx, self._image_ptr(image)))
         return image
 
     def load_image(self, image: torch.Tensor):
-        L.check(L.lib().pic_state_load(self.ctx, image.data_ptr()))
+        L.check(L.lib().pic_state_load(self.ctx, self._image_ptr(image)))
 
     def adjoint_reverse(self, image, lpos, lu, lE, lB, lpos_before, lu_before, stride: int):
         """adjoint_step from the state in `image`, the particle adjoints
@@ -313,7 +321,7 @@ class PicSim:
         for t in (lpos, lu, lE, lB, lpos_before, lu_before):
             assert t.dtype == self.dtype and t.is_contiguous() and t.device == self.device
         assert lpos_before.shape[-1] == stride and lu_before.shape[-1] == stride
-        L.check(L.lib().pic_adjoint_reverse(self.ctx, image.data_ptr(), lpos.data_ptr(), lu.data_ptr(),
+        L.check(L.lib().pic_adjoint_reverse(self.ctx, self._image_ptr(image), lpos.data_ptr(), lu.data_ptr(),
                                             lE.data_ptr(), lB.data_ptr(), lpos_before.data_ptr(),
                                             lu_before.data_ptr(), int(stride)))
 
