@@ -17,6 +17,8 @@ from autograd.
 """
 from __future__ import annotations
 
+import contextlib
+
 import torch
 
 from . import _lib as L
@@ -25,17 +27,32 @@ from .sim import Box, PicSim
 STEP_FLAGS = L.PIC_FUSED | L.PIC_PUSH_HALF_B
 
 
+@contextlib.contextmanager
+def _sim_stream(sim: PicSim):
+    """torch's allocations, copies and fills on the simulation's stream, behind
+    the caller's work and ahead of the caller's next."""
+    cur = torch.cuda.current_stream(sim.device)
+    if cur == sim.stream:
+        yield
+        return
+    sim.stream.wait_stream(cur)
+    with torch.cuda.stream(sim.stream):
+        yield
+    cur.wait_stream(sim.stream)
+
+
 def forward(sim: PicSim, nsteps: int, window: int = 8) -> dict:
     """Run nsteps tracked fused steps; return {step: state image} at the
     window starts."""
     if not sim.cfg.options & L.PIC_OPT_TRACK:
         raise ValueError("the simulation needs options=PIC_OPT_TRACK")
     fn = L.lib().pic_step
-    ckpts = {0: sim.save_image()}
-    for k in range(nsteps):
-        L.check(fn(sim.ctx, STEP_FLAGS))
-        if (k + 1) % window == 0 and k + 1 < nsteps:
-            ckpts[k + 1] = sim.save_image()
+    with _sim_stream(sim):
+        ckpts = {0: sim.save_image()}
+        for k in range(nsteps):
+            L.check(fn(sim.ctx, STEP_FLAGS))
+            if (k + 1) % window == 0 and k + 1 < nsteps:
+                ckpts[k + 1] = sim.save_image()
     return ckpts
 
 
@@ -64,6 +81,14 @@ def backward(sim: PicSim, ckpts: dict, nsteps: int, lE, lB, lpos=None, lu=None, 
     Leaves the initial state in the workspace, and every error bit that the
     sweep latched: with one of them (``sim.error()``) the adjoints are not
     valid."""
+    with _sim_stream(sim):
+        out = _sweep(sim, ckpts, nsteps, lE, lB, lpos, lu, window)
+    for t in out:
+        t.record_stream(torch.cuda.current_stream(sim.device))
+    return out
+
+
+def _sweep(sim: PicSim, ckpts: dict, nsteps: int, lE, lB, lpos, lu, window: int):
     fn = L.lib().pic_step
     la, ua, _, _ = sim.adjoint_buffers()
     lb, ub, _, _ = sim.adjoint_buffers()

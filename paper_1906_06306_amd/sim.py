@@ -303,6 +303,10 @@ class PicSim:
         if (image.dtype != torch.uint8 or not image.is_contiguous() or image.device != self.ws.device
                 or image.numel() < n.value):
             raise L.PicError(L.PIC_E_ARG, f"a state image is a contiguous uint8 tensor of {n.value} bytes on {self.device}")
+        cur = torch.cuda.current_stream(self.device)
+        if cur != self.stream:                 # the library's stream reads or writes it
+            self.stream.wait_stream(cur)
+            image.record_stream(self.stream)
         return image.data_ptr()
 
     def save_image(self, image: torch.Tensor | None = None) -> torch.Tensor:
