@@ -562,7 +562,11 @@ k_push_persistent(Params<R> p)
 // the LDS serves together take quads 16 particles apart: particles sorted by
 // cell otherwise send whole waves to one address (512^2, 16 particles per cell
 // and species, sorted, FP32: 320 us with one particle per lane in order,
-// 87 us now).
+// 87 us now).  Two particles in 3D at FP64, where four need more than the 128
+// registers of a 1,024-thread group (26 spilled; 64x48x40, 16 particles per cell
+// and species, 4^3 tiles unsorted: 135 us with one particle per lane, 151 us with four,
+// 101 us with two; 8^3 tiles sorted 305, 139 and 109 us).  In 1D and 2D FP64 four
+// are better where particles are sorted (2D 8^2 tiles 70 us, 84 us with two).
 template <typename R, int D, typename A>
 __global__ void __launch_bounds__(1024) k_deposit(Params<R> p)
 {
@@ -581,12 +585,13 @@ __global__ void __launch_bounds__(1024) k_deposit(Params<R> p)
     const R q = p.charge[td.box * p.nspecies + s];
     const int lane = threadIdx.x & 63;
     const int quad = ((lane & 15) << 2) | (lane >> 4);
+    constexpr int NQ = D == 3 && sizeof(R) == 8 ? 2 : 4;
     // segments start at multiples of 64 slots and their capacities are
-    // multiples of 64: every quad of a count lies in its segment, aligned
+    // multiples of 64: every quad (or pair) of a count lies in its segment, aligned
     struct alignas(16) Quad {
-        R v[4];
+        R v[NQ];
     };
-    for (int i0 = ((threadIdx.x & ~63) + quad) * 4; i0 < cnt; i0 += blockDim.x * 4) {
+    for (int i0 = ((threadIdx.x & ~63) + quad) * NQ; i0 < cnt; i0 += blockDim.x * NQ) {
         Quad a[D], b[D], u[3];
 #pragma unroll
         for (int d = 0; d < D; ++d) {
@@ -596,7 +601,7 @@ __global__ void __launch_bounds__(1024) k_deposit(Params<R> p)
 #pragma unroll
         for (int m = 0; m < 3; ++m) u[m] = *reinterpret_cast<const Quad *>(p.u + m * cap + so + i0);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < NQ; ++j) {
             if (i0 + j >= cnt) break;
             R x1[3] = {0, 0, 0}, x2[3] = {0, 0, 0}, uu[3], dv[3], r;
 #pragma unroll

@@ -36,6 +36,7 @@ def kernels(tmp_path_factory):
 # a pattern of demangled names, how many instantiations match
 LEAN = [
     (r"k_state_copy<", 6),
+    (r"k_deposit<", 9),
 ]
 
 
