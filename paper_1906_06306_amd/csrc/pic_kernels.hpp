@@ -539,8 +539,12 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(push_
 // Persistent walker: a grid sized to the resident work-groups pulls
 // segments (largest first) from an atomic counter until every one is taken;
 // every work-group leaves the loop when the counter passes the segment count.
+// With walls it is compiled for 4 waves: the loop's own registers make it spill
+// 17 at k_push's bound for 8^3 FP32 tiles (step of a 256x64x64 box of 8 particles
+// per cell and species: 503 us, 474 us at 4 waves).  Without walls 2 spill there
+// and the added waves are worth them (461 us, 467 us at 4 waves).
 template <typename R, int D, bool FUSED, bool HALFB, typename A, int TC, bool WALLS, int PUSHER>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(push_waves<R, D, TC>(), 8)))
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(WALLS ? 4 : push_waves<R, D, TC>(), 8)))
 k_push_persistent(Params<R> p)
 {
     extern __shared__ __align__(16) unsigned char smem[];

@@ -37,6 +37,8 @@ def kernels(tmp_path_factory):
 LEAN = [
     (r"k_state_copy<", 6),
     (r"k_deposit<", 9),
+    (r"k_push<float, 3, true, \w+, long long, 8, ", 4),                   # the 3D shock's tiles
+    (r"k_push_persistent<float, 3, true, \w+, long long, 8, true, ", 2),
 ]
 
 
