@@ -243,10 +243,11 @@ def run_gpu(plasma, args, precision, steps, warmup, tile, block=256, profile_onl
     step()
     diag = sim.diagnostics()
     diag["max_segment_fill"] = sim.fill_ratio()
+    push_threads = sim.push_threads()
     sim.close()
     del sim
     torch.cuda.empty_cache()
-    return dict(seconds=dt, push_ms=push_ms, diag=diag, later=later, clock=clock)
+    return dict(seconds=dt, push_ms=push_ms, push_threads=push_threads, diag=diag, later=later, clock=clock)
 
 
 def valu_roofline(key_hash, prec, tile, args, n_p, push_ms):
@@ -613,10 +614,11 @@ def bench_shock(args):
         dt = time.perf_counter() - t1
         push_ms = float(np.mean([a.elapsed_time(b) for a, b in evs]))
         diag = sim.diagnostics()
+        push_threads = sim.push_threads()
         sim.close()
         del sim
         torch.cuda.empty_cache()
-        results[name] = dict(seconds=dt, push_ms=push_ms, diag=diag, block=blk)
+        results[name] = dict(seconds=dt, push_ms=push_ms, diag=diag, block=blk, push_threads=push_threads)
         log(f"{name}: {dt / args.steps * 1e3:.3f} ms/step, push {push_ms:.3f} ms, status {diag['status']}")
     for k, v in results.items():
         if v["diag"]["status"] != 0:
@@ -640,7 +642,7 @@ def bench_shock(args):
                      "push_ms": r["push_ms"], "algorithmic_bytes_per_launch": pb},
         "step_roofline_frac": algorithmic_bytes(D, 4, n_p, n_c) * value / n_p / 1e9 / HBM_PEAK_GBS,
         "ms_per_step_by_run": {k: v["seconds"] / args.steps * 1e3 for k, v in results.items()},
-        "block": r["block"],
+        "block": r["block"], "push_threads": r["push_threads"],
         "status": {k: v["diag"]["status"] for k, v in results.items()},
     }
     print(json.dumps(out), flush=True)
@@ -902,6 +904,7 @@ def main():
                                f"{args.ppc} ppc/species pair plasma, "
                                "theta=0.3, sigma=10, dB/B0=1 (64 modes), c/w_p=3 cells, Courant 0.45",
                    "particles": n_p, "cells": n_c, "tile": tile32, "block": blk32,
+                   "push_threads": r32["push_threads"],
                    "pusher": args.pusher, "filter_passes": args.filter_passes, "fdtd_order": args.fdtd_order,
                    "autotune_ms_per_step": tune32},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -934,7 +937,8 @@ def main():
                                          "frac": a64 / HBM_PEAK_GBS, "algorithmic_bytes_per_launch": pb64,
                                          "traffic": MEASURED_PUSH_TRAFFIC.get((kernel_source_hash(), "fp64", tile64,
                                                                                args.n, args.ppc))},
-                       "tile": tile64, "block": blk64, "autotune_ms_per_step": tune64,
+                       "tile": tile64, "block": blk64, "push_threads": r64["push_threads"],
+                       "autotune_ms_per_step": tune64,
                        "gauss_max": r64["diag"]["gauss_max"], "continuity_max": r64["diag"]["continuity_max"],
                        "status": r64["diag"]["status"],
                        "vs_oracle_1step_rel_l2": err64,

@@ -114,9 +114,13 @@ typedef struct {
                              every box; 1 for dimensions >= dim             */
     int32_t block;        /* threads per work-group of particle kernels
                              (64..1024, multiple of 64); 0 = default 256.
-                             The push takes 2, 4, ... times as many (up to
-                             1024) where the segments are too few to fill
-                             the device (same results; FP64 to rounding)    */
+                             The push takes more where that puts more waves
+                             on a CU, because the segments are few or LDS is
+                             the limit: block doubled while below 256, then
+                             a multiple of 256 up to 1024 (same results; FP64
+                             to rounding).  pic_push_threads
+                             tells what it takes, PIC_OPT_EXACT_BLOCK keeps
+                             it at block                                    */
     double cfl;           /* Courant number c, 0 < c <= 1/sqrt(D)           */
     const int32_t *box_cells;   /* host [n_boxes][3] cells per dimension     */
     const double *charge;       /* host [n_boxes][n_species] q (signed)      */
@@ -188,6 +192,9 @@ typedef struct {
  * With it, pic_push_interp requires PIC_FUSED and PIC_SORT_CELLS is
  * rejected (neither path records origins). */
 #define PIC_OPT_TRACK 4u
+/* pic_config.options: the push takes exactly pic_config.block threads per
+ * work-group. */
+#define PIC_OPT_EXACT_BLOCK 8u
 
 /* Byte offsets of the regions inside the caller's workspace.  Fields:
  * [3][cells_total] each, boxes concatenated (box b starts at cell offset
@@ -300,6 +307,10 @@ pic_status pic_fdtd_step(pic_ctx *ctx, int32_t phase);
  * (App. D) and compacts the particles that stay, moving leavers to the
  * segment's outbox (the "tag outflowing / pack" rows of Table 1). */
 pic_status pic_push_interp(pic_ctx *ctx, uint32_t species_mask, uint32_t flags);
+
+/* Threads per work-group of the context's pushes with PIC_FUSED in flags, or
+ * without it; 0 before the first of them (see pic_config.block). */
+pic_status pic_push_threads(pic_ctx *ctx, uint32_t flags, int32_t *threads);
 
 /* comp_curr + clear_vir_cur + cur_exchange for the species in species_mask
  * (each pushed in this step): after an unfused push, ZigZag

@@ -32,12 +32,13 @@ PIC_ALL_SPECIES = 0xFFFFFFFF
 PIC_OPT_ACC_WORKING = 1
 PIC_OPT_PERSISTENT = 2
 PIC_OPT_TRACK = 4
+PIC_OPT_EXACT_BLOCK = 8
 PIC_WALL_X = 1
 PIC_PUSHER_BORIS = 0
 PIC_PUSHER_VAY = 1
 PIC_PUSHER_HC = 2
 
-EXPORTS = ["pic_query", "pic_init_tiles", "pic_fdtd_step", "pic_push_interp", "pic_deposit_current",
+EXPORTS = ["pic_query", "pic_init_tiles", "pic_fdtd_step", "pic_push_interp", "pic_push_threads", "pic_deposit_current",
            "pic_sort_migrate", "pic_step", "pic_inject", "pic_filter_current", "pic_graph_capture", "pic_graph_launch", "pic_error",
            "pic_diagnostics", "pic_diagnostics_static", "pic_diagnostics_boxes", "pic_adjoint_unpermute", "pic_adjoint_step",
            "pic_adjoint_reverse", "pic_state_bytes", "pic_state_save", "pic_state_load", "pic_destroy", "pic_last_error"]
@@ -103,6 +104,7 @@ def lib():
             "pic_init_tiles": [P, P, P, U64, P, P, P],
             "pic_fdtd_step": [P, I32],
             "pic_push_interp": [P, U32, U32],
+            "pic_push_threads": [P, U32, P],
             "pic_deposit_current": [P, U32, U32],
             "pic_sort_migrate": [P, U32, P, P, I64],
             "pic_step": [P, U32],

@@ -47,7 +47,11 @@ def candidates(plasma, elem: int):
 
 def tune(plasma, precision: str = "fp32", blocks=(256,), capacity_factor: float = 2.0, steps: int = 4,
          log=None):
-    """Return (best (T, block), {(T, block): seconds per step})."""
+    """Return (best (T, block), {(T, block): seconds per step}).
+
+    A block from which the library's push takes as many threads as from one
+    already timed with the same tile runs the same step: it shares that time
+    (of such blocks the first listed is returned)."""
     elem = 8 if precision == "fp64" else 4
     edges = candidates(plasma, elem)
     if not edges:
@@ -55,15 +59,19 @@ def tune(plasma, precision: str = "fp32", blocks=(256,), capacity_factor: float 
                          "and fits the LDS; give the tile explicitly")
     results = {}
     for T in edges:
+        timed = {}                     # threads of the push -> seconds per step
         for blk in blocks:
             sim = PicSim(plasma, tile=(T,) * plasma.D, precision=precision, block=blk,
                          capacity_factor=capacity_factor)
-            sec = time_step(sim, steps=steps)
+            sim.step(1, half_b_in_push=True)
+            n = sim.push_threads()
+            if n not in timed:
+                timed[n] = time_step(sim, steps=steps)
             sim.close()
             del sim
             torch.cuda.empty_cache()
-            results[(T, blk)] = sec
+            results[(T, blk)] = timed[n]
             if log:
-                log(f"autotune {precision} T={T} block={blk}: {sec * 1e3:.3f} ms/step")
+                log(f"autotune {precision} T={T} block={blk} (push {n}): {timed[n] * 1e3:.3f} ms/step")
     best = min(results, key=results.get)
     return best, results

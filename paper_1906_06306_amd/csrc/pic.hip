@@ -305,6 +305,7 @@ struct pic_ctx {
     bool acc_working;   // LDS current block in the working precision
     bool persistent;    // push as a persistent tile walker
     bool track;         // origin tracking and adjoint scratch present
+    bool exact_block;   // the push takes block threads, not choose_group's
     bool walls;         // some box has conducting walls in x
     int pusher;         // PIC_PUSHER_*
     int filter_passes;  // binomial passes pic_step applies to J
@@ -486,21 +487,23 @@ struct Impl {
         return PIC_OK;
     }
 
-    // Threads per work-group of the push: the configured block, or a multiple of
-    // it (to 1,024) where that puts more waves on a CU.  A CU holds few groups when
-    // the launch has few segments or LDS limits it; a larger group then fills
+    // Threads per work-group of the push: the configured block, or more where that
+    // puts more waves on a CU (the block doubled while below 256, then multiples
+    // of 256 to 1,024; PIC_OPT_EXACT_BLOCK keeps the block).  A CU holds few groups
+    // when the launch has few segments or LDS limits it; a larger group then fills
     // it (each group takes whole segments, so nothing else can).  Of equal
-    // wave counts the larger group where every segment is resident at once
-    // (the largest segment ends the launch, and ends sooner), else the smaller
-    // (fewer waves meet at the barrier of each group).  Step with the block of
-    // 256 threads against the choice: 2D 256^2 FP32 (512 segments) 50.4 and
+    // wave counts the larger group where the segments take at most two rounds of
+    // resident groups (the largest segment ends the launch, and ends sooner), else
+    // the smaller (fewer waves meet at the barrier of each group).  Step with the
+    // block of 256 threads against the choice: 2D 256^2 FP32 (512 segments) 50.4 and
     // 46.9 us with 512; five steps and diagnostics of 512x384 (1,536 segments)
     // 615 and 606 us with 512; 3D FP64 box (480 segments, one group per CU)
     // 107.6 and 83.8 us with 1024; 512^2 FP64 with a block of 128 232 and 215 us
     // with 256.  1024^2 FP32 (8,192 segments) keeps 256: 512 takes 465 against
     // 451 us.
     // No larger than the particles a segment starts with (1D, 384 segments of 192
-    // particles, FP32: push 7.7 us with 256 threads, 10.5 us with 1,024).
+    // particles, FP32: push 7.7 us with 256 threads, 10.5 us with 1,024).  The host
+    // knows only the counts at init: a run filled by injection keeps its block.
     // Three times 256 only where it fills a CU that the LDS leaves short of waves
     // (two groups of 8^3 FP32 tiles, 24 waves against 16: shock of 256x64x64 732
     // and 705 us); of few segments it would take room that other streams' launches
@@ -510,6 +513,10 @@ struct Impl {
     static pic_status choose_group(pic_ctx *x, K kern, size_t lds, int64_t items, int &group)
     {
         if (group) return PIC_OK;
+        if (x->exact_block) {
+            group = x->block;
+            return PIC_OK;
+        }
         int best = x->block;
         int64_t best_waves = 0, most = 0;
         for (int g = x->block; g <= 1024; g = g < 256 ? 2 * g : (g / 256 + 1) * 256) {
@@ -517,11 +524,11 @@ struct Impl {
             HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(kern), g, lds));
             const int64_t resident = std::max(per_cu, 1);
             const int64_t waves = std::min(resident, (items + x->n_cu - 1) / x->n_cu) * (g / 64);
-            const bool one_round = items <= resident * x->n_cu * 2;
+            const bool two_rounds = items <= resident * x->n_cu * 2;
             const bool odd = (g & (g - 1)) && g != x->block && resident * (g / 64) <= most;
             most = std::max(most, resident * (g / 64));
             if (g > x->block && (int64_t)g * items > x->L.n_input) break;
-            if (per_cu > 0 && !odd && (waves > best_waves || (waves == best_waves && one_round))) {
+            if (per_cu > 0 && !odd && (waves > best_waves || (waves == best_waves && two_rounds))) {
                 best = g;
                 best_waves = waves;
             }
@@ -1221,6 +1228,7 @@ pic_status pic_init_tiles(const pic_config *cfg, const int64_t *counts, void *wo
     x->acc_working = (cfg->options & PIC_OPT_ACC_WORKING) != 0;
     x->persistent = (cfg->options & PIC_OPT_PERSISTENT) != 0;
     x->track = (cfg->options & PIC_OPT_TRACK) != 0;
+    x->exact_block = (cfg->options & PIC_OPT_EXACT_BLOCK) != 0;
     x->walls = false;
     x->pusher = cfg->pusher;
     x->filter_passes = cfg->filter_passes;
@@ -1324,6 +1332,13 @@ pic_status pic_push_interp(pic_ctx *x, uint32_t species_mask, uint32_t flags)
     if (st) return st;
     x->pushed |= mask;
     x->state = fused ? 2 : 1;
+    return PIC_OK;
+}
+
+pic_status pic_push_threads(pic_ctx *x, uint32_t flags, int32_t *threads)
+{
+    if (!x || !threads) return fail(PIC_E_ARG, "null argument");
+    *threads = x->push_group[(flags & PIC_FUSED) != 0];
     return PIC_OK;
 }
 

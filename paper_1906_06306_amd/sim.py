@@ -181,6 +181,13 @@ class PicSim:
         flags = (L.PIC_FUSED if fused else 0) | (L.PIC_PUSH_HALF_B if half_b else 0)
         L.check(L.lib().pic_push_interp(self.ctx, self._mask(species), flags))
 
+    def push_threads(self, fused: bool = True) -> int:
+        """Threads per work-group that the push takes for this block (0 before
+        the first one): `block` or more, or `block` with PIC_OPT_EXACT_BLOCK."""
+        n = ctypes.c_int32()
+        L.check(L.lib().pic_push_threads(self.ctx, L.PIC_FUSED if fused else 0, ctypes.byref(n)))
+        return n.value
+
     @staticmethod
     def _mask(species) -> int:
         if species is None:
