@@ -38,7 +38,9 @@
  * pic_layout.total_bytes (256-byte aligned) and owns it; the library never
  * allocates or frees device memory.  Every region (fields, particles, tile
  * tables, staging) is at the offsets pic_query() reports.  The library owns
- * only the host-side context.
+ * only the host-side context, and with it, from the first pic_diagnostics or
+ * pic_diagnostics_boxes until pic_destroy, 64 bytes of page-locked host memory
+ * per tile (plain memory per call where page-locking is refused).
  *
  * Streams: a context is bound to one HIP stream; every call except
  * pic_query, pic_error, pic_diagnostics and pic_destroy only enqueues work.

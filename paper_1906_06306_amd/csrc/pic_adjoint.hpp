@@ -17,7 +17,7 @@ namespace pic {
 
 // ------------------------------------------------------ ZigZag adjoint
 
-// Value j of one component of a straight segment (segment_values) is F w; its
+// Value j of one component of a straight segment (segment_weights) is F w; its
 // derivatives are dF w along the component and F da, F db along the NT
 // transverse grid dimensions a (and b).  i = 0, 1: with respect to x1, x2.
 template <typename R, int NT>
@@ -78,8 +78,9 @@ struct SegmentGrad {
 // 2D + (3 - D) parts: 1,545 vector instructions per 64 particles of the 2D FP32
 // kernel, 193 registers, 186 us per step of a shear layer of 256^2 cells, 32
 // particles each; this: 1,125, 110 and 142 us).  Multiply-adds are written out and
-// nothing else is contracted: the results are those of the dual numbers, bit
-// for bit.
+// nothing else is contracted: in 1D and 2D the results are those of the dual
+// numbers, bit for bit, in 3D FP32 as near to the FP64 ones (2.50e-7 relative
+// for the position adjoints of 32x32x24 cells with either).
 template <typename R, int D, typename LA>
 __device__ __forceinline__ void zigzag_adjoint(const LA *sLJ, const Strides st, const int32_t T[3], const R x1[3],
                                                const R x2[3], const R dv[3], R q, R lx1[3], R lx2[3], R ldv[3])
@@ -178,7 +179,7 @@ __device__ __forceinline__ void zigzag_adjoint(const LA *sLJ, const Strides st, 
 
 // Value, gradient with respect to the particle position, and (with SCATTER)
 // the scatter lam * weight into the FP64 adjoint block L of one
-// staggered component (same stencil as interp_comp).
+// staggered component (same stencil as interp_at).
 template <typename R, int D, int COMP, bool SCATTER>
 __device__ __forceinline__ R interp_comp_adj(const R *__restrict__ F, double *L, int s1, int s2,
                                              const Stencil<R, D> &st, R lam, R g[3])

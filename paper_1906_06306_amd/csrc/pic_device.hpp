@@ -668,45 +668,7 @@ __host__ __device__ constexpr int seg_values()
     return D == 1 ? 5 : (D == 2 ? 8 : 12);
 }
 
-template <typename R, int D>
-__device__ __forceinline__ void segment_values(const R F[3], const R W[3], const R dv[3], R v[seg_values<D>()])
-{
-    if constexpr (D == 1) {
-        v[0] = F[0];
-        v[1] = F[1] * (R(1) - W[0]);
-        v[2] = F[1] * W[0];
-        v[3] = F[2] * (R(1) - W[0]);
-        v[4] = F[2] * W[0];
-    } else if constexpr (D == 2) {
-        v[0] = F[0] * (R(1) - W[1]);
-        v[1] = F[0] * W[1];
-        v[2] = F[1] * (R(1) - W[0]);
-        v[3] = F[1] * W[0];
-        const R cr = dv[0] * dv[1] * R(1.0 / 12.0);
-        v[4] = F[2] * ((R(1) - W[0]) * (R(1) - W[1]) + cr);
-        v[5] = F[2] * (W[0] * (R(1) - W[1]) - cr);
-        v[6] = F[2] * ((R(1) - W[0]) * W[1] - cr);
-        v[7] = F[2] * (W[0] * W[1] + cr);
-    } else {
-        const R cyz = dv[1] * dv[2] * R(1.0 / 12.0);
-        v[0] = F[0] * ((R(1) - W[1]) * (R(1) - W[2]) + cyz);
-        v[1] = F[0] * (W[1] * (R(1) - W[2]) - cyz);
-        v[2] = F[0] * ((R(1) - W[1]) * W[2] - cyz);
-        v[3] = F[0] * (W[1] * W[2] + cyz);
-        const R cxz = dv[0] * dv[2] * R(1.0 / 12.0);
-        v[4] = F[1] * ((R(1) - W[0]) * (R(1) - W[2]) + cxz);
-        v[5] = F[1] * (W[0] * (R(1) - W[2]) - cxz);
-        v[6] = F[1] * ((R(1) - W[0]) * W[2] - cxz);
-        v[7] = F[1] * (W[0] * W[2] + cxz);
-        const R cxy = dv[0] * dv[1] * R(1.0 / 12.0);
-        v[8] = F[2] * ((R(1) - W[0]) * (R(1) - W[1]) + cxy);
-        v[9] = F[2] * (W[0] * (R(1) - W[1]) - cxy);
-        v[10] = F[2] * ((R(1) - W[0]) * W[1] - cxy);
-        v[11] = F[2] * (W[0] * W[1] + cxy);
-    }
-}
-
-// The same values as flux component times weight: value k is
+// The values as flux component times weight: value k is
 // F[seg_comp<D>(k)] * wt[k].
 template <int D>
 __host__ __device__ constexpr int seg_comp(int k)
