@@ -500,7 +500,11 @@ struct Impl {
     // 615 and 606 us with 512; 3D FP64 box (480 segments, one group per CU)
     // 107.6 and 83.8 us with 1024; 512^2 FP64 with a block of 128 232 and 215 us
     // with 256.  1024^2 FP32 (8,192 segments) keeps 256: 512 takes 465 against
-    // 451 us.
+    // 451 us.  Where there are more rounds, only from half as many waves again: fewer
+    // do not pay for the barriers and for the last, part-filled group of each
+    // segment (3D FP64, 6^3 tiles of 1,080 particles, 128 registers: 996 us with 12
+    // waves of 256 threads, 1,091 us with 16 of 512; of 2,160: 826 and 864 us; 2D 20x24
+    // tiles alike, 604 and 600 us).
     // No larger than the particles a segment starts with (1D, 384 segments of 192
     // particles, FP32: push 7.7 us with 256 threads, 10.5 us with 1,024).  The host
     // knows only the counts at init: a run filled by injection keeps its block.
@@ -518,7 +522,7 @@ struct Impl {
             return PIC_OK;
         }
         int best = x->block;
-        int64_t best_waves = 0, most = 0;
+        int64_t best_waves = 0, block_waves = 0, most = 0;
         for (int g = x->block; g <= 1024; g = g < 256 ? 2 * g : (g / 256 + 1) * 256) {
             int per_cu = 0;
             HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(kern), g, lds));
@@ -528,6 +532,8 @@ struct Impl {
             const bool odd = (g & (g - 1)) && g != x->block && resident * (g / 64) <= most;
             most = std::max(most, resident * (g / 64));
             if (g > x->block && (int64_t)g * items > x->L.n_input) break;
+            if (g == x->block) block_waves = waves;
+            if (g > x->block && !two_rounds && 2 * waves < 3 * block_waves) continue;
             if (per_cu > 0 && !odd && (waves > best_waves || (waves == best_waves && two_rounds))) {
                 best = g;
                 best_waves = waves;

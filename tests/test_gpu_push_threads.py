@@ -40,3 +40,17 @@ def test_exact_block(D, n, T, ppc, prec, persistent):
     for other in got[:2]:
         for a, b in zip(other, got[2], strict=True):
             assert np.abs(a - b).max() <= tol * max(1.0, np.abs(b).max())
+
+
+@pytest.mark.parametrize("T,raised", [((6, 6, 6), False), ((8, 8, 8), True)])
+def test_many_segments_keep_the_block_unless_waves_grow_by_half(T, raised):
+    """FP64, more segments than two rounds of resident groups: 6^3 tiles hold
+    12 waves of 256 threads on a CU and 16 of 512, 8^3 tiles 4 and 16."""
+    from paper_1906_06306_amd.sim import PicSim
+    n = tuple(12 * t for t in T)
+    sim = PicSim(synth.small_random(3, n, 5, theta=0.3, seed=2), tile=T, precision="fp64", block=256,
+                 capacity_factor=1.6)
+    sim.step(1, half_b_in_push=True)
+    assert (sim.push_threads() > 256) == raised
+    assert sim.error() == 0
+    sim.close()
