@@ -435,8 +435,13 @@ pic_status fill(pic_ctx *x, T *p, int64_t n, T v)
 
 template <typename R, int D>
 struct Impl {
-    // LDS of the push (layout: push_tile), and the choice of the layout for
-    // tiles with runtime edges: the interleaved rows unless they do not fit
+    // LDS of the push (layout: push_tile), and for tiles with runtime edges the
+    // choice of the layout: the first of interleaved rows with the direction
+    // codes in LDS, the rows (planes in 3D) with the codes in memory, and one
+    // plane per component, that leaves a CU as many work-groups as the last,
+    // which is the smallest.  2D, 12 particles per cell and species: FP64 tiles of
+    // 26x36, rows (one group) 655 us, planes (two) 610 us; FP32 of 38x38, rows with codes
+    // 390 us, without (two) 343 us.
     template <int TC>
     static size_t push_lds(pic_ctx *x, Params<R> &p, bool fused, size_t acc_bytes)
     {
@@ -446,11 +451,19 @@ struct Impl {
         const size_t tail = fused ? pic::push_lds_tail<D, true>() : pic::push_lds_tail<D, false>();
         const size_t cur = fused ? 3 * e0 * rows * acc_bytes : 0;
         const size_t planes = (3 * e0 * rows + 3 * fbn) * sizeof(R) + cur + tail;
-        const size_t bytes = (D == 3 ? planes : 6 * e0 * rows * sizeof(R) + cur + tail) + (fused ? pic::dir_lds<D>() : 0);
+        const size_t codes = fused ? pic::dir_lds<D>() : 0;
+        const size_t lean = D == 3 ? planes : 6 * e0 * rows * sizeof(R) + cur + tail;
+        // work-groups of the configured block that fit the LDS, which is handed
+        // out in steps of 1,280 bytes, and the 32 waves of a CU
+        auto groups = [&](size_t bytes) {
+            return std::min<size_t>(160 * 1024 / ((bytes + 1279) / 1280 * 1280), 32 * 64 / x->block);
+        };
+        const size_t most = groups(planes);
         p.dir_lds = pic::dir_lds<D>();
         p.lds_planes = 0;
-        if (TC > 0 || bytes <= 160 * 1024) return bytes;
+        if (TC > 0 || (most > 0 && groups(lean + codes) >= most)) return lean + codes;
         p.dir_lds = 0;
+        if (most > 0 && groups(lean) >= most) return lean;
         p.lds_planes = 1;
         return planes;
     }

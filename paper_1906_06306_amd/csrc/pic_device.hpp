@@ -66,7 +66,7 @@ struct Params {
     int32_t *ob_boff;         // [tile*species][ncodes+1] outbox bucket starts by direction code
     int32_t *ob_idx;          // [tile*species][ob_cap] outbox slots in bucket order
     int32_t lds_planes;       // the push keeps E and B in LDS as planes of their own (tiles
-                              // whose interleaved rows would not fit), see FieldLds
+                              // whose interleaved rows cost a work-group), see FieldLds
     int32_t dir_lds;          // leavers whose direction code the push keeps in LDS
     R *bnext;                 // [3][cells_total] B after both half updates (whole step), or null
 };
@@ -283,7 +283,7 @@ struct CurBox {
 // lies beyond those offsets in any case, and rows of 66 elements map an 8 x 8
 // plane of cells, which an ordered plasma keeps in one wave, onto few banks (8^3
 // tiles, FP32, walls: push 611 us with rows, 587 us with planes).  Planes
-// also in 2D tiles whose rows would not fit the 160 KB of LDS.
+// also in 1D and 2D tiles where the larger rows would cost a CU a work-group.
 template <int D>
 struct FieldLds {
     Strides e, b;
