@@ -59,19 +59,20 @@ def tune(plasma, precision: str = "fp32", blocks=(256,), capacity_factor: float 
                          "and fits the LDS; give the tile explicitly")
     results = {}
     for T in edges:
-        timed = {}                     # threads of the push -> seconds per step
+        threads = {}                   # block -> threads of its push
         for blk in blocks:
             sim = PicSim(plasma, tile=(T,) * plasma.D, precision=precision, block=blk,
                          capacity_factor=capacity_factor)
-            sim.step(1, half_b_in_push=True)
-            n = sim.push_threads()
-            if n not in timed:
-                timed[n] = time_step(sim, steps=steps)
+            results[(T, blk)] = time_step(sim, steps=steps)
+            threads[blk] = sim.push_threads()
             sim.close()
             del sim
             torch.cuda.empty_cache()
-            results[(T, blk)] = timed[n]
             if log:
-                log(f"autotune {precision} T={T} block={blk} (push {n}): {timed[n] * 1e3:.3f} ms/step")
+                log(f"autotune {precision} T={T} block={blk} (push {threads[blk]}): "
+                    f"{results[(T, blk)] * 1e3:.3f} ms/step")
+        times = {blk: results[(T, blk)] for blk in blocks}
+        for blk in blocks:
+            results[(T, blk)] = min(times[b] for b in blocks if threads[b] == threads[blk])
     best = min(results, key=results.get)
     return best, results
