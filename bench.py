@@ -37,9 +37,9 @@ METRIC = "particle-steps/sec (push+deposit+FDTD) FP32 vs FP64 at 1 GPU; % HBM ro
 # contents without comments), precision, tile edge, cells per side and
 # particles per cell: any other kernel code reports no traffic.
 MEASURED_PUSH_TRAFFIC = {
-    ("78bcdb30f7e1fc3e", "fp32", 16, 1024, 16): 1654027904,
-    ("78bcdb30f7e1fc3e", "fp32", 32, 1024, 16): 1543251135,
-    ("78bcdb30f7e1fc3e", "fp64", 16, 1024, 16): 3154948140,
+    ("58995d5c4cae7ffe", "fp32", 16, 1024, 16): 1653116970,
+    ("58995d5c4cae7ffe", "fp32", 32, 1024, 16): 1543774344,
+    ("58995d5c4cae7ffe", "fp64", 16, 1024, 16): 3154351662,
 }
 
 # wave64 VALU instructions per 64 particles of the same push, from rocprofv3
@@ -47,9 +47,9 @@ MEASURED_PUSH_TRAFFIC = {
 # chip's VALU issue peak: 256 CUs x 4 SIMDs, one wave64 instruction per 4
 # clocks per SIMD (16 lanes; FP32 not packed) at 2.4 GHz
 MEASURED_PUSH_VALU_PER_64 = {
-    ("78bcdb30f7e1fc3e", "fp32", 16, 1024, 16): 341.5,
-    ("78bcdb30f7e1fc3e", "fp32", 32, 1024, 16): 338.2,
-    ("78bcdb30f7e1fc3e", "fp64", 16, 1024, 16): 388.7,
+    ("58995d5c4cae7ffe", "fp32", 16, 1024, 16): 341.5,
+    ("58995d5c4cae7ffe", "fp32", 32, 1024, 16): 338.2,
+    ("58995d5c4cae7ffe", "fp64", 16, 1024, 16): 388.7,
 }
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4
 
@@ -92,7 +92,8 @@ def parse():
     ap.add_argument("--ppc", type=int, default=16, help="particles per cell per species")
     ap.add_argument("--tile", default="auto", help="tile edge, or 'auto' (autotuner over 8/16/32)")
     ap.add_argument("--block", type=int, default=0,
-                    help="work-group size of the particle kernels; 0: the autotuner picks 128, 256 or 512 "
+                    help="work-group size of the particle kernels (the push may take more: push_threads); "
+                         "0: the autotuner picks 128, 256 or 512 "
                          "(256 when the tile is given)")
     ap.add_argument("--no-fp64", action="store_true")
     ap.add_argument("--no-cpu", action="store_true")
